@@ -191,8 +191,8 @@ msc_status msc_bdf2_step(msc_ctx* c, int32_t nsteps, msc_step_stats* stats);
  * same collision and streaming).  With periodic boundaries and FP64 or FP32
  * storage the march runs in place by the AA access pattern (pairs of steps on
  * one population array; an odd count ends with one step of the two-buffer
- * sweep), otherwise on the two-buffer sweep; both give identical results
- * (msc_set_tuning key 10).  Resets the BDF history: the next
+ * sweep) and in 2D several steps per launch, otherwise on the two-buffer
+ * sweep; all give identical results (msc_set_tuning key 10).  Resets the BDF history: the next
  * msc_bdf2_step is BDF1 from the current state with m^n = P f^n.
  * Errors: MSC_ERR_INVALID_ARG (nsteps < 0); MSC_ERR_NONFINITE when the final
  * state holds a non-finite value (checked once at the end). */
@@ -331,8 +331,8 @@ msc_status msc_kernel_time(msc_ctx* c, int32_t kind, double* seconds, int64_t* l
  * corrector's column pass as three kernels (x transforms, per-wavevector
  * solve, inverse transforms): 0 = automatic (split from N_x = 512), 1 =
  * split, 2 = one fused kernel, 10 = march msc_explicit_step in place by the
- * AA pattern (pairs of steps on one population array; periodic boundaries
- * with FP64 or FP32 storage; 0/1, default 1), 11 = D3Q19 with N_z = 128: run
+ * AA pattern (pairs of steps on one population array, in 2D several steps
+ * per launch; periodic boundaries with FP64 or FP32 storage; 0/1, default 1), 11 = D3Q19 with N_z = 128: run
  * the dual-time sweeps after the first of a step on 4 x 128 tiles of 512
  * threads (0/1, default 1), 12 = with the shadow corrector and FP64 or FP32
  * storage, in 3D and in 2D where the row transforms run as passes of their

@@ -12,7 +12,7 @@
 
 #include <hip/hip_ext.h>
 
-#include "msc_aa.h"
+#include "msc_march2.h"
 #include "msc_adjoint.h"
 #include "msc_sweep_launch.h"
 #include "msc_fullsym.h"
@@ -255,26 +255,35 @@ class Solver : public SolverBase {
       SweepArgs<T, TM> S = sweep_args(0.0);
       const int64_t chunk = 64;
       int64_t done = 0;
-      const bool aa = aa_ok();
-      // AA march: pairs of steps in place on A; an odd count ends with one
-      // two-buffer sweep
-      const int64_t paired = aa ? (nsteps & ~(int64_t)1) : 0;
-      if (tune.use_graph && (aa ? paired : nsteps) >= chunk && !timing) {
-        hipGraphExec_t ge = explicit_graph(A, B, (int)chunk, aa);
-        for (; done + chunk <= (aa ? paired : nsteps); done += chunk) MSC_HIPCK(hipGraphLaunch(ge, st));
+      const int kind = explicit_kind();
+      // steps that the chosen kernels take before the tiled sweep takes the
+      // rest one by one: all of them (tiled), or pairs of steps
+      const int64_t paired = (kind == EX_TILED) ? 0 : (nsteps & ~(int64_t)1);
+      const int64_t graphed = (kind == EX_TILED) ? nsteps : paired;
+      if (tune.use_graph && graphed >= chunk && !timing) {
+        hipGraphExec_t ge = explicit_graph(A, B, (int)chunk, kind);
+        for (; done + chunk <= graphed; done += chunk) MSC_HIPCK(hipGraphLaunch(ge, st));
+      }
+      T* cur = A;
+      T* oth = B;
+      if (kind == EX_MULTI) {
+        const int sm = march2_steps(march2_tile());
+        for (; done + sm <= paired; done += sm) {
+          launch_march2(cur, oth);
+          std::swap(cur, oth);
+        }
       }
       for (; done < paired; done += 2) {
-        launch_aa(A, false);
-        launch_aa(A, true);
+        launch_aa(cur, false);
+        launch_aa(cur, true);
       }
-      const bool swapped = aa ? (nsteps & 1) : false;
       for (; done < nsteps; ++done) {
-        const int64_t i = aa ? 0 : done;
-        S.src = (i & 1) ? B : A;
-        S.dst = (i & 1) ? A : B;
+        S.src = cur;
+        S.dst = oth;
         launch_sweep_timed(SW_EXPLICIT, S, 1);
+        std::swap(cur, oth);
       }
-      if (aa ? swapped : (nsteps & 1)) std::swap(cur_roles().slot_hist[0], cur_roles().slot_w[0]);
+      if (cur != A) std::swap(cur_roles().slot_hist[0], cur_roles().slot_w[0]);
       MSC_HIPCK(hipMemcpyAsync(ctl, ctl_h, sizeof(DevCtl), hipMemcpyHostToDevice, st));
       reset_history_from_current();
       // non-finite check on the final state
@@ -285,6 +294,61 @@ class Solver : public SolverBase {
       }
       return MSC_OK;
     });
+  }
+
+  // How the explicit march runs: the tiled two-buffer sweep; the in-place AA
+  // march; or, in 2D, several steps per launch (the AA pattern in LDS), with
+  // AA pairs for what is left of the count.  Kernel timing reports single
+  // steps, so it takes the AA march.
+  enum { EX_TILED = 0, EX_AA = 1, EX_MULTI = 2 };
+  int explicit_kind() const {
+    if (!aa_ok()) return EX_TILED;
+    return (!timing && march2_tile() >= 0) ? EX_MULTI : EX_AA;
+  }
+
+  // Tile of k_march2, or -1 where the grid is smaller than a tile.  Measured
+  // us per step (single-step AA march; 8 x 16 tile; 16 x 16; the large one):
+  // FP64 N = 128 2.9; 0.93; 1.07; 1.6, N = 256 3.3; 1.40; 1.19; 1.7, N = 512
+  // 6.4; 4.4; 3.2; 2.9, N = 2048 100; -; -; 45; FP32 N = 128 2.8; 0.87; 1.0;
+  // 1.5, N = 256 2.8; 1.28; 1.07; 2.0, N = 512 4.3; 3.0; 2.9; 2.2, N = 2048
+  // 44; -; -; 28.  Small tiles fill the chip and keep a step's chain short;
+  // with more tiles than compute units the halo work decides.
+  int march2_tile() const {
+    if (D != 2 || DV) return -1;
+    if (G.NS <= 32768 && G.N0 >= 8 && G.N2 >= 16) return 0;
+    if (G.NS <= 131072 && G.N0 >= 16 && G.N2 >= 16) return 1;
+    if (G.NS > 131072 && G.N0 >= 32 && G.N2 >= 32) return 2;
+    return -1;
+  }
+  static int march2_steps(int tile) { return tile == 2 ? 4 : 8; }
+
+  // march2_steps(tile) steps from in to out
+  void launch_march2(const T* in, T* out) {
+    if constexpr (D == 2 && !DV) {
+      March2Args<T> A{};
+      A.in = in;
+      A.out = out;
+      A.Nx = G.N0;
+      A.Ny = G.N2;
+      A.lgy = ilog2(G.N2);
+      A.wp = wp;
+      A.wm = wm;
+      const int tile = march2_tile();
+      if (tile == 0)
+        launch_march2_tile<8, 16, 8, 512>(A);
+      else if (tile == 1)
+        launch_march2_tile<16, 16, 8, 1024>(A);
+      else if constexpr (sizeof(T) == 8)
+        launch_march2_tile<16, 32, 4, 512>(A);
+      else
+        launch_march2_tile<32, 32, 4, 1024>(A);
+    }
+  }
+  template <int BX, int BY, int SM, int NT>
+  void launch_march2_tile(March2Args<T>& A) {
+    A.lgty = ilog2(G.N2 / BY);
+    hipLaunchKernelGGL((k_march2<T, BX, BY, SM, NT>), dim3((G.N0 / BX) * (G.N2 / BY)), dim3(NT), 0, st, A);
+    MSC_HIPCK(hipGetLastError());
   }
 
   // The in-place (AA) explicit march: periodic boundaries and full-population
@@ -1028,7 +1092,7 @@ class Solver : public SolverBase {
   const T* g_b = nullptr;
   int g_chunk = 0;
   float g_sig = 0.0f;
-  bool g_aa = false;
+  int g_kind = 0;
 
   // kernel timing
   bool timing = false;
@@ -1803,8 +1867,8 @@ class Solver : public SolverBase {
     }
   }
 
-  hipGraphExec_t explicit_graph(T* A, T* B, int chunk, bool aa) {
-    if (gexec && g_a == A && g_b == B && g_chunk == chunk && g_sig == sig && g_aa == aa) return gexec;
+  hipGraphExec_t explicit_graph(T* A, T* B, int chunk, int kind) {
+    if (gexec && g_a == A && g_b == B && g_chunk == chunk && g_sig == sig && g_kind == kind) return gexec;
     if (gexec) (void)hipGraphExecDestroy(gexec);
     if (graph) (void)hipGraphDestroy(graph);
     gexec = nullptr;
@@ -1814,8 +1878,13 @@ class Solver : public SolverBase {
     SweepArgs<T, TM> S = sweep_args(0.0);
     S.L = strip_explicit;
     S.nstrip = G.N0 / strip_explicit;
-    for (int i = 0; i < chunk; ++i) {
-      if (aa) {
+    if (kind == EX_MULTI) {
+      // an even number of launches: the chunk ends in A
+      const int nl = chunk / march2_steps(march2_tile());
+      for (int i = 0; i < nl; ++i) launch_march2((i & 1) ? B : A, (i & 1) ? A : B);
+    }
+    for (int i = 0; kind != EX_MULTI && i < chunk; ++i) {
+      if (kind == EX_AA) {
         launch_aa(A, (i & 1) != 0);
         continue;
       }
@@ -1832,7 +1901,7 @@ class Solver : public SolverBase {
     g_b = B;
     g_chunk = chunk;
     g_sig = sig;
-    g_aa = aa;
+    g_kind = kind;
     return gexec;
   }
 
