@@ -176,9 +176,13 @@ __host__ __device__ inline const float* dev_moments(const T* p, int Q, int64_t N
   return reinterpret_cast<const float*>(p + (int64_t)Q * NS);
 }
 
+// As in the collision, the functions below fuse multiply-adds only within one
+// expression, so that every kernel that inlines them rounds alike.
+//
 // Equilibrium (Eq. feq) in FP32 from moments M = (p, u).
 template <class L>
 __device__ inline float feq_f32(int k, const float* M) {
+#pragma clang fp contract(on)
   float cu = 0.f, uu = 0.f;
 #pragma unroll
   for (int b = 0; b < L::D; ++b) {
@@ -191,6 +195,7 @@ __device__ inline float feq_f32(int k, const float* M) {
 // f from (g, M).
 template <class L>
 __device__ inline void dev_rebuild(const _Float16* g, const float* M, float sig, float* f) {
+#pragma clang fp contract(on)
   float gs[L::Q], s0 = 0.f, s1[3] = {0.f, 0.f, 0.f};
 #pragma unroll
   for (int k = 0; k < L::Q; ++k) {
@@ -216,6 +221,7 @@ __device__ inline void dev_rebuild(const _Float16* g, const float* M, float sig,
 // collision's arithmetic); the explicit map sums in FP32.
 template <class L, class AT = float>
 __device__ inline void dev_split(const float* f, float isig, _Float16* g, float* M) {
+#pragma clang fp contract(on)
   AT acc[L::D + 1];
 #pragma unroll
   for (int b = 0; b <= L::D; ++b) acc[b] = 0;

@@ -34,9 +34,9 @@ namespace msc {
 // term h_q (Eq. bdf2) and the extrapolated trial (Sec. 3.1) while loading.
 enum { SW_EXPLICIT = 0, SW_DTS = 1, SW_DTS_LIFT = 2, SW_DTS_SETUP = 3, SW_DTS_LIFT_ROWS = 4, SW_DTS_SETUP1 = 5 };
 // SW_DTS_LIFT_ROWS: the lift mode with the correction's inverse row transform
-// done by the sweep itself (2D, tiles spanning whole rows, one-plane strips):
-// each block inverts the band spectrum rows of its source planes in LDS
-// instead of reading dm.
+// done by the sweep itself (k_sweep_rows: 2D, tiles spanning whole rows,
+// one-plane strips): each block inverts the band spectrum rows of its source
+// planes in LDS instead of reading dm.
 __host__ __device__ constexpr bool lift_mode(int m) { return m == SW_DTS_LIFT || m == SW_DTS_LIFT_ROWS; }
 // SW_DTS_SETUP1: the first sweep of a step with a trial extrapolated from at
 // most two states (order <= 1), which holds no f^{n-2} registers
@@ -308,6 +308,27 @@ struct SrcPtrs {
   const double* mp;  // m^{n-1} (setup mode)
   double* mw;        // m^n written (setup mode with recon)
 };
+
+// Algorithm 1 mode: the buffers of (step n, sweep ell) from the control slots;
+// false when the march is not at that point.
+template <int MODE, class T, class TM>
+__device__ __forceinline__ bool sweep_sources(const SweepArgs<T, TM>& A, SrcPtrs<T>& P, T* __restrict__& dst) {
+  const uint64_t ph = A.ctl->phase;
+  if (!phase_ready(ph, A.n, A.ell)) return false;
+  const Roles& ro = A.ctl->roles[A.n & 1];
+  if (setup_mode(MODE)) {
+    P.s0 = A.fb.p[ro.slot_hist[0]];
+    P.s1 = A.fb.p[ro.slot_hist[1]];
+    P.s2 = A.fb.p[ro.slot_hist[2]];
+    P.mc = A.recon ? A.h_prev : A.mb[ro.slot_m[0]];
+    P.mp = A.mb[ro.slot_m[1]];
+    P.mw = A.mb[ro.slot_m[0]];
+  } else {
+    P.s0 = A.fb.p[ro.slot_w[(A.ell - 1) & 1]];
+  }
+  dst = A.fb.p[ro.slot_w[A.ell & 1]];
+  return true;
+}
 
 // Raw loads of one site, issued one plane ahead of their use so that the
 // memory latency overlaps the previous plane's collision.
@@ -631,12 +652,8 @@ __global__ __launch_bounds__(NT, (sweep_min_waves<L, T, MODE, T1>())) void k_swe
   // for deviation storage (they are full populations there)
   using LT = typename std::conditional<PopDev<T>::value, float, T>::type;
   constexpr bool ROWFFT = (T1 == 1 && MODE != SW_EXPLICIT && NT == T2);
-  constexpr bool ROWINV = (MODE == SW_DTS_LIFT_ROWS);
-  static_assert(!ROWINV || (ROWFFT && L::D == 2), "inverse rows need 2D tiles spanning whole rows");
+  static_assert(MODE != SW_DTS_LIFT_ROWS, "k_sweep_rows serves the inverse row transforms");
   __shared__ cpx<CT> fbuf[ROWFFT ? 4 * T2 : 1];
-  // inverted dm rows of the three source planes of a one-plane strip: line
-  // 2p packs (dm_0 + i dm_1) of plane p, line 2p+1 holds dm_2; ping-pong
-  __shared__ cpx<CT> ibuf[ROWINV ? 12 * T2 : 1];
   constexpr bool TWOBAR = sweep_two_barriers<L, T>();
   constexpr int DP = ring_depth(0, TWOBAR), DZ = ring_depth(1, TWOBAR), DM = ring_depth(2, TWOBAR);
   __shared__ LT ldsP[DP][NGP][NI];
@@ -646,22 +663,7 @@ __global__ __launch_bounds__(NT, (sweep_min_waves<L, T, MODE, T1>())) void k_swe
 
   SrcPtrs<T> P{A.src, nullptr, nullptr, nullptr, nullptr, nullptr};
   T* __restrict__ dst = A.dst;
-  if (A.ctl) {
-    const uint64_t ph = A.ctl->phase;
-    if (!phase_ready(ph, A.n, A.ell)) return;  // uniform for the grid
-    const Roles& ro = A.ctl->roles[A.n & 1];
-    if (setup_mode(MODE)) {
-      P.s0 = A.fb.p[ro.slot_hist[0]];
-      P.s1 = A.fb.p[ro.slot_hist[1]];
-      P.s2 = A.fb.p[ro.slot_hist[2]];
-      P.mc = A.recon ? A.h_prev : A.mb[ro.slot_m[0]];
-      P.mp = A.mb[ro.slot_m[1]];
-      P.mw = A.mb[ro.slot_m[0]];
-    } else {
-      P.s0 = A.fb.p[ro.slot_w[(A.ell - 1) & 1]];
-    }
-    dst = A.fb.p[ro.slot_w[A.ell & 1]];
-  }
+  if (A.ctl && !sweep_sources<MODE>(A, P, dst)) return;  // uniform for the grid
   if (A.did_run && blockIdx.x == 0 && threadIdx.x == 0) *A.did_run = 1;
 
   // XCD-aware tile order: blocks b, b+8, b+16, ... run on one XCD, so give
@@ -745,51 +747,6 @@ __global__ __launch_bounds__(NT, (sweep_min_waves<L, T, MODE, T1>())) void k_swe
       load_raw<L, T, TM, MODE>(A, P, ((int64_t)xs0 * N1 + wrapi(b1 + hi1, N1)) * N2 + wrapi(b2 + hi2, N2), hraw);
     }
   }
-  // SW_DTS_LIFT_ROWS: inverse transform along y of the band spectrum rows of
-  // the source planes x0-1, x0, x0+1 (Eq. fft-convention, the 1/N_Omega is in
-  // the spectrum): the conjugate-symmetric extension of each field's half
-  // band, fields 0 and 1 packed in one complex line, field 2 in a second;
-  // the same arithmetic as the separate inverse row pass
-  const cpx<CT>* dmr = nullptr;
-  if constexpr (ROWINV) {
-    const int NB = A.NBr;
-    const int64_t FS = (int64_t)N0 * NB;
-    for (int i = tid; i < 3 * T2; i += NT) {
-      const int p = i / T2, jj = i - p * T2;
-      const int64_t o = (int64_t)wrapi(x0 - 1 + p, N0) * NB;
-      cpx<CT> a0 = {0, 0}, a1 = {0, 0}, a2 = {0, 0};
-      if (jj < NB) {
-        a0 = A.spec_in[o + jj];
-        a1 = A.spec_in[FS + o + jj];
-        a2 = A.spec_in[2 * FS + o + jj];
-        if (jj == 0) {
-          a0.y = 0;
-          a1.y = 0;
-          a2.y = 0;
-        }
-      } else if (T2 - jj < NB) {
-        const int jm = T2 - jj;
-        a0 = A.spec_in[o + jm];
-        a1 = A.spec_in[FS + o + jm];
-        a2 = A.spec_in[2 * FS + o + jm];
-        a0.y = -a0.y;
-        a1.y = -a1.y;
-        a2.y = -a2.y;
-      }
-      ibuf[(2 * p) * T2 + jj] = {a0.x - a1.y, a0.y + a1.x};
-      ibuf[(2 * p + 1) * T2 + jj] = a2;
-    }
-    __syncthreads();
-    dmr = lds_fft<CT>(ibuf, ibuf + 6 * T2, A.lgr, 6, +1, A.twr);
-#pragma unroll
-    for (int j = 0; j < SPT; ++j) {
-      const int i2 = tid + j * NT;
-      raw[j].dmv[0] = (TM)dmr[i2].x;
-      raw[j].dmv[1] = (TM)dmr[i2].y;
-      raw[j].dmv[2] = (TM)dmr[T2 + i2].x;
-    }
-  }
-
   for (int it = 0; it < A.L + 2; ++it) {
     const int xs = wrapi(x0 - 1 + it, N0);
     const bool wP = it <= A.L - 1;             // dest plane it+1 is finalised later
@@ -811,12 +768,6 @@ __global__ __launch_bounds__(NT, (sweep_min_waves<L, T, MODE, T1>())) void k_swe
         if (it + 1 < A.L + 2) {
           const int xn = wrapi(x0 + it, N0);
           load_raw<L, T, TM, MODE>(A, P, ((int64_t)xn * N1 + (b1 + i1)) * N2 + (b2 + i2), dstr);
-          if constexpr (ROWINV) {
-            const cpx<CT>* row = dmr + 2 * (it + 1) * T2;
-            dstr.dmv[0] = (TM)row[i2].x;
-            dstr.dmv[1] = (TM)row[i2].y;
-            dstr.dmv[2] = (TM)row[T2 + i2].x;
-          }
         }
       };
       CT C[Q];

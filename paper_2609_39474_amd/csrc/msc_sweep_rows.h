@@ -1,0 +1,185 @@
+// The fused sweep (see msc_sweep.h) on a 2D grid whose rows fit one tile, with
+// one destination plane per block: the three source rows of a destination row
+// in parallel, one group of T2 threads each, instead of one after the other.
+//
+// On these grids (N_y <= 256, at most 512 rows) every block runs at once, so
+// the sweep takes as long as one block's chain of dependent work.  k_sweep's
+// chain is three plane steps of load, collision and barrier; here it is one.
+// The groups push their post-collision values to one array in LDS, and the
+// middle group, which holds the trial populations of the destination row,
+// finalises it.  The arithmetic is k_sweep's, so populations, P r and spectra
+// are bit-identical to it.
+//
+// The lift mode inverts the band spectrum rows of the three source planes in
+// LDS before the collision (all 3 T2 threads), and with fuse_rows the block
+// transforms its row of P r forward, as k_sweep does.
+#pragma once
+
+#include "msc_sweep.h"
+
+namespace msc {
+
+template <class T, class TM, int T2, int MODE>
+__global__ __launch_bounds__(3 * T2) void k_sweep_rows(SweepArgs<T, TM> A) {
+  using L = D2Q9;
+  using CT = typename CompT<T>::type;
+  using LT = typename std::conditional<PopDev<T>::value, float, T>::type;
+  constexpr int Q = L::Q, D = L::D;
+  constexpr bool DV = PopDev<T>::value;
+  constexpr bool ROWINV = (MODE == SW_DTS_LIFT_ROWS);
+  constexpr bool DUAL = (MODE != SW_EXPLICIT);
+  constexpr int NRED = T2 < 64 ? T2 : T2 / 64;
+  __shared__ LT val[Q][T2];  // post-collision values by destination
+  __shared__ cpx<CT> fbuf[DUAL ? 4 * T2 : 1];
+  __shared__ cpx<CT> ibuf[ROWINV ? 12 * T2 : 1];
+  __shared__ double red[NRED];
+
+  SrcPtrs<T> P{A.src, nullptr, nullptr, nullptr, nullptr, nullptr};
+  T* __restrict__ dst = A.dst;
+  if (A.ctl && !sweep_sources<MODE>(A, P, dst)) return;
+  if (A.did_run && blockIdx.x == 0 && threadIdx.x == 0) *A.did_run = 1;
+
+  const int N0 = A.N0;
+  const int64_t NS = A.NS;
+  const int x0 = xcd_item(blockIdx.x, gridDim.x);  // adjacent rows on one XCD
+  const int tid = threadIdx.x;
+  const int pl = tid / T2, y = tid & (T2 - 1);  // source plane x0 - 1 + pl
+  const int xs = (x0 - 1 + pl) & (N0 - 1);
+  const int64_t site = (int64_t)xs * T2 + y;
+  RawSite<L, T, TM, MODE> raw;
+  load_raw<L, T, TM, MODE>(A, P, site, raw);
+  if constexpr (ROWINV) {
+    // inverse transform along y of the band spectrum rows of the three source
+    // planes (the conjugate-symmetric extension of each field's half band,
+    // fields 0 and 1 packed in one complex line, field 2 in a second)
+    const int NB = A.NBr;
+    const int64_t FS = (int64_t)N0 * NB, o = (int64_t)xs * NB;
+    cpx<CT> a0 = {0, 0}, a1 = {0, 0}, a2 = {0, 0};
+    if (y < NB) {
+      a0 = A.spec_in[o + y];
+      a1 = A.spec_in[FS + o + y];
+      a2 = A.spec_in[2 * FS + o + y];
+      if (y == 0) {
+        a0.y = 0;
+        a1.y = 0;
+        a2.y = 0;
+      }
+    } else if (T2 - y < NB) {
+      const int jm = T2 - y;
+      a0 = A.spec_in[o + jm];
+      a1 = A.spec_in[FS + o + jm];
+      a2 = A.spec_in[2 * FS + o + jm];
+      a0.y = -a0.y;
+      a1.y = -a1.y;
+      a2.y = -a2.y;
+    }
+    ibuf[(2 * pl) * T2 + y] = {a0.x - a1.y, a0.y + a1.x};
+    ibuf[(2 * pl + 1) * T2 + y] = a2;
+    __syncthreads();
+    const cpx<CT>* dmr = lds_fft<CT>(ibuf, ibuf + 6 * T2, A.lgr, 6, +1, A.twr) + 2 * pl * T2;
+    raw.dmv[0] = (TM)dmr[y].x;
+    raw.dmv[1] = (TM)dmr[y].y;
+    raw.dmv[2] = (TM)dmr[T2 + y].x;
+  }
+
+  CT f[Q], C[Q];
+  double hs[4], mns[4], mtr[4];
+  collide_raw<L, T, TM, MODE>(A, raw, f, C, hs, mtr, mns);
+  if (setup_mode(MODE) && pl == 1) {
+#pragma unroll
+    for (int b = 0; b <= D; ++b) A.h[b * NS + site] = hs[b];
+    if (A.recon) {
+#pragma unroll
+      for (int b = 0; b <= D; ++b) P.mw[b * NS + site] = mns[b];
+    }
+  }
+  // push (Eq. sweep): the directions that carry this plane into x0
+#pragma unroll
+  for (int k = 0; k < Q; ++k)
+    if (L::cx(k) == 1 - pl) val[k][(y + L::cy(k)) & (T2 - 1)] = (LT)C[k];
+  __syncthreads();
+
+  double r2 = 0.0;
+  if (pl == 1) {
+    CT vv[Q], pr[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < Q; ++k) vv[k] = (CT)val[k][y];
+    if (A.walls) cavity_rows<CT>(vv, x0, y, N0, T2, (CT)A.ulid);
+    float Mq[DV ? D + 1 : 1];
+    if constexpr (DV) {
+      // store (g, M); the residual is taken against the stored output
+      T gq[Q];
+      dev_split<L, typename std::conditional<DUAL, double, float>::type>(vv, A.isig, gq, Mq);
+#pragma unroll
+      for (int k = 0; k < Q; ++k) __builtin_nontemporal_store(gq[k], &dst[k * NS + site]);
+      float* dM = dev_moments(dst, Q, NS);
+#pragma unroll
+      for (int b = 0; b <= D; ++b) __builtin_nontemporal_store(Mq[b], &dM[b * NS + site]);
+      if (DUAL) dev_rebuild<L>(gq, Mq, A.sig, vv);
+    }
+#pragma unroll
+    for (int k = 0; k < Q; ++k) {
+      const CT v = vv[k];
+      if constexpr (!DV) __builtin_nontemporal_store((T)v, &dst[k * NS + site]);
+      if (DUAL) {
+        const CT r = v - f[k];
+        if (A.rout) __builtin_nontemporal_store((TM)r, &A.rout[k * NS + site]);
+        pr[0] += r;
+#pragma unroll
+        for (int b = 0; b < D; ++b)
+          if (ca<L>(k, b) != 0) pr[1 + b] += (CT)ca<L>(k, b) * r;
+        r2 += (double)r * (double)r;
+      }
+    }
+    if constexpr (DV && DUAL) {
+      // P r exactly: the stored output moments minus the trial's
+#pragma unroll
+      for (int b = 0; b <= D; ++b) pr[b] = (CT)((double)Mq[b] - mtr[b]);
+    }
+    if constexpr (DUAL) {
+      if (A.fuse_rows) {
+        fbuf[y] = {pr[0], pr[1]};
+        fbuf[T2 + y] = {pr[2], (CT)0};
+      } else if (!A.rout && !A.skip_pr) {
+#pragma unroll
+        for (int b = 0; b <= D; ++b) __builtin_nontemporal_store((TM)pr[b], &A.Pr[b * NS + site]);
+      }
+    }
+  }
+  if constexpr (DUAL) {
+    if (pl == 1) {
+      // FP64 sum of r^2 over the row, as k_sweep's block sum
+      if constexpr (T2 >= 64) {
+        double v = r2;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+        if ((y & 63) == 0) red[y >> 6] = v;
+      } else {
+        red[y] = r2;
+      }
+    }
+    __syncthreads();
+    if (tid == 0) {
+      double acc = 0.0;
+      for (int i = 0; i < NRED; ++i) acc += red[i];
+      A.partials[blockIdx.x] = acc;
+    }
+    if (A.fuse_rows) {
+      // forward transform along y of this row's P r, band j <= N_y/4 kept
+      // (Eq. fft-convention, shadow-mask); unpack the packed pair
+      const cpx<CT>* out = lds_fft<CT>(fbuf, fbuf + 2 * T2, A.lgr, 2, -1, A.twr);
+      const int NB = A.NBr;
+      const int64_t FS = (int64_t)N0 * NB;
+      if (tid < NB) {
+        const cpx<CT> z = out[tid];
+        const cpx<CT> zc = out[(T2 - tid) & (T2 - 1)];
+        const int64_t o = (int64_t)x0 * NB + tid;
+        A.spec[o] = {(CT)0.5 * (z.x + zc.x), (CT)0.5 * (z.y - zc.y)};
+        A.spec[FS + o] = {(CT)0.5 * (z.y + zc.y), (CT)0.5 * (zc.x - z.x)};
+        A.spec[2 * FS + o] = out[T2 + tid];
+      }
+    }
+  }
+}
+
+}  // namespace msc
