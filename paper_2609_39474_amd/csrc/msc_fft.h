@@ -7,15 +7,15 @@
 // j = 0..N/4 (the negative half follows by conjugate symmetry) and the other
 // axes keep |j| <= N/4.
 //
-// Transforms are Stockham passes of radix 8 (then one of radix 4 or 2 for the
-// remaining factors of two) on complex lines held in LDS, ping-ponging between
-// two LDS arrays; the
-// twiddle table exp(-2 pi i t/N) is precomputed per axis.  The per-wavevector
+// Transforms are Stockham passes on complex lines (msc_linefft.h in 2D,
+// msc_ldsfft.h in 3D); the twiddle table exp(-2 pi i t/N) is precomputed per
+// axis.  The per-wavevector
 // 3x3 (2D) / 4x4 (3D) solve of Eq. (schur) runs in FP64 inside the kernel that
 // holds the full spectrum line of the last axis.
 #pragma once
 
 #include "msc_kernels.h"
+#include "msc_linefft.h"
 
 namespace msc {
 
@@ -36,17 +36,19 @@ __device__ __forceinline__ void schur_solve(const double* kv, const double (*r)[
     kr_re += kv[b] * r[1 + b][0];
     kr_im += kv[b] * r[1 + b][1];
   }
-  // numerator r_p - i (k.r_m)/b ; -i*(x + iy) = y - ix
-  const double num_re = r[0][0] + kr_im / bc;
-  const double num_im = r[0][1] - kr_re / bc;
-  const double den = a + cs2 * kk / bc;
-  const double dp_re = num_re / den, dp_im = num_im / den;
+  // numerator r_p - i (k.r_m)/b ; -i*(x + iy) = y - ix.  Two divisions, the
+  // other quotients by their reciprocals (one FP64 division is a chain of
+  // about ten dependent operations)
+  const double ib = 1.0 / bc, iden = 1.0 / (a + cs2 * kk * ib);
+  const double num_re = r[0][0] + kr_im * ib;
+  const double num_im = r[0][1] - kr_re * ib;
+  const double dp_re = num_re * iden, dp_im = num_im * iden;
   out[0][0] = dp_re * scale;
   out[0][1] = dp_im * scale;
   for (int b = 0; b < D; ++b) {
     // (r_b - cs2 i k_b dp)/b ; i*dp = (-dp_im, dp_re)
-    const double re = (r[1 + b][0] + cs2 * kv[b] * dp_im) / bc;
-    const double im = (r[1 + b][1] - cs2 * kv[b] * dp_re) / bc;
+    const double re = (r[1 + b][0] + cs2 * kv[b] * dp_im) * ib;
+    const double im = (r[1 + b][1] - cs2 * kv[b] * dp_re) * ib;
     out[1 + b][0] = re * scale;
     out[1 + b][1] = im * scale;
   }
@@ -67,14 +69,14 @@ __device__ __forceinline__ void schur_solve_adjoint(const double* kv, const doub
     kr_re += kv[b] * r[1 + b][0];
     kr_im += kv[b] * r[1 + b][1];
   }
-  const double den = a + cs2 * kk / bc;
-  const double yp_re = (r[0][0] - cs2 * kr_im / bc) / den;
-  const double yp_im = (r[0][1] + cs2 * kr_re / bc) / den;
+  const double ib = 1.0 / bc, iden = 1.0 / (a + cs2 * kk * ib);
+  const double yp_re = (r[0][0] - cs2 * kr_im * ib) * iden;
+  const double yp_im = (r[0][1] + cs2 * kr_re * ib) * iden;
   out[0][0] = yp_re * scale;
   out[0][1] = yp_im * scale;
   for (int b = 0; b < D; ++b) {
-    out[1 + b][0] = (r[1 + b][0] - kv[b] * yp_im) / bc * scale;
-    out[1 + b][1] = (r[1 + b][1] + kv[b] * yp_re) / bc * scale;
+    out[1 + b][0] = (r[1 + b][0] - kv[b] * yp_im) * ib * scale;
+    out[1 + b][1] = (r[1 + b][1] + kv[b] * yp_re) * ib * scale;
   }
 }
 
@@ -94,12 +96,10 @@ template <class CT, class TM>
 struct Fft2Args {
   CorrGuard g;
   int do_accept;  // Algorithm 1 mode: the first pass decides acceptance (and reconstructs m^{n+1})
-  int decide_only;  // with do_accept: take the decision only (the sweep left P r out)
   int decide;     // the row pass ran inside the sweep: the column pass decides instead
   int adjoint;    // apply chi H^{-H} (transpose of the correction) instead of chi H^{-1}
-  int Nx, Ny, lgx, lgy;
+  int Nx, Ny;
   int NBy;      // N_y/4 + 1
-  int rows_per_block, cols_per_block;
   const TM* Pr;            // 3 x Nx x Ny
   cpx<CT>* spec;           // 3 x Nx x NBy
   TM* dm;                  // 3 x Nx x Ny
@@ -108,63 +108,111 @@ struct Fft2Args {
   double a, nu, inv_ns;
 };
 
-template <class L, class T, class CT, class TM>
-__global__ __launch_bounds__(256) void k_fft2_rows_fwd(Fft2Args<CT, TM> A, AcceptArgs<L, T> Ac, FinishArgs Fin) {
+// Block shape of the row passes: 2 R lines of one block's R rows, R > 1 only
+// where one row's two lines would not fill two wavefronts.
+template <class CT, int LG>
+struct RowsShape {
+  using F = LineFft<CT, LG, line_le(LG)>;
+  static constexpr int R = 2 * F::TPL >= 128 ? 1 : 128 / (2 * F::TPL);
+  static constexpr int NT = 2 * R * F::TPL;
+  static constexpr int LDS = 2 * R * F::N * (F::WAVE ? 1 : 2);
+};
+
+template <class L, class T, class CT, class TM, int LG>
+__global__ __launch_bounds__((RowsShape<CT, LG>::NT)) void k_fft2_rows_fwd(Fft2Args<CT, TM> A, AcceptArgs<L, T> Ac,
+                                                                         FinishArgs Fin) {
+  using S = RowsShape<CT, LG>;
+  using F = typename S::F;
+  constexpr int N = F::N, E = F::E, TPL = F::TPL;
+  __shared__ cpx<CT> lds[S::LDS];
+  const int line = threadIdx.x / TPL, t = threadIdx.x & (TPL - 1);
+  const int x = blockIdx.x * S::R + (line >> 1);
+  cpx<CT> w[F::NTW];
+  F::load_tw(A.twy, t, w);
   if (A.do_accept) {
     // Algorithm 1: decide on sweep ell of step n here; if accepted,
     // reconstruct m^{n+1} on this block's rows instead of transforming
-    __shared__ double red[256];
+    __shared__ double red[S::NT / 64];
     const int dec = finish_block(Fin, red);
     if (dec != DEC_RUNNING) {
       if (dec == DEC_ACCEPTED) {
-        const int64_t s0 = (int64_t)blockIdx.x * A.rows_per_block * A.Ny;
-        accept_sites<L, T>(Ac, s0 + threadIdx.x, s0 + (int64_t)A.rows_per_block * A.Ny, blockDim.x);
+        const int64_t s0 = (int64_t)blockIdx.x * S::R * N, s1 = s0 + (int64_t)S::R * N;
+        accept_sites<L, T>(Ac, s0 + threadIdx.x, s1 < Ac.NS ? s1 : Ac.NS, blockDim.x);
       }
       return;
     }
-    if (A.decide_only) return;
   } else if (A.g.skip()) {
     return;
   }
-  extern __shared__ unsigned char smem_raw[];
-  cpx<CT>* buf = reinterpret_cast<cpx<CT>*>(smem_raw);
-  const int Ny = A.Ny, R = A.rows_per_block;
-  cpx<CT>* tmp = buf + 2 * R * Ny;
-  const int x0 = blockIdx.x * R;
-  const int64_t NS = (int64_t)A.Nx * Ny;
-  for (int i = threadIdx.x; i < R * Ny; i += blockDim.x) {
-    const int r = i / Ny, y = i - r * Ny;
-    const int64_t s = (int64_t)(x0 + r) * Ny + y;
-    buf[(2 * r) * Ny + y] = {(CT)A.Pr[s], (CT)A.Pr[NS + s]};
-    buf[(2 * r + 1) * Ny + y] = {(CT)A.Pr[2 * NS + s], (CT)0};
+  if (F::WAVE && x >= A.Nx) return;  // fewer rows than one block's
+  const int64_t NS = (int64_t)A.Nx * N, s0 = (int64_t)x * N;
+  cpx<CT> v[E];
+#pragma unroll
+  for (int i = 0; i < E; ++i) {
+    const int64_t s = s0 + t + i * TPL;
+    v[i] = (line & 1) ? cpx<CT>{(CT)A.Pr[2 * NS + s], (CT)0} : cpx<CT>{(CT)A.Pr[s], (CT)A.Pr[NS + s]};
   }
-  __syncthreads();
-  const cpx<CT>* out = lds_fft<CT>(buf, tmp, A.lgy, 2 * R, -1, A.twy);
+  cpx<CT>* a = lds + line * N;
+  cpx<CT>* b = F::WAVE ? a : a + S::LDS / 2;
+  F::template run<-1>(v, t, a, b, w);
+  cpx<CT>* nat = (F::NX & 1) ? b : a;
+#pragma unroll
+  for (int i = 0; i < E; ++i) nat[t + i * TPL] = v[i];
+  if constexpr (F::WAVE)
+    wave_fence();
+  else
+    __syncthreads();
   const int NB = A.NBy;
-  for (int i = threadIdx.x; i < R * NB; i += blockDim.x) {
-    const int r = i / NB, j = i - r * NB;
-    const cpx<CT> z = out[(2 * r) * Ny + j];
-    const cpx<CT> zc = out[(2 * r) * Ny + ((Ny - j) & (Ny - 1))];
+  const int64_t FS = (int64_t)A.Nx * NB, o = (int64_t)x * NB;
+  auto store = [&](int j, cpx<CT> z) {
+    if (line & 1) {
+      A.spec[2 * FS + o + j] = z;
+      return;
+    }
     // unpack: F0 = (Z(j) + conj Z(-j))/2, F1 = (Z(j) - conj Z(-j))/(2i)
-    const cpx<CT> f0 = {(CT)0.5 * (z.x + zc.x), (CT)0.5 * (z.y - zc.y)};
-    const cpx<CT> f1 = {(CT)0.5 * (z.y + zc.y), (CT)0.5 * (zc.x - z.x)};
-    const int64_t o = (int64_t)(x0 + r) * NB + j;
-    const int64_t FS = (int64_t)A.Nx * NB;
-    A.spec[o] = f0;
-    A.spec[FS + o] = f1;
-    A.spec[2 * FS + o] = out[(2 * r + 1) * Ny + j];
-  }
+    const cpx<CT> zc = nat[(N - j) & (N - 1)];
+    A.spec[o + j] = {(CT)0.5 * (z.x + zc.x), (CT)0.5 * (z.y - zc.y)};
+    A.spec[FS + o + j] = {(CT)0.5 * (z.y + zc.y), (CT)0.5 * (zc.x - z.x)};
+  };
+#pragma unroll
+  for (int i = 0; i < E / 4; ++i) store(t + i * TPL, v[i]);
+  if (t == 0) store(N / 4, v[E / 4]);
 }
 
-// Pass 2: for a group of j_y columns, forward transform along x, the FP64
-// Schur solve on the band |j_x| <= N_x/4 (zero elsewhere), and the inverse
-// transform along x, in place in the band spectrum array.
-template <class L, class T, class CT, class TM>
-__global__ __launch_bounds__(512) void k_fft2_cols_solve(Fft2Args<CT, TM> A, AcceptArgs<L, T> Ac, FinishArgs Fin) {
+// Pass 2: one retained j_y column per block, its three fields on TPL threads
+// each: forward transform along x, the FP64 Schur solve on the band |j_x| <=
+// N_x/4 (zero elsewhere), and the inverse transform along x, in place in the
+// band spectrum array.  A few dozen to a few hundred blocks: the pass is one
+// block's chain of load, transform, solve, transform, store, so a column is
+// spread over as many threads as its stages can use.
+template <class CT, int LG>
+struct ColsShape {
+  using F = LineFft<CT, LG, line_le(LG)>;
+  static constexpr int NT = 3 * F::TPL > 256 ? 3 * F::TPL : 256;
+  static constexpr int LDS = 3 * F::N * (F::WAVE ? 1 : 2);
+};
+
+template <class L, class T, class CT, class TM, int LG>
+__global__ __launch_bounds__((ColsShape<CT, LG>::NT)) void k_fft2_cols_solve(Fft2Args<CT, TM> A, AcceptArgs<L, T> Ac,
+                                                                           FinishArgs Fin) {
+  using S = ColsShape<CT, LG>;
+  using F = typename S::F;
+  constexpr int N = F::N, E = F::E, TPL = F::TPL;
+  static_assert(F::WAVE || S::NT == 3 * TPL, "every thread takes part in the barriers of long lines");
+  __shared__ cpx<CT> lds[S::LDS];
+  const int f = threadIdx.x / TPL, t = threadIdx.x & (TPL - 1);
+  // XCD-aware column order (the grid is padded to a multiple of 8)
+  const int NB = A.NBy, jy = xcd_item(blockIdx.x, gridDim.x);
+  const int64_t FS = (int64_t)N * NB;
+  const bool mine = f < 3 && jy < NB;
+  cpx<CT> w[F::NTW], v[E];
+  F::load_tw(A.twx, t, w);
+#pragma unroll
+  for (int i = 0; i < E; ++i) v[i] = mine ? A.spec[f * FS + (int64_t)(t + i * TPL) * NB + jy] : cpx<CT>{0, 0};
   if (A.decide) {
     // Algorithm 1 with the row pass fused into the sweep: decide here; if
     // accepted, reconstruct m^{n+1} over the whole field instead
-    __shared__ double red[4];
+    __shared__ double red[S::NT / 64];
     const int dec = finish_block(Fin, red);
     if (dec != DEC_RUNNING) {
       if (dec == DEC_ACCEPTED)
@@ -175,110 +223,101 @@ __global__ __launch_bounds__(512) void k_fft2_cols_solve(Fft2Args<CT, TM> A, Acc
   } else if (A.g.skip()) {
     return;
   }
-  // XCD-aware column order over the first pad8(column blocks) blocks; the
-  // rest (decision mode) only reconstruct
-  const int Nx = A.Nx, JB = A.cols_per_block, NB = A.NBy;
-  const int GC = pad8((NB + JB - 1) / JB);
-  const int cbk = ((int)blockIdx.x < GC) ? xcd_item(blockIdx.x, GC) : (int)blockIdx.x;
-  if (cbk * JB >= NB) return;  // padding or reconstruction-only block
-  extern __shared__ unsigned char smem_raw[];
-  cpx<CT>* buf = reinterpret_cast<cpx<CT>*>(smem_raw);
-  cpx<CT>* tmp = buf + 3 * JB * Nx;
-  const int j0 = cbk * JB;
-  const int64_t FS = (int64_t)Nx * NB;
-  // transform t = f*JB + c holds column j0 + c of field f
-  for (int i = threadIdx.x; i < 3 * JB * Nx; i += blockDim.x) {
-    const int c = i % JB;
-    const int rest = i / JB;
-    const int x = rest % Nx, f = rest / Nx;
-    const int j = j0 + c;
-    buf[(f * JB + c) * Nx + x] = (j < NB) ? A.spec[f * FS + (int64_t)x * NB + j] : cpx<CT>{0, 0};
+  if (jy >= NB) return;  // grid padding
+  cpx<CT>* a = lds + (f < 3 ? f : 0) * N;
+  cpx<CT>* b = F::WAVE ? a : a + S::LDS / 2;
+  if (f < 3) F::template run<-1>(v, t, a, b, w);
+  // the band of the three spectra meets in LDS; wavevector q of the band is
+  // j_x = q or q - (N/2 + 1) mod N
+  cpx<CT>* s = (F::NX & 1) ? b : a;
+  const cpx<CT>* base = (F::NX & 1) ? lds + S::LDS / 2 : lds;
+  if (F::WAVE) base = lds;
+  if (f < 3) {
+#pragma unroll
+    for (int i = 0; i < E; ++i)
+      if (in_band(signed_index(t + i * TPL, N), N)) s[t + i * TPL] = v[i];
   }
   __syncthreads();
-  cpx<CT>* F = lds_fft<CT>(buf, tmp, A.lgx, 3 * JB, -1, A.twx);
-  cpx<CT>* G = (F == buf) ? tmp : buf;
   const double two_pi = 6.283185307179586476925286766559;
-  for (int i = threadIdx.x; i < JB * Nx; i += blockDim.x) {
-    const int c = i / Nx, jx = i - c * Nx;
-    const int jy = j0 + c;
-    const int sjx = signed_index(jx, Nx);
-    if (jy < NB && in_band(sjx, Nx)) {
-      double kv[2] = {two_pi * sjx / Nx, two_pi * jy / A.Ny};
-      double r[3][2], o[3][2];
-      for (int f = 0; f < 3; ++f) {
-        const cpx<CT> v = F[(f * JB + c) * Nx + jx];
-        r[f][0] = (double)v.x;
-        r[f][1] = (double)v.y;
-      }
-      if (A.adjoint)
-        schur_solve_adjoint<2>(kv, r, A.a, A.nu, A.inv_ns, o);
-      else
-        schur_solve<2>(kv, r, A.a, A.nu, A.inv_ns, o);
-      for (int f = 0; f < 3; ++f) G[(f * JB + c) * Nx + jx] = {(CT)o[f][0], (CT)o[f][1]};
-    } else {
-      for (int f = 0; f < 3; ++f) G[(f * JB + c) * Nx + jx] = {(CT)0, (CT)0};
+  for (int q = threadIdx.x; q <= N / 2; q += S::NT) {
+    const int jx = q <= N / 4 ? q : q + N / 2 - 1;
+    const double kv[2] = {two_pi * signed_index(jx, N) / N, two_pi * jy / A.Ny};
+    double r[3][2], o[3][2];
+    cpx<CT>* c = const_cast<cpx<CT>*>(base) + jx;
+#pragma unroll
+    for (int g = 0; g < 3; ++g) {
+      r[g][0] = (double)c[g * N].x;
+      r[g][1] = (double)c[g * N].y;
     }
+    if (A.adjoint)
+      schur_solve_adjoint<2>(kv, r, A.a, A.nu, A.inv_ns, o);
+    else
+      schur_solve<2>(kv, r, A.a, A.nu, A.inv_ns, o);
+#pragma unroll
+    for (int g = 0; g < 3; ++g) c[g * N] = {(CT)o[g][0], (CT)o[g][1]};
   }
   __syncthreads();
-  cpx<CT>* H = lds_fft<CT>(G, F, A.lgx, 3 * JB, +1, A.twx);
-  for (int i = threadIdx.x; i < 3 * JB * Nx; i += blockDim.x) {
-    const int c = i % JB;
-    const int rest = i / JB;
-    const int x = rest % Nx, f = rest / Nx;
-    const int j = j0 + c;
-    if (j < NB) A.spec[f * FS + (int64_t)x * NB + j] = H[(f * JB + c) * Nx + x];
-  }
+  if (f >= 3) return;  // only where lines need no barrier
+#pragma unroll
+  for (int i = 0; i < E; ++i)
+    v[i] = in_band(signed_index(t + i * TPL, N), N) ? s[t + i * TPL] : cpx<CT>{0, 0};
+  if constexpr (F::WAVE)
+    wave_fence();
+  F::template run<+1>(v, t, (F::NX & 1) ? a : b, s, w);
+#pragma unroll
+  for (int i = 0; i < E; ++i) A.spec[f * FS + (int64_t)(t + i * TPL) * NB + jy] = v[i];
 }
 
 // Pass 3: inverse transform along y from the half band to real rows.  The
 // band of field f at x is extended by conjugate symmetry (Z(N - j) =
 // conj Z(j)); fields 0 and 1 share one complex inverse transform (real and
 // imaginary parts), field 2 uses the real part of a second one.
-template <class CT, class TM>
-__global__ __launch_bounds__(256) void k_fft2_rows_inv(Fft2Args<CT, TM> A) {
+template <class CT, class TM, int LG>
+__global__ __launch_bounds__((RowsShape<CT, LG>::NT)) void k_fft2_rows_inv(Fft2Args<CT, TM> A) {
+  using S = RowsShape<CT, LG>;
+  using F = typename S::F;
+  constexpr int N = F::N, E = F::E, TPL = F::TPL;
+  __shared__ cpx<CT> lds[S::LDS];
+  const int line = threadIdx.x / TPL, t = threadIdx.x & (TPL - 1);
+  const int x = blockIdx.x * S::R + (line >> 1);
+  cpx<CT> w[F::NTW];
+  F::load_tw(A.twy, t, w);
   if (A.g.skip()) return;
-  extern __shared__ unsigned char smem_raw[];
-  cpx<CT>* buf = reinterpret_cast<cpx<CT>*>(smem_raw);
-  const int Ny = A.Ny, R = A.rows_per_block, NB = A.NBy;
-  cpx<CT>* tmp = buf + 2 * R * Ny;
-  const int x0 = blockIdx.x * R;
-  const int64_t FS = (int64_t)A.Nx * NB;
-  for (int i = threadIdx.x; i < R * Ny; i += blockDim.x) {
-    const int r = i / Ny, j = i - r * Ny;
-    const int64_t o = (int64_t)(x0 + r) * NB;
-    cpx<CT> a0 = {0, 0}, a1 = {0, 0}, a2 = {0, 0};
-    if (j < NB) {
-      a0 = A.spec[o + j];
-      a1 = A.spec[FS + o + j];
-      a2 = A.spec[2 * FS + o + j];
+  if (F::WAVE && x >= A.Nx) return;
+  const int NB = A.NBy;
+  const int64_t FS = (int64_t)A.Nx * NB, o = (int64_t)x * NB;
+  cpx<CT> v[E];
+#pragma unroll
+  for (int i = 0; i < E; ++i) {
+    const int j = t + i * TPL;
+    const bool lower = j < NB;
+    const int jj = lower ? j : N - j;
+    v[i] = {0, 0};
+    if (jj < NB) {
+      cpx<CT> a0 = A.spec[((line & 1) ? 2 * FS : 0) + o + jj];
+      cpx<CT> a1 = (line & 1) ? cpx<CT>{0, 0} : A.spec[FS + o + jj];
       if (j == 0) {
         a0.y = 0;
         a1.y = 0;
-        a2.y = 0;
+      } else if (!lower) {
+        a0.y = -a0.y;
+        a1.y = -a1.y;
       }
-    } else if (Ny - j < NB) {
-      const int jj = Ny - j;
-      a0 = A.spec[o + jj];
-      a1 = A.spec[FS + o + jj];
-      a2 = A.spec[2 * FS + o + jj];
-      a0.y = -a0.y;
-      a1.y = -a1.y;
-      a2.y = -a2.y;
+      v[i] = {a0.x - a1.y, a0.y + a1.x};  // pack a0 + i a1
     }
-    // pack a0 + i a1
-    buf[(2 * r) * Ny + j] = {a0.x - a1.y, a0.y + a1.x};
-    buf[(2 * r + 1) * Ny + j] = a2;
   }
-  __syncthreads();
-  const cpx<CT>* out = lds_fft<CT>(buf, tmp, A.lgy, 2 * R, +1, A.twy);
-  const int64_t NS = (int64_t)A.Nx * Ny;
-  for (int i = threadIdx.x; i < R * Ny; i += blockDim.x) {
-    const int r = i / Ny, y = i - r * Ny;
-    const int64_t s = (int64_t)(x0 + r) * Ny + y;
-    const cpx<CT> z = out[(2 * r) * Ny + y];
-    A.dm[s] = (TM)z.x;
-    A.dm[NS + s] = (TM)z.y;
-    A.dm[2 * NS + s] = (TM)out[(2 * r + 1) * Ny + y].x;
+  cpx<CT>* a = lds + line * N;
+  F::template run<+1>(v, t, a, F::WAVE ? a : a + S::LDS / 2, w);
+  const int64_t NS = (int64_t)A.Nx * N, s0 = (int64_t)x * N;
+#pragma unroll
+  for (int i = 0; i < E; ++i) {
+    const int64_t s = s0 + t + i * TPL;
+    if (line & 1) {
+      A.dm[2 * NS + s] = (TM)v[i].x;
+    } else {
+      A.dm[s] = (TM)v[i].x;
+      A.dm[NS + s] = (TM)v[i].y;
+    }
   }
 }
 
@@ -293,7 +332,6 @@ template <class CT, class TM>
 struct Fft3Args {
   CorrGuard g;
   int do_accept;
-  int decide_only;  // with do_accept: take the decision only (the sweep left P r out)
   int adjoint;
   int Nx, Ny, Nz, lgx, lgy, lgz;
   int NBz;  // N_z/4 + 1
@@ -331,7 +369,6 @@ __global__ __launch_bounds__(256) void k_fft3_z_fwd(Fft3Args<CT, TM> A, AcceptAr
       }
       return;
     }
-    if (A.decide_only) return;
   } else if (A.g.skip()) {
     return;
   }

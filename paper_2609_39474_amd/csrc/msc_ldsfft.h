@@ -1,6 +1,5 @@
 // Complex arithmetic and the Stockham transform (radix 8, 4, 2) of lines held in
-// LDS, shared by the transform passes of the shadow correction and by the
-// sweep's fused forward row transform.
+// LDS, of a length known at run time.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -14,6 +13,7 @@ struct cpx {
 
 template <class CT>
 __device__ __forceinline__ cpx<CT> cmul(cpx<CT> a, cpx<CT> b) {
+#pragma clang fp contract(on)
   return {a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x};
 }
 template <class CT>

@@ -1,0 +1,166 @@
+// Stockham transforms of lines whose length is fixed at compile time, held in
+// registers between stages.
+//
+// A line of N = 2^LG complex elements belongs to TPL = N / 2^LE consecutive
+// threads; thread t holds the 2^LE elements t + i TPL.  Every stage of radix
+// R <= 2^LE takes its butterflies' inputs and leaves its outputs in that
+// distribution: the first stage needs no load from LDS, the last no store to
+// it, and the stages between exchange once.  The transforms here are short
+// chains that one or a few wavefronts run alone, so their time is instruction
+// and LDS latency: with the length known, indices, strides and twiddle
+// positions fold into constants, the first stage has no twiddles, and the
+// twiddles of the others can be loaded before the data arrives.  One line of
+// 256 alone takes 0.44 us in FP64 and 0.35 us in FP32, against 2.05 and 1.92
+// us with a run-time length and every stage through LDS (lds_fft).
+//
+// Lines that fit one wavefront (TPL <= 64, TPL threads aligned inside a
+// wavefront) need no barrier: LDS operations of a wavefront complete in order.
+// Longer lines exchange through two buffers with one barrier per exchange, in
+// which the whole block takes part.
+#pragma once
+
+#include <type_traits>
+
+#include "msc_ldsfft.h"
+
+namespace msc {
+
+template <class CT, int R, int ST, int SIGN>
+__device__ __forceinline__ void reg_dft(cpx<CT>* a) {
+#pragma clang fp contract(on)
+  if constexpr (R == 2) {
+    const cpx<CT> s = cadd(a[0], a[ST]), d = csub(a[0], a[ST]);
+    a[0] = s;
+    a[ST] = d;
+  } else if constexpr (R == 4) {
+    const cpx<CT> s02 = cadd(a[0], a[2 * ST]), d02 = csub(a[0], a[2 * ST]);
+    const cpx<CT> s13 = cadd(a[ST], a[3 * ST]), d13 = cmuli(csub(a[ST], a[3 * ST]), SIGN);
+    a[0] = cadd(s02, s13);
+    a[ST] = cadd(d02, d13);
+    a[2 * ST] = csub(s02, s13);
+    a[3 * ST] = csub(d02, d13);
+  } else {
+    static_assert(R == 8, "radix 2, 4 or 8");
+    // even outputs: the 4-point DFT of v_m + v_{m+4}; odd ones: that of
+    // (v_m - v_{m+4}) e^(SIGN 2 pi i m / 8)
+    cpx<CT> e[4], o[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      e[m] = cadd(a[m * ST], a[(m + 4) * ST]);
+      o[m] = csub(a[m * ST], a[(m + 4) * ST]);
+    }
+    const CT r = (CT)0.70710678118654752440, sg = (CT)SIGN;
+    o[1] = cpx<CT>{r * (o[1].x - sg * o[1].y), r * (o[1].y + sg * o[1].x)};
+    o[2] = cmuli(o[2], SIGN);
+    o[3] = cpx<CT>{r * (-o[3].x - sg * o[3].y), r * (-o[3].y + sg * o[3].x)};
+    reg_dft<CT, 4, 1, SIGN>(e);
+    reg_dft<CT, 4, 1, SIGN>(o);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      a[2 * m * ST] = e[m];
+      a[(2 * m + 1) * ST] = o[m];
+    }
+  }
+}
+
+// orders a wavefront's own LDS accesses (the hardware keeps them in order;
+// this keeps the compiler from moving them)
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <class CT, int LG, int LE>
+struct LineFft {
+  static_assert(LG >= LE && LE >= 2 && LE <= 3, "radices up to 8, a line holds a thread's elements");
+  static constexpr int N = 1 << LG, E = 1 << LE, TPL = N / E;
+  static constexpr bool WAVE = TPL <= 64;
+  static constexpr int NST = (LG + LE - 1) / LE;  // stages: radix E while it divides, then the rest
+  static constexpr int NX = NST - 1;              // exchanges
+  static constexpr int lr(int p) { return p < LG / LE ? LE : LG - (LG / LE) * LE; }
+  static constexpr int tw_before(int p) {  // twiddles of the stages before p
+    int n = 0;
+    for (int q = 1; q < p; ++q) n += (E >> lr(q)) * ((1 << lr(q)) - 1);
+    return n;
+  }
+  static constexpr int NTW = tw_before(NST) > 0 ? tw_before(NST) : 1;
+
+  // this thread's twiddles exp(-2 pi i m k / (R Ns)) of every stage, from the
+  // table exp(-2 pi i j / N)
+  template <int P = 1>
+  static __device__ __forceinline__ void load_tw(const cpx<CT>* __restrict__ tw, int t, cpx<CT>* w) {
+    if constexpr (P < NST) {
+      constexpr int R = 1 << lr(P), LNS = P * LE, NB = E / R;
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        const int k = (t + b * TPL) & ((1 << LNS) - 1);
+#pragma unroll
+        for (int m = 1; m < R; ++m) w[tw_before(P) + b * (R - 1) + m - 1] = tw[m * k * (N / R >> LNS)];
+      }
+      load_tw<P + 1>(tw, t, w);
+    }
+  }
+
+  static __device__ __forceinline__ int slot(int i) {
+    constexpr int G = 128 / (int)sizeof(cpx<CT>);
+    return N >= G ? lds_swz<CT>(i) : i;
+  }
+
+  // in place: v[i] = x[t + i TPL] -> X[t + i TPL], SIGN = -1 forward, +1
+  // inverse (no scaling).  a, b: the line's N elements of LDS for the even
+  // and the odd exchanges (may be one and the same where WAVE).
+  template <int SIGN, int P = 0>
+  static __device__ __forceinline__ void run(cpx<CT>* v, int t, cpx<CT>* a, cpx<CT>* b, const cpx<CT>* w) {
+#pragma clang fp contract(on)
+    constexpr int R = 1 << lr(P), LNS = P * LE, NB = E / R;
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      if constexpr (P > 0) {
+#pragma unroll
+        for (int m = 1; m < R; ++m) {
+          cpx<CT> x = w[tw_before(P) + q * (R - 1) + m - 1];
+          if (SIGN > 0) x.y = -x.y;
+          v[q + m * NB] = cmul(v[q + m * NB], x);
+        }
+      }
+      reg_dft<CT, R, NB, SIGN>(v + q);
+    }
+    if constexpr (P + 1 < NST) {
+#pragma unroll
+      for (int q = 0; q < NB; ++q) {
+        const int j = t + q * TPL, k = j & ((1 << LNS) - 1);
+        const int base = ((j - k) << lr(P)) + k;
+#pragma unroll
+        for (int m = 0; m < R; ++m) a[slot(base + (m << LNS))] = v[q + m * NB];
+      }
+      if constexpr (WAVE)
+        wave_fence();
+      else
+        __syncthreads();
+#pragma unroll
+      for (int i = 0; i < E; ++i) v[i] = a[slot(t + i * TPL)];
+      if constexpr (WAVE) wave_fence();
+      run<SIGN, P + 1>(v, t, b, a, w);
+    }
+  }
+};
+
+constexpr int ilog2c(int n) { return n <= 1 ? 0 : 1 + ilog2c(n / 2); }
+
+// log2 of the elements per thread where a few lines run alone (the 2D passes):
+// radix 4 for short instruction chains while the threads last; N = 512 fits
+// one wavefront with radix 8 (FP64 0.72 us against 0.86 with radix 4), N =
+// 1024 does not (radix 4 on four wavefronts 1.27, radix 8 on two 1.83 us).
+constexpr int line_le(int lg) { return (lg <= 8 || lg == 10) ? 2 : 3; }
+
+// f(integral_constant<int, lg>) for LO <= lg <= HI
+template <int LO, int HI, class F>
+void with_lg(int lg, F&& f) {
+  if (lg == LO)
+    f(std::integral_constant<int, LO>{});
+  else if constexpr (LO < HI)
+    with_lg<LO + 1, HI>(lg, f);
+}
+
+}  // namespace msc

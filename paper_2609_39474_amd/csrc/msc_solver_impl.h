@@ -1910,9 +1910,9 @@ class Solver : public SolverBase {
   // device: the sweep (the first one of a step also forms h_q and the
   // extrapolated trial), the one-block acceptance test, then either the
   // reconstruction of m^{n+1} (accepted) or the shadow correction.
-  // last: the final iteration enqueued for this step; its correction passes
-  // after the first are left out (they run only if the step goes on, and then
-  // enqueue_correction_tail supplies them before the next sweep).
+  // last: the final iteration enqueued for this step; its correction is left
+  // out (it runs only if the step goes on, and then enqueue_correction_tail
+  // supplies it before the next sweep).
   // recon: this step's setup sweep forms m^n (the previous step, coefficient
   // a_prev, left it); defer: this step's acceptance leaves m^{n+1} to the
   // next step's setup sweep.
@@ -1978,41 +1978,39 @@ class Solver : public SolverBase {
 
     AcceptArgs<L, T> Ac = accept_args(n, ell, a);
     Ac.defer = defer ? 1 : 0;
-    if (P.corrector == MSC_CORRECTOR_SHADOW) {
+    if (P.corrector == MSC_CORRECTOR_SHADOW && !last) {
       XformBufs<CT, TM> B{Pr, dm, spec_of(ell), spec2, {tw[0], tw[1], tw[2]}};
-      enqueue_transform<CT, TM>(ctl, n, ell, a, &Ac, false, B, &F, true, !last && !fuse_inv, fuse_rows, skip_pr);
+      enqueue_transform<CT, TM>(ctl, n, ell, a, &Ac, false, B, &F, fuse_rows, fuse_inv);
     } else if (fullsym()) {
       enqueue_fullsym(ctl, n, ell, a, &Ac, &F, true, !last, nullptr);
     } else {
-      hipLaunchKernelGGL((k_accept<L, T>), dim3(ew_grid()), dim3(256), 0, st, Ac, F);
+      // the decision alone (without the shadow corrector, and for the sweep
+      // enqueued last for its step, which is predicted to end it); one block
+      // unless an accepted step is to be reconstructed here
+      hipLaunchKernelGGL((k_accept<L, T>), dim3(defer ? 1 : ew_grid()), dim3(256), 0, st, Ac, F);
       MSC_HIPCK(hipGetLastError());
     }
   }
 
-  // The correction passes after the first for (step n, sweep ell), guarded on
-  // the device (they run only if that sweep was not accepted).
+  // The correction of (step n, sweep ell), the sweep enqueued last for its
+  // step, guarded on the device (it runs only if that sweep was not accepted;
+  // the decision was taken).
   void enqueue_correction_tail(int n, int ell, double a) {
     if (fullsym()) {
       enqueue_fullsym(ctl, n, ell, a, nullptr, nullptr, false, true, nullptr);
       return;
     }
     if (P.corrector != MSC_CORRECTOR_SHADOW) return;
-    if (fuse_inv) return;  // the next sweep inverts the rows itself
     XformBufs<CT, TM> B{Pr, dm, spec_of(ell), spec2, {tw[0], tw[1], tw[2]}};
     if constexpr (!PopDev<T>::value) {
-      // the tail follows the last sweep enqueued for the step; a lift sweep
-      // there left P r out: form it, then every pass, the first one guarded
-      // rather than deciding (the decision was taken)
+      // a lift sweep enqueued last left P r out: form it
       if (skip_pr_ok() && ell >= 2) {
         PrArgs<T, TM> R{ctl, n, ell, fb, dm, Pr, G.NS};
         hipLaunchKernelGGL((k_recompute_pr<L, T, TM>), dim3(ew_grid()), dim3(256), 0, st, R);
         MSC_HIPCK(hipGetLastError());
-        enqueue_transform<CT, TM>(ctl, n, ell, a, nullptr, false, B, nullptr, true, true, false);
-        return;
       }
     }
-    AcceptArgs<L, T> Ac = accept_args(n, ell, a);
-    enqueue_transform<CT, TM>(ctl, n, ell, a, &Ac, false, B, nullptr, false, true, fuse_rows);
+    enqueue_transform<CT, TM>(ctl, n, ell, a, nullptr, false, B, nullptr, fuse_rows, fuse_inv);
   }
 
   // band spectrum of the correction after sweep ell (alternating buffers
@@ -2035,29 +2033,6 @@ class Solver : public SolverBase {
     Ac.a = a;
     Ac.inv1pa2 = 1.0 / (1.0 + a / 2.0);
     return Ac;
-  }
-
-  // FFT launch shapes
-  // rows per block of the row passes: LDS-limited, and small enough that the
-  // grid has >= 1024 blocks (four per CU) when the grid is large enough: these
-  // passes are latency-bound, and one row per block instead of four cuts the
-  // corrected march by 18% at N = 512 FP32, one instead of two by 4% at N = 1024
-  int fft_rows_per_block(size_t c = sizeof(cpx<CT>)) const {
-    int R = (int)std::max<size_t>(1, (size_t)65536 / (4 * G.N2 * c));
-    int p = 1;
-    while (p * 2 <= R) p *= 2;
-    while (p > 1 && G.N0 / p < 1024) p >>= 1;
-    return std::min(p, G.N0);
-  }
-  // columns per block of the column pass: LDS-limited, and as few as give
-  // >= 256 blocks (one per CU: at N = 512 one column per block instead of
-  // two cuts the corrected march by 7%, at N = 1024 FP32 by 5%)
-  int fft_cols_per_block(size_t c = sizeof(cpx<CT>)) const {
-    int J = (int)std::max<size_t>(1, (size_t)98304 / (6 * G.N0 * c));
-    J = std::min(J, 16);
-    const int NB = G.N2 / 4 + 1;
-    while (J > 1 && (NB + J - 1) / J < 256) J >>= 1;
-    return std::max(J, 1);
   }
 
   // 3D launch shapes: pencils per block of the z passes, j_z columns per
@@ -2115,16 +2090,7 @@ class Solver : public SolverBase {
   template <class CX = CT, class TX = TM>
   void set_fft_attrs() {
     const size_t c = sizeof(cpx<CX>);
-    if constexpr (D == 2) {
-      const int rows_b = (int)(4 * fft_rows_per_block(c) * G.N2 * c);
-      const int cols_b = (int)(6 * fft_cols_per_block(c) * G.N0 * c);
-      MSC_HIPCK(hipFuncSetAttribute((const void*)k_fft2_rows_fwd<L, T, CX, TX>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, rows_b));
-      MSC_HIPCK(hipFuncSetAttribute((const void*)k_fft2_rows_inv<CX, TX>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, rows_b));
-      MSC_HIPCK(hipFuncSetAttribute((const void*)k_fft2_cols_solve<L, T, CX, TX>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, cols_b));
-    } else {
+    if constexpr (D == 3) {
       const int zb = (int)(4 * fft3_pencils_per_block(c) * G.n[2] * c);
       const int Nmax = std::max(G.n[0], G.n[1]);
       const int cb = (int)(8 * fft3_cols_per_block(c) * Nmax * c);
@@ -2257,26 +2223,24 @@ class Solver : public SolverBase {
     enqueue_transform<CT, TM>(c, n, ell, a, Ac, false, B);
   }
 
+  // With Ac and Fin the first pass decides on the sweep.  rows_in_sweep: the
+  // sweep wrote the row spectrum, so the column pass is the first;
+  // inv_in_sweep: the next sweep inverts the rows.
   template <class CX, class TX>
   void enqueue_transform(const DevCtl* c, int n, int ell, double a, const AcceptArgs<L, T>* Ac, bool adjoint,
-                         const XformBufs<CX, TX>& B, const FinishArgs* Fin = nullptr, bool head = true,
-                         bool tail = true, bool rows_in_sweep = false, bool decide_only = false) {
-    AcceptArgs<L, T> none{};
-    const FinishArgs nofin{};
-    const size_t cb = sizeof(cpx<CX>);
+                         const XformBufs<CX, TX>& B, const FinishArgs* Fin = nullptr, bool rows_in_sweep = false,
+                         bool inv_in_sweep = false) {
+    const AcceptArgs<L, T> acc = Ac ? *Ac : AcceptArgs<L, T>{};
+    const FinishArgs fin = Fin ? *Fin : FinishArgs{};
     if constexpr (D == 2) {
       Fft2Args<CX, TX> F{};
       F.g = CorrGuard{c, n, ell};
-      F.do_accept = Ac ? 1 : 0;
-      F.decide_only = (Ac && decide_only) ? 1 : 0;
+      F.do_accept = (Ac && !rows_in_sweep) ? 1 : 0;
+      F.decide = (Ac && rows_in_sweep) ? 1 : 0;
       F.adjoint = adjoint ? 1 : 0;
       F.Nx = G.N0;
       F.Ny = G.N2;
-      F.lgx = ilog2(G.N0);
-      F.lgy = ilog2(G.N2);
       F.NBy = G.N2 / 4 + 1;
-      F.rows_per_block = fft_rows_per_block(cb);
-      F.cols_per_block = fft_cols_per_block(cb);
       F.Pr = B.in;
       F.spec = B.spec1;
       F.dm = B.out;
@@ -2285,48 +2249,33 @@ class Solver : public SolverBase {
       F.a = a;
       F.nu = nu;
       F.inv_ns = 1.0 / (double)G.NS;
-      const size_t rows_b = 4 * (size_t)F.rows_per_block * G.N2 * cb;
-      const size_t cols_b = 6 * (size_t)F.cols_per_block * G.N0 * cb;
-      const int grows = G.N0 / F.rows_per_block;
-      // column blocks rounded up to a multiple of 8 (the XCD-aware order)
-      const int gcols = pad8((F.NBy + F.cols_per_block - 1) / F.cols_per_block);
-      if (rows_in_sweep) {
-        // the sweep wrote the row spectrum; the column pass decides
-        F.do_accept = 0;
-        F.decide = 1;
-        if (head) {
-          // enough blocks for the reconstruction of an accepted step; blocks
-          // beyond the column count stop after the decision otherwise
-          const int gdec = std::max<int>(gcols, (int)std::min<int64_t>((G.NS + 255) / 256, 4096));
-          hipLaunchKernelGGL((k_fft2_cols_solve<L, T, CX, TX>), dim3(gdec), dim3(256), cols_b, st, F,
-                             Ac ? *Ac : none, Fin ? *Fin : nofin);
-          MSC_HIPCK(hipGetLastError());
-        }
-        if (tail) {
-          hipLaunchKernelGGL((k_fft2_rows_inv<CX, TX>), dim3(grows), dim3(256), rows_b, st, F);
-          MSC_HIPCK(hipGetLastError());
-        }
-        return;
-      }
-      if (head) {
-        hipLaunchKernelGGL((k_fft2_rows_fwd<L, T, CX, TX>), dim3(grows), dim3(256), rows_b, st, F,
-                           Ac ? *Ac : none, Fin ? *Fin : nofin);
-        MSC_HIPCK(hipGetLastError());
-      }
-      if (tail) {
-        // 512 threads: two waves per SIMD on the one block per CU that the
-        // column count allows (N = 1024 FP64 march 0.361 -> 0.347 ms per step,
-        // N = 512 and 2048 FP32 4-5%; 1024 threads no better)
-        hipLaunchKernelGGL((k_fft2_cols_solve<L, T, CX, TX>), dim3(gcols), dim3(512), cols_b, st, F, none, nofin);
-        MSC_HIPCK(hipGetLastError());
-        hipLaunchKernelGGL((k_fft2_rows_inv<CX, TX>), dim3(grows), dim3(256), rows_b, st, F);
-        MSC_HIPCK(hipGetLastError());
-      }
+      // the longest lines whose transforms fit (fft_fits)
+      constexpr int LX = sizeof(CX) == 8 ? 10 : 11, LY = LX + 1;
+      if (!rows_in_sweep)
+        with_lg<2, LY>(ilog2(G.N2), [&](auto lg) {
+          using S = RowsShape<CX, lg.value>;
+          hipLaunchKernelGGL((k_fft2_rows_fwd<L, T, CX, TX, lg.value>), dim3((G.N0 + S::R - 1) / S::R), dim3(S::NT),
+                             0, st, F, acc, fin);
+        });
+      MSC_HIPCK(hipGetLastError());
+      with_lg<2, LX>(ilog2(G.N0), [&](auto lg) {
+        // one column per block, in the XCD-aware order
+        hipLaunchKernelGGL((k_fft2_cols_solve<L, T, CX, TX, lg.value>), dim3(pad8(F.NBy)),
+                           dim3(ColsShape<CX, lg.value>::NT), 0, st, F, acc, fin);
+      });
+      MSC_HIPCK(hipGetLastError());
+      if (!inv_in_sweep)
+        with_lg<2, LY>(ilog2(G.N2), [&](auto lg) {
+          using S = RowsShape<CX, lg.value>;
+          hipLaunchKernelGGL((k_fft2_rows_inv<CX, TX, lg.value>), dim3((G.N0 + S::R - 1) / S::R), dim3(S::NT), 0, st,
+                             F);
+        });
+      MSC_HIPCK(hipGetLastError());
     } else {
+      const size_t cb = sizeof(cpx<CX>);
       Fft3Args<CX, TX> F{};
       F.g = CorrGuard{c, n, ell};
       F.do_accept = Ac ? 1 : 0;
-      F.decide_only = (Ac && decide_only) ? 1 : 0;
       F.adjoint = adjoint ? 1 : 0;
       F.Nx = G.n[0];
       F.Ny = G.n[1];
@@ -2360,12 +2309,8 @@ class Solver : public SolverBase {
       // inverse pass slower, 34.5 -> 38.3 us, so it keeps one group per block)
       const int gz = (int)(((int64_t)F.Nx * F.Ny) / R);
       const int gzf = std::min(gz, resident_blocks((const void*)k_fft3_z_fwd<L, T, CX, TX>, 256, zb));
-      if (head) {
-        hipLaunchKernelGGL((k_fft3_z_fwd<L, T, CX, TX>), dim3(gzf), dim3(256), zb, st, F, Ac ? *Ac : none,
-                           Fin ? *Fin : nofin);
-        MSC_HIPCK(hipGetLastError());
-      }
-      if (!tail) return;
+      hipLaunchKernelGGL((k_fft3_z_fwd<L, T, CX, TX>), dim3(gzf), dim3(256), zb, st, F, acc, fin);
+      MSC_HIPCK(hipGetLastError());
       hipLaunchKernelGGL((k_fft3_y_fwd<CX, TX>), dim3(pad8(F.Nx * ng)), dim3(256), yb, st, F);
       MSC_HIPCK(hipGetLastError());
       hipLaunchKernelGGL((k_fft3_x_solve<CX, TX>), dim3(pad8(F.NBy * ng)), dim3(256), xb, st, F);

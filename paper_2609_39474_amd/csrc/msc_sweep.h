@@ -24,7 +24,7 @@
 #include <type_traits>
 
 #include "msc_common.h"
-#include "msc_ldsfft.h"
+#include "msc_linefft.h"
 
 namespace msc {
 
@@ -637,6 +637,42 @@ __host__ __device__ constexpr int sweep_min_waves() {
                                                                                        : 1;
 }
 
+// Forward transform along y of one row of P r (fields 0 and 1 packed in the
+// complex line fbuf[0 .. T2), field 2 in the next), band j <= N_y/4 kept (Eq.
+// fft-convention, shadow-mask), into row xd of the band spectrum; by the
+// block's first T2 / 2 threads, after a barrier.
+template <int T2, class T, class TM, class CT>
+__device__ __forceinline__ void row_spectrum(const SweepArgs<T, TM>& A, cpx<CT>* fbuf, int tid, int xd,
+                                             const cpx<CT>* tw) {
+#pragma clang fp contract(on)
+  using F = LineFft<CT, ilog2c(T2), 2>;
+  if (tid >= 2 * F::TPL) return;
+  const int line = tid / F::TPL, t = tid & (F::TPL - 1);
+  cpx<CT>* ln = fbuf + line * T2;
+  cpx<CT> v[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = ln[t + i * F::TPL];
+  wave_fence();
+  F::template run<-1>(v, t, ln, ln, tw);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) ln[t + i * F::TPL] = v[i];
+  wave_fence();
+  const int NB = A.NBr;
+  const int64_t FS = (int64_t)A.N0 * NB, o = (int64_t)xd * NB;
+  auto store = [&](int j, cpx<CT> z) {
+    if (line) {
+      A.spec[2 * FS + o + j] = z;
+      return;
+    }
+    // unpack: F0 = (Z(j) + conj Z(-j))/2, F1 = (Z(j) - conj Z(-j))/(2i)
+    const cpx<CT> zc = ln[(T2 - j) & (T2 - 1)];
+    A.spec[o + j] = {(CT)0.5 * (z.x + zc.x), (CT)0.5 * (z.y - zc.y)};
+    A.spec[FS + o + j] = {(CT)0.5 * (z.y + zc.y), (CT)0.5 * (zc.x - z.x)};
+  };
+  store(t, v[0]);
+  if (t == 0) store(F::TPL, v[1]);
+}
+
 template <class L, class T, class TM, int NT, int T1, int T2, int MODE>
 __global__ __launch_bounds__(NT, (sweep_min_waves<L, T, MODE, T1>())) void k_sweep(SweepArgs<T, TM> A) {
   using CT = typename CompT<T>::type;
@@ -651,9 +687,9 @@ __global__ __launch_bounds__(NT, (sweep_min_waves<L, T, MODE, T1>())) void k_swe
   // post-collision values travel through LDS in the storage type, or FP32
   // for deviation storage (they are full populations there)
   using LT = typename std::conditional<PopDev<T>::value, float, T>::type;
-  constexpr bool ROWFFT = (T1 == 1 && MODE != SW_EXPLICIT && NT == T2);
+  constexpr bool ROWFFT = (L::D == 2 && T1 == 1 && MODE != SW_EXPLICIT && NT == T2);
   static_assert(MODE != SW_DTS_LIFT_ROWS, "k_sweep_rows serves the inverse row transforms");
-  __shared__ cpx<CT> fbuf[ROWFFT ? 4 * T2 : 1];
+  __shared__ cpx<CT> fbuf[ROWFFT ? 2 * T2 : 1];
   constexpr bool TWOBAR = sweep_two_barriers<L, T>();
   constexpr int DP = ring_depth(0, TWOBAR), DZ = ring_depth(1, TWOBAR), DM = ring_depth(2, TWOBAR);
   __shared__ LT ldsP[DP][NGP][NI];
@@ -962,20 +998,11 @@ __global__ __launch_bounds__(NT, (sweep_min_waves<L, T, MODE, T1>())) void k_swe
       }
       if constexpr (ROWFFT) {
         if (A.fuse_rows) {
-          // forward transform along y of this plane's P r, band j <= N_y/4
-          // kept (Eq. fft-convention, shadow-mask); unpack the packed pair
           __syncthreads();
-          const cpx<CT>* out = lds_fft<CT>(fbuf, fbuf + 2 * T2, A.lgr, 2, -1, A.twr);
-          const int NB = A.NBr;
-          const int64_t FS = (int64_t)N0 * NB;
-          for (int j = tid; j < NB; j += NT) {
-            const cpx<CT> z = out[j];
-            const cpx<CT> zc = out[(T2 - j) & (T2 - 1)];
-            const int64_t o = (int64_t)xd * NB + j;
-            A.spec[o] = {(CT)0.5 * (z.x + zc.x), (CT)0.5 * (z.y - zc.y)};
-            A.spec[FS + o] = {(CT)0.5 * (z.y + zc.y), (CT)0.5 * (zc.x - z.x)};
-            A.spec[2 * FS + o] = out[T2 + j];
-          }
+          using F = LineFft<CT, ilog2c(T2), 2>;
+          cpx<CT> tw[F::NTW];
+          F::load_tw(A.twr, tid & (F::TPL - 1), tw);
+          row_spectrum<T2>(A, fbuf, tid, xd, tw);
           __syncthreads();  // fbuf is refilled by the next plane
         }
       }

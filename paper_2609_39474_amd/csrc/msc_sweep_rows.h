@@ -7,12 +7,12 @@
 // chain is three plane steps of load, collision and barrier; here it is one.
 // The groups push their post-collision values to one array in LDS, and the
 // middle group, which holds the trial populations of the destination row,
-// finalises it.  The arithmetic is k_sweep's, so populations, P r and spectra
-// are bit-identical to it.
+// finalises it.  The arithmetic is k_sweep's, so populations and P r are
+// bit-identical to it.
 //
-// The lift mode inverts the band spectrum rows of the three source planes in
-// LDS before the collision (all 3 T2 threads), and with fuse_rows the block
-// transforms its row of P r forward, as k_sweep does.
+// The lift mode inverts the band spectrum rows of the three source planes
+// before the collision (six lines at once), and with fuse_rows the block
+// transforms its row of P r forward.
 #pragma once
 
 #include "msc_sweep.h"
@@ -29,9 +29,10 @@ __global__ __launch_bounds__(3 * T2) void k_sweep_rows(SweepArgs<T, TM> A) {
   constexpr bool ROWINV = (MODE == SW_DTS_LIFT_ROWS);
   constexpr bool DUAL = (MODE != SW_EXPLICIT);
   constexpr int NRED = T2 < 64 ? T2 : T2 / 64;
+  constexpr int LG = ilog2c(T2);
   __shared__ LT val[Q][T2];  // post-collision values by destination
-  __shared__ cpx<CT> fbuf[DUAL ? 4 * T2 : 1];
-  __shared__ cpx<CT> ibuf[ROWINV ? 12 * T2 : 1];
+  __shared__ cpx<CT> fbuf[DUAL ? 2 * T2 : 1];  // the row of P r, then its spectrum
+  __shared__ cpx<CT> ibuf[ROWINV ? 6 * T2 : 1];
   __shared__ double red[NRED];
 
   SrcPtrs<T> P{A.src, nullptr, nullptr, nullptr, nullptr, nullptr};
@@ -48,35 +49,45 @@ __global__ __launch_bounds__(3 * T2) void k_sweep_rows(SweepArgs<T, TM> A) {
   const int64_t site = (int64_t)xs * T2 + y;
   RawSite<L, T, TM, MODE> raw;
   load_raw<L, T, TM, MODE>(A, P, site, raw);
+  using F = LineFft<CT, LG, 2>;
+  cpx<CT> tw[F::NTW];
+  // (the table is there only for sweeps that transform rows)
+  if (DUAL && A.fuse_rows) F::load_tw(A.twr, tid & (F::TPL - 1), tw);
   if constexpr (ROWINV) {
     // inverse transform along y of the band spectrum rows of the three source
     // planes (the conjugate-symmetric extension of each field's half band,
-    // fields 0 and 1 packed in one complex line, field 2 in a second)
-    const int NB = A.NBr;
-    const int64_t FS = (int64_t)N0 * NB, o = (int64_t)xs * NB;
-    cpx<CT> a0 = {0, 0}, a1 = {0, 0}, a2 = {0, 0};
-    if (y < NB) {
-      a0 = A.spec_in[o + y];
-      a1 = A.spec_in[FS + o + y];
-      a2 = A.spec_in[2 * FS + o + y];
-      if (y == 0) {
-        a0.y = 0;
-        a1.y = 0;
-        a2.y = 0;
-      }
-    } else if (T2 - y < NB) {
-      const int jm = T2 - y;
-      a0 = A.spec_in[o + jm];
-      a1 = A.spec_in[FS + o + jm];
-      a2 = A.spec_in[2 * FS + o + jm];
-      a0.y = -a0.y;
-      a1.y = -a1.y;
-      a2.y = -a2.y;
+    // fields 0 and 1 packed in line 2p of plane p, field 2 in line 2p + 1)
+    const int line = tid / F::TPL, t = tid & (F::TPL - 1);
+    if (line < 6) {
+      const int NB = A.NBr;
+      const int64_t FS = (int64_t)N0 * NB, o = (int64_t)((x0 - 1 + (line >> 1)) & (N0 - 1)) * NB;
+      // element j of the line, j <= N_y/4
+      auto elem = [&](int j) -> cpx<CT> {
+        if (line & 1) {
+          const cpx<CT> a2 = A.spec_in[2 * FS + o + j];
+          return {a2.x, j == 0 ? (CT)0 : a2.y};
+        }
+        const cpx<CT> a0 = A.spec_in[o + j], a1 = A.spec_in[FS + o + j];
+        return j == 0 ? cpx<CT>{a0.x, a1.x} : cpx<CT>{a0.x - a1.y, a0.y + a1.x};
+      };
+      // its conjugate-symmetric partner N_y - j
+      auto conj_elem = [&](int j) -> cpx<CT> {
+        if (line & 1) {
+          const cpx<CT> a2 = A.spec_in[2 * FS + o + j];
+          return {a2.x, -a2.y};
+        }
+        const cpx<CT> a0 = A.spec_in[o + j], a1 = A.spec_in[FS + o + j];
+        return {a0.x + a1.y, a1.x - a0.y};
+      };
+      cpx<CT> v[4] = {elem(t), {0, 0}, {0, 0}, conj_elem(F::TPL - t)};
+      if (t == 0) v[1] = elem(F::TPL);
+      cpx<CT>* ln = ibuf + line * T2;
+      F::template run<+1>(v, t, ln, ln, tw);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) ln[t + i * F::TPL] = v[i];
     }
-    ibuf[(2 * pl) * T2 + y] = {a0.x - a1.y, a0.y + a1.x};
-    ibuf[(2 * pl + 1) * T2 + y] = a2;
     __syncthreads();
-    const cpx<CT>* dmr = lds_fft<CT>(ibuf, ibuf + 6 * T2, A.lgr, 6, +1, A.twr) + 2 * pl * T2;
+    const cpx<CT>* dmr = ibuf + 2 * pl * T2;
     raw.dmv[0] = (TM)dmr[y].x;
     raw.dmv[1] = (TM)dmr[y].y;
     raw.dmv[2] = (TM)dmr[T2 + y].x;
@@ -164,21 +175,7 @@ __global__ __launch_bounds__(3 * T2) void k_sweep_rows(SweepArgs<T, TM> A) {
       for (int i = 0; i < NRED; ++i) acc += red[i];
       A.partials[blockIdx.x] = acc;
     }
-    if (A.fuse_rows) {
-      // forward transform along y of this row's P r, band j <= N_y/4 kept
-      // (Eq. fft-convention, shadow-mask); unpack the packed pair
-      const cpx<CT>* out = lds_fft<CT>(fbuf, fbuf + 2 * T2, A.lgr, 2, -1, A.twr);
-      const int NB = A.NBr;
-      const int64_t FS = (int64_t)N0 * NB;
-      if (tid < NB) {
-        const cpx<CT> z = out[tid];
-        const cpx<CT> zc = out[(T2 - tid) & (T2 - 1)];
-        const int64_t o = (int64_t)x0 * NB + tid;
-        A.spec[o] = {(CT)0.5 * (z.x + zc.x), (CT)0.5 * (z.y - zc.y)};
-        A.spec[FS + o] = {(CT)0.5 * (z.y + zc.y), (CT)0.5 * (zc.x - z.x)};
-        A.spec[2 * FS + o] = out[T2 + tid];
-      }
-    }
+    if (A.fuse_rows) row_spectrum<T2>(A, fbuf, tid, x0, tw);
   }
 }
 
