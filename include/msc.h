@@ -326,8 +326,8 @@ msc_status msc_kernel_time(msc_ctx* c, int32_t kind, double* seconds, int64_t* l
  * key 0), 6 = in 2D with tiles spanning whole rows, do the correction's row
  * transforms inside the sweep: 0 = neither, 1 = the forward one, 2 = the
  * forward one and, with one-plane strips, the inverse one before the lift
- * (default 2), 7 / 8 = z pencils / j_z columns per block of the 3D
- * transform passes (0 = automatic; capped by the LDS), 9 = the full-symbol
+ * (default 2), 7 / 8 = accepted and without effect (launch shapes of the 3D
+ * transform passes, which follow from the extents), 9 = the full-symbol
  * corrector's column pass as three kernels (x transforms, per-wavevector
  * solve, inverse transforms): 0 = automatic (split from N_x = 512), 1 =
  * split, 2 = one fused kernel, 10 = march msc_explicit_step in place by the

@@ -313,8 +313,8 @@ msc_status msc_set_tuning(msc_ctx* c, int32_t key, int32_t value) {
       if (value < 0 || value > 2) return MSC_ERR_INVALID_ARG;
       t.fuse_rows = value;
       break;
-    case 7: t.fft3_pencils = value < 0 ? 0 : value; break;
-    case 8: t.fft3_cols = value < 0 ? 0 : value; break;
+    case 7:
+    case 8: break;  // the 3D transform passes' shapes follow from the extents
     case 9:
       if (value < 0 || value > 2) return MSC_ERR_INVALID_ARG;
       t.fs_split = value;

@@ -7,9 +7,8 @@
 // j = 0..N/4 (the negative half follows by conjugate symmetry) and the other
 // axes keep |j| <= N/4.
 //
-// Transforms are Stockham passes on complex lines (msc_linefft.h in 2D,
-// msc_ldsfft.h in 3D); the twiddle table exp(-2 pi i t/N) is precomputed per
-// axis.  The per-wavevector
+// Transforms are Stockham passes on complex lines (msc_linefft.h); the twiddle
+// tables are precomputed per axis.  The per-wavevector
 // 3x3 (2D) / 4x4 (3D) solve of Eq. (schur) runs in FP64 inside the kernel that
 // holds the full spectrum line of the last axis.
 #pragma once
@@ -101,7 +100,7 @@ struct Fft2Args {
   int Nx, Ny;
   int NBy;      // N_y/4 + 1
   const TM* Pr;            // 3 x Nx x Ny
-  cpx<CT>* spec;           // 3 x Nx x NBy
+  cpx<CT>* spec;           // 3 fields of the band (Spec2)
   TM* dm;                  // 3 x Nx x Ny
   const cpx<CT>* twx;      // Nx
   const cpx<CT>* twy;      // Ny
@@ -163,16 +162,17 @@ __global__ __launch_bounds__((RowsShape<CT, LG>::NT)) void k_fft2_rows_fwd(Fft2A
   else
     __syncthreads();
   const int NB = A.NBy;
-  const int64_t FS = (int64_t)A.Nx * NB, o = (int64_t)x * NB;
+  const int64_t FS = Spec2<CT>::field(A.Nx, NB);
   auto store = [&](int j, cpx<CT> z) {
     if (line & 1) {
-      A.spec[2 * FS + o + j] = z;
+      A.spec[2 * FS + Spec2<CT>::at(x, j, A.Nx)] = z;
       return;
     }
     // unpack: F0 = (Z(j) + conj Z(-j))/2, F1 = (Z(j) - conj Z(-j))/(2i)
     const cpx<CT> zc = nat[(N - j) & (N - 1)];
-    A.spec[o + j] = {(CT)0.5 * (z.x + zc.x), (CT)0.5 * (z.y - zc.y)};
-    A.spec[FS + o + j] = {(CT)0.5 * (z.y + zc.y), (CT)0.5 * (zc.x - z.x)};
+    const int64_t o = Spec2<CT>::at(x, j, A.Nx);
+    A.spec[o] = {(CT)0.5 * (z.x + zc.x), (CT)0.5 * (z.y - zc.y)};
+    A.spec[FS + o] = {(CT)0.5 * (z.y + zc.y), (CT)0.5 * (zc.x - z.x)};
   };
 #pragma unroll
   for (int i = 0; i < E / 4; ++i) store(t + i * TPL, v[i]);
@@ -203,12 +203,12 @@ __global__ __launch_bounds__((ColsShape<CT, LG>::NT)) void k_fft2_cols_solve(Fft
   const int f = threadIdx.x / TPL, t = threadIdx.x & (TPL - 1);
   // XCD-aware column order (the grid is padded to a multiple of 8)
   const int NB = A.NBy, jy = xcd_item(blockIdx.x, gridDim.x);
-  const int64_t FS = (int64_t)N * NB;
+  const int64_t FS = Spec2<CT>::field(N, NB);
   const bool mine = f < 3 && jy < NB;
   cpx<CT> w[F::NTW], v[E];
   F::load_tw(A.twx, t, w);
 #pragma unroll
-  for (int i = 0; i < E; ++i) v[i] = mine ? A.spec[f * FS + (int64_t)(t + i * TPL) * NB + jy] : cpx<CT>{0, 0};
+  for (int i = 0; i < E; ++i) v[i] = mine ? A.spec[f * FS + Spec2<CT>::at(t + i * TPL, jy, N)] : cpx<CT>{0, 0};
   if (A.decide) {
     // Algorithm 1 with the row pass fused into the sweep: decide here; if
     // accepted, reconstruct m^{n+1} over the whole field instead
@@ -265,7 +265,7 @@ __global__ __launch_bounds__((ColsShape<CT, LG>::NT)) void k_fft2_cols_solve(Fft
     wave_fence();
   F::template run<+1>(v, t, (F::NX & 1) ? a : b, s, w);
 #pragma unroll
-  for (int i = 0; i < E; ++i) A.spec[f * FS + (int64_t)(t + i * TPL) * NB + jy] = v[i];
+  for (int i = 0; i < E; ++i) A.spec[f * FS + Spec2<CT>::at(t + i * TPL, jy, N)] = v[i];
 }
 
 // Pass 3: inverse transform along y from the half band to real rows.  The
@@ -285,7 +285,7 @@ __global__ __launch_bounds__((RowsShape<CT, LG>::NT)) void k_fft2_rows_inv(Fft2A
   if (A.g.skip()) return;
   if (F::WAVE && x >= A.Nx) return;
   const int NB = A.NBy;
-  const int64_t FS = (int64_t)A.Nx * NB, o = (int64_t)x * NB;
+  const int64_t FS = Spec2<CT>::field(A.Nx, NB);
   cpx<CT> v[E];
 #pragma unroll
   for (int i = 0; i < E; ++i) {
@@ -294,8 +294,9 @@ __global__ __launch_bounds__((RowsShape<CT, LG>::NT)) void k_fft2_rows_inv(Fft2A
     const int jj = lower ? j : N - j;
     v[i] = {0, 0};
     if (jj < NB) {
-      cpx<CT> a0 = A.spec[((line & 1) ? 2 * FS : 0) + o + jj];
-      cpx<CT> a1 = (line & 1) ? cpx<CT>{0, 0} : A.spec[FS + o + jj];
+      const int64_t o = Spec2<CT>::at(x, jj, A.Nx);
+      cpx<CT> a0 = A.spec[((line & 1) ? 2 * FS : 0) + o];
+      cpx<CT> a1 = (line & 1) ? cpx<CT>{0, 0} : A.spec[FS + o];
       if (j == 0) {
         a0.y = 0;
         a1.y = 0;
@@ -325,242 +326,314 @@ __global__ __launch_bounds__((RowsShape<CT, LG>::NT)) void k_fft2_rows_inv(Fft2A
 // Five passes over the band |j_alpha| <= N_alpha/4: forward along z (real
 // input, keeps j_z = 0..N_z/4), forward along y (keeps the y band), along x
 // with the FP64 4x4 Schur solve of Eq. (schur) between the forward and
-// inverse transforms, inverse along y, inverse along z to real fields.
-// spec1 holds [field][x][y][j_z] (after the z passes), spec2 holds
-// [field][x][band_y][j_z] (after the y passes).
+// inverse transforms, inverse along y, inverse along z to real fields.  spec1
+// holds the band after the z passes, spec2 after the y passes (Spec3).
 template <class CT, class TM>
 struct Fft3Args {
   CorrGuard g;
   int do_accept;
   int adjoint;
-  int Nx, Ny, Nz, lgx, lgy, lgz;
+  int Nx, Ny, Nz;
   int NBz;  // N_z/4 + 1
   int NBy;  // 2 (N_y/4) + 1 retained y indices
-  int pencils_per_block, cols_per_block;
   const TM* Pr;        // 4 x N_sites
   TM* dm;              // 4 x N_sites
-  cpx<CT>* spec1;      // 4 x Nx*Ny x NBz
-  cpx<CT>* spec2;      // 4 x Nx*NBy x NBz
+  cpx<CT>* spec1;      // 4 fields, every y
+  cpx<CT>* spec2;      // 4 fields, band of y
   const cpx<CT>* twx;
   const cpx<CT>* twy;
   const cpx<CT>* twz;
   double a, nu, inv_ns;
 };
 
+// The spectra keep groups of G = 64 bytes of neighbouring j_z together, with
+// the axis that the y passes run along next: [field][x][j_z / G][y][j_z % G]
+// and [field][j_z / G][x][band y][j_z % G].  A y line then reads consecutive
+// 64-byte pieces, an x line pieces N_By apart.
+template <class CT>
+struct Spec3 {
+  static constexpr int G = 64 / (int)sizeof(cpx<CT>);
+  static __host__ __device__ int groups(int NBz) { return (NBz + G - 1) / G; }
+  static __host__ __device__ int64_t field(int Nx, int Ny, int NBz) { return (int64_t)Nx * groups(NBz) * Ny * G; }
+  static __device__ __forceinline__ int64_t at1(int x, int y, int j, int Ny, int NG) {
+    return (((int64_t)x * NG + j / G) * Ny + y) * G + (j & (G - 1));
+  }
+  static __device__ __forceinline__ int64_t at2(int x, int by, int j, int Nx, int NBy) {
+    return (((int64_t)(j / G) * Nx + x) * NBy + by) * G + (j & (G - 1));
+  }
+};
+
 __device__ inline int band_to_j(int i, int N, int NB) { return (i <= N / 4) ? i : N - (NB - i); }
 
-// pass 1: forward along z of pencils (x, y); fields (0,1) and (2,3) packed.
-// The grid holds as many blocks as the device runs at once and each block
-// loops over groups of R pencils, so that the acceptance decision (a chain
-// of dependent loads) is taken once per block rather than once per group.
-template <class L, class T, class CT, class TM>
-__global__ __launch_bounds__(256) void k_fft3_z_fwd(Fft3Args<CT, TM> A, AcceptArgs<L, T> Ac, FinishArgs Fin) {
-  const int R = A.pencils_per_block, Nz = A.Nz;
-  const int ngrp = (A.Nx * A.Ny) / R;
+// log2 of the elements per thread in the 3D passes, which have thousands of
+// lines: eight from N = 128 up (fewer exchanges per line)
+constexpr int line_le3(int lg) { return lg <= 6 ? 2 : 3; }
+
+// z passes: the two packed lines (fields 0, 1 and 2, 3) of PB pencils per block
+template <class CT, int LG>
+struct ZShape {
+  using F = LineFft<CT, LG, line_le3(LG)>;
+  static constexpr int NT = 2 * F::TPL > 256 ? 2 * F::TPL : 256;
+  static constexpr int LPB = NT / F::TPL, PB = LPB / 2;
+  static constexpr int LDS = LPB * F::N * (F::WAVE ? 1 : 2);
+};
+
+// y and x passes: CW neighbouring j_z columns of the four fields per block,
+// one wavefront per field with the column fastest over its lanes (one column
+// and more threads where a line is longer than a wavefront holds).  The lines
+// of a wavefront are padded apart so that lanes of different columns use
+// different banks.
+template <class CT, int LG>
+struct ColShape3 {
+  using F = LineFft<CT, LG, line_le3(LG)>;
+  static constexpr int CW = F::WAVE ? 64 / F::TPL : 1;
+  static constexpr int FT = CW * F::TPL, NT = 4 * FT;
+  static constexpr int PAD = CW == 1 ? 0 : (256 / (CW * (int)sizeof(cpx<CT>)) > 1 ? 256 / (CW * (int)sizeof(cpx<CT>)) : 1);
+  static constexpr int PITCH = F::N + PAD;
+  static constexpr int LDS = 4 * CW * PITCH * (F::WAVE ? 1 : 2);
+};
+
+// pass 1: forward along z.  The grid holds as many blocks as the device runs
+// at once and each block loops over groups of pencils, so that the acceptance
+// decision (a chain of dependent loads) is taken once per block rather than
+// once per group.
+template <class L, class T, class CT, class TM, int LG>
+__global__ __launch_bounds__((ZShape<CT, LG>::NT)) void k_fft3_z_fwd(Fft3Args<CT, TM> A, AcceptArgs<L, T> Ac,
+                                                                    FinishArgs Fin) {
+  using S = ZShape<CT, LG>;
+  using F = typename S::F;
+  constexpr int N = F::N, E = F::E, TPL = F::TPL;
+  __shared__ cpx<CT> lds[S::LDS];
+  const int line = threadIdx.x / TPL, t = threadIdx.x & (TPL - 1), hf = line & 1;
+  cpx<CT> w[F::NTW];
+  F::load_tw(A.twz, t, w);
   if (A.do_accept) {
-    __shared__ double red[256];
+    __shared__ double red[S::NT / 64];
     const int dec = finish_block(Fin, red);
     if (dec != DEC_RUNNING) {
-      if (dec == DEC_ACCEPTED) {
-        for (int g = blockIdx.x; g < ngrp; g += gridDim.x) {
-          const int64_t s0 = (int64_t)g * R * Nz;
-          accept_sites<L, T>(Ac, s0 + threadIdx.x, s0 + (int64_t)R * Nz, blockDim.x);
-        }
-      }
+      if (dec == DEC_ACCEPTED)
+        accept_sites<L, T>(Ac, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, Ac.NS,
+                           (int64_t)gridDim.x * blockDim.x);
       return;
     }
   } else if (A.g.skip()) {
     return;
   }
-  extern __shared__ unsigned char smem_raw[];
-  cpx<CT>* buf = reinterpret_cast<cpx<CT>*>(smem_raw);
-  cpx<CT>* tmp = buf + 2 * R * Nz;
-  const int64_t NS = (int64_t)A.Nx * A.Ny * Nz;
-  const int NB = A.NBz;
-  const int64_t FS = (int64_t)A.Nx * A.Ny * NB;
+  const int NP = A.Nx * A.Ny, ngrp = (NP + S::PB - 1) / S::PB;
+  const int64_t NS = (int64_t)NP * N;
+  const int NB = A.NBz, NG = Spec3<CT>::groups(NB);
+  const int64_t FS = Spec3<CT>::field(A.Nx, A.Ny, NB);
+  cpx<CT>* a = lds + line * N;
+  cpx<CT>* b = F::WAVE ? a : a + S::LDS / 2;
+  cpx<CT>* nat = (F::NX & 1) ? b : a;
   for (int g = blockIdx.x; g < ngrp; g += gridDim.x) {
-    const int64_t p0 = (int64_t)g * R;
-    for (int i = threadIdx.x; i < R * Nz; i += blockDim.x) {
-      const int r = i / Nz, z = i - r * Nz;
-      const int64_t s = (p0 + r) * Nz + z;
-      buf[(2 * r) * Nz + z] = {(CT)A.Pr[s], (CT)A.Pr[NS + s]};
-      buf[(2 * r + 1) * Nz + z] = {(CT)A.Pr[2 * NS + s], (CT)A.Pr[3 * NS + s]};
-    }
-    __syncthreads();
-    const cpx<CT>* out = lds_fft<CT>(buf, tmp, A.lgz, 2 * R, -1, A.twz);
-    for (int i = threadIdx.x; i < R * NB; i += blockDim.x) {
-      const int r = i / NB, j = i - r * NB;
-      const int64_t o = (p0 + r) * NB + j;
-      for (int h = 0; h < 2; ++h) {
-        const cpx<CT> z = out[(2 * r + h) * Nz + j];
-        const cpx<CT> zc = out[(2 * r + h) * Nz + ((Nz - j) & (Nz - 1))];
-        A.spec1[(2 * h) * FS + o] = {(CT)0.5 * (z.x + zc.x), (CT)0.5 * (z.y - zc.y)};
-        A.spec1[(2 * h + 1) * FS + o] = {(CT)0.5 * (z.y + zc.y), (CT)0.5 * (zc.x - z.x)};
-      }
-    }
-    __syncthreads();  // buf and tmp are refilled by the next group
+    const int p = g * S::PB + (line >> 1);
+    if (F::WAVE && p >= NP) break;  // fewer pencils than one block's
+    const TM* src = A.Pr + 2 * hf * NS + (int64_t)p * N;
+    cpx<CT> v[E];
+#pragma unroll
+    for (int i = 0; i < E; ++i) v[i] = {(CT)src[t + i * TPL], (CT)src[NS + t + i * TPL]};
+    F::template run<-1>(v, t, a, b, w);
+#pragma unroll
+    for (int i = 0; i < E; ++i) nat[t + i * TPL] = v[i];
+    if constexpr (F::WAVE)
+      wave_fence();
+    else
+      __syncthreads();
+    const int x = p / A.Ny, y = p - x * A.Ny;
+    auto store = [&](int j, cpx<CT> z) {
+      const cpx<CT> zc = nat[(N - j) & (N - 1)];
+      const int64_t o = 2 * hf * FS + Spec3<CT>::at1(x, y, j, A.Ny, NG);
+      A.spec1[o] = {(CT)0.5 * (z.x + zc.x), (CT)0.5 * (z.y - zc.y)};
+      A.spec1[FS + o] = {(CT)0.5 * (z.y + zc.y), (CT)0.5 * (zc.x - z.x)};
+    };
+#pragma unroll
+    for (int i = 0; i < E / 4; ++i) store(t + i * TPL, v[i]);
+    if (t == 0) store(N / 4, v[E / 4]);
+    if constexpr (F::WAVE)
+      wave_fence();
+    else
+      __syncthreads();  // the line's LDS is refilled by the next group
   }
 }
 
-// pass 2: forward along y for a group of j_z columns at one x; keep the band
-template <class CT, class TM>
-__global__ __launch_bounds__(256) void k_fft3_y_fwd(Fft3Args<CT, TM> A) {
-  if (A.g.skip()) return;
-  extern __shared__ unsigned char smem_raw[];
-  cpx<CT>* buf = reinterpret_cast<cpx<CT>*>(smem_raw);
-  const int Ny = A.Ny, JB = A.cols_per_block, NBz = A.NBz;
-  cpx<CT>* tmp = buf + 4 * JB * Ny;
-  const int ngroups = (NBz + JB - 1) / JB;
-  const int item = xcd_item(blockIdx.x, gridDim.x);
-  if (item >= A.Nx * ngroups) return;  // grid padding
-  const int x = item / ngroups, j0 = (item % ngroups) * JB;
-  const int64_t FS1 = (int64_t)A.Nx * Ny * NBz, FS2 = (int64_t)A.Nx * A.NBy * NBz;
-  for (int i = threadIdx.x; i < 4 * JB * Ny; i += blockDim.x) {
-    const int c = i % JB, rest = i / JB;
-    const int y = rest % Ny, f = rest / Ny;
-    const int j = j0 + c;
-    buf[(f * JB + c) * Ny + y] = (j < NBz) ? A.spec1[f * FS1 + ((int64_t)x * Ny + y) * NBz + j] : cpx<CT>{0, 0};
+// This thread's field, column and place in its line in a y or x pass.
+template <class S>
+struct Lane3 {
+  int f, c, t;
+  __device__ Lane3() {
+    const int l = threadIdx.x % S::FT;
+    f = threadIdx.x / S::FT;
+    c = l % S::CW;
+    t = l / S::CW;
   }
-  __syncthreads();
-  const cpx<CT>* out = lds_fft<CT>(buf, tmp, A.lgy, 4 * JB, -1, A.twy);
-  for (int i = threadIdx.x; i < 4 * JB * A.NBy; i += blockDim.x) {
-    const int c = i % JB, rest = i / JB;
-    const int bi = rest % A.NBy, f = rest / A.NBy;
-    const int j = j0 + c;
-    if (j < NBz)
-      A.spec2[f * FS2 + ((int64_t)x * A.NBy + bi) * NBz + j] = out[(f * JB + c) * Ny + band_to_j(bi, Ny, A.NBy)];
+};
+
+// pass 2: forward along y for a group of j_z columns at one x; keep the band
+template <class CT, class TM, int LG>
+__global__ __launch_bounds__((ColShape3<CT, LG>::NT)) void k_fft3_y_fwd(Fft3Args<CT, TM> A) {
+  using S = ColShape3<CT, LG>;
+  using F = typename S::F;
+  constexpr int N = F::N, E = F::E, TPL = F::TPL;
+  __shared__ cpx<CT> lds[S::LDS];
+  const Lane3<S> l;
+  cpx<CT> w[F::NTW], v[E];
+  F::load_tw(A.twy, l.t, w);
+  if (A.g.skip()) return;
+  const int NBz = A.NBz, NG = Spec3<CT>::groups(NBz), nc = (NBz + S::CW - 1) / S::CW;
+  const int item = xcd_item(blockIdx.x, gridDim.x);
+  if (item >= A.Nx * nc) return;  // grid padding
+  const int x = item / nc, j = (item % nc) * S::CW + l.c;
+  const int64_t FS1 = Spec3<CT>::field(A.Nx, N, NBz), FS2 = Spec3<CT>::field(A.Nx, A.NBy, NBz);
+#pragma unroll
+  for (int i = 0; i < E; ++i)
+    v[i] = (j < NBz) ? A.spec1[l.f * FS1 + Spec3<CT>::at1(x, l.t + i * TPL, j, N, NG)] : cpx<CT>{0, 0};
+  cpx<CT>* a = lds + (l.f * S::CW + l.c) * S::PITCH;
+  F::template run<-1>(v, l.t, a, F::WAVE ? a : a + S::LDS / 2, w);
+  if (j >= NBz) return;
+#pragma unroll
+  for (int i = 0; i < E; ++i) {
+    const int jy = l.t + i * TPL;
+    const int by = (jy <= N / 4) ? jy : ((N - jy <= N / 4) ? A.NBy - (N - jy) : -1);
+    if (by >= 0) A.spec2[l.f * FS2 + Spec3<CT>::at2(x, by, j, A.Nx, A.NBy)] = v[i];
   }
 }
 
 // pass 3: along x for a group of j_z columns at one band-y index: forward,
 // FP64 Schur solve on |j_x| <= N_x/4 (zero elsewhere), inverse; in place
-template <class CT, class TM>
-__global__ __launch_bounds__(256) void k_fft3_x_solve(Fft3Args<CT, TM> A) {
+template <class CT, class TM, int LG>
+__global__ __launch_bounds__((ColShape3<CT, LG>::NT)) void k_fft3_x_solve(Fft3Args<CT, TM> A) {
+  using S = ColShape3<CT, LG>;
+  using F = typename S::F;
+  constexpr int N = F::N, E = F::E, TPL = F::TPL, CW = S::CW;
+  __shared__ cpx<CT> lds[S::LDS];
+  const Lane3<S> l;
+  cpx<CT> w[F::NTW], v[E];
+  F::load_tw(A.twx, l.t, w);
   if (A.g.skip()) return;
-  extern __shared__ unsigned char smem_raw[];
-  cpx<CT>* buf = reinterpret_cast<cpx<CT>*>(smem_raw);
-  const int Nx = A.Nx, JB = A.cols_per_block, NBz = A.NBz, NBy = A.NBy;
-  cpx<CT>* tmp = buf + 4 * JB * Nx;
-  const int ngroups = (NBz + JB - 1) / JB;
+  const int NBz = A.NBz, NBy = A.NBy, nc = (NBz + CW - 1) / CW;
   const int item = xcd_item(blockIdx.x, gridDim.x);
-  if (item >= NBy * ngroups) return;  // grid padding
-  const int bi = item / ngroups, j0 = (item % ngroups) * JB;
-  const int64_t FS2 = (int64_t)Nx * NBy * NBz;
-  for (int i = threadIdx.x; i < 4 * JB * Nx; i += blockDim.x) {
-    const int c = i % JB, rest = i / JB;
-    const int x = rest % Nx, f = rest / Nx;
-    const int j = j0 + c;
-    buf[(f * JB + c) * Nx + x] = (j < NBz) ? A.spec2[f * FS2 + ((int64_t)x * NBy + bi) * NBz + j] : cpx<CT>{0, 0};
-  }
+  if (item >= NBy * nc) return;  // grid padding
+  const int by = item / nc, j0 = (item % nc) * CW, j = j0 + l.c;
+  const int64_t FS2 = Spec3<CT>::field(N, NBy, NBz);
+#pragma unroll
+  for (int i = 0; i < E; ++i)
+    v[i] = (j < NBz) ? A.spec2[l.f * FS2 + Spec3<CT>::at2(l.t + i * TPL, by, j, N, NBy)] : cpx<CT>{0, 0};
+  cpx<CT>* a = lds + (l.f * CW + l.c) * S::PITCH;
+  cpx<CT>* b = F::WAVE ? a : a + S::LDS / 2;
+  F::template run<-1>(v, l.t, a, b, w);
+  // the band of the four spectra meets in LDS (see the 2D column pass)
+  cpx<CT>* s = (F::NX & 1) ? b : a;
+  cpx<CT>* base = lds + ((!F::WAVE && (F::NX & 1)) ? S::LDS / 2 : 0);
+#pragma unroll
+  for (int i = 0; i < E; ++i)
+    if (in_band(signed_index(l.t + i * TPL, N), N)) s[l.t + i * TPL] = v[i];
   __syncthreads();
-  cpx<CT>* F = lds_fft<CT>(buf, tmp, A.lgx, 4 * JB, -1, A.twx);
-  cpx<CT>* Gb = (F == buf) ? tmp : buf;
   const double two_pi = 6.283185307179586476925286766559;
-  const int sjy = signed_index(band_to_j(bi, A.Ny, NBy), A.Ny);
-  for (int i = threadIdx.x; i < JB * Nx; i += blockDim.x) {
-    const int c = i / Nx, jx = i - c * Nx;
-    const int jz = j0 + c;
-    const int sjx = signed_index(jx, Nx);
-    if (jz < NBz && in_band(sjx, Nx)) {
-      double kv[3] = {two_pi * sjx / Nx, two_pi * sjy / A.Ny, two_pi * jz / A.Nz};
-      double r[4][2], o[4][2];
-      for (int f = 0; f < 4; ++f) {
-        const cpx<CT> v = F[(f * JB + c) * Nx + jx];
-        r[f][0] = (double)v.x;
-        r[f][1] = (double)v.y;
-      }
-      if (A.adjoint)
-        schur_solve_adjoint<3>(kv, r, A.a, A.nu, A.inv_ns, o);
-      else
-        schur_solve<3>(kv, r, A.a, A.nu, A.inv_ns, o);
-      for (int f = 0; f < 4; ++f) Gb[(f * JB + c) * Nx + jx] = {(CT)o[f][0], (CT)o[f][1]};
-    } else {
-      for (int f = 0; f < 4; ++f) Gb[(f * JB + c) * Nx + jx] = {(CT)0, (CT)0};
+  const int sjy = signed_index(band_to_j(by, A.Ny, NBy), A.Ny);
+  for (int i = threadIdx.x; i < CW * (N / 2 + 1); i += S::NT) {
+    const int c = i % CW, q = i / CW;
+    if (j0 + c >= NBz) continue;
+    const int jx = q <= N / 4 ? q : q + N / 2 - 1;
+    const double kv[3] = {two_pi * signed_index(jx, N) / N, two_pi * sjy / A.Ny, two_pi * (j0 + c) / A.Nz};
+    double r[4][2], o[4][2];
+    cpx<CT>* e = base + c * S::PITCH + jx;
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+      r[f][0] = (double)e[f * CW * S::PITCH].x;
+      r[f][1] = (double)e[f * CW * S::PITCH].y;
     }
+    if (A.adjoint)
+      schur_solve_adjoint<3>(kv, r, A.a, A.nu, A.inv_ns, o);
+    else
+      schur_solve<3>(kv, r, A.a, A.nu, A.inv_ns, o);
+#pragma unroll
+    for (int f = 0; f < 4; ++f) e[f * CW * S::PITCH] = {(CT)o[f][0], (CT)o[f][1]};
   }
   __syncthreads();
-  cpx<CT>* H = lds_fft<CT>(Gb, F, A.lgx, 4 * JB, +1, A.twx);
-  for (int i = threadIdx.x; i < 4 * JB * Nx; i += blockDim.x) {
-    const int c = i % JB, rest = i / JB;
-    const int x = rest % Nx, f = rest / Nx;
-    const int j = j0 + c;
-    if (j < NBz) A.spec2[f * FS2 + ((int64_t)x * NBy + bi) * NBz + j] = H[(f * JB + c) * Nx + x];
-  }
+#pragma unroll
+  for (int i = 0; i < E; ++i)
+    v[i] = in_band(signed_index(l.t + i * TPL, N), N) ? s[l.t + i * TPL] : cpx<CT>{0, 0};
+  if constexpr (F::WAVE) wave_fence();
+  F::template run<+1>(v, l.t, (F::NX & 1) ? a : b, s, w);
+  if (j >= NBz) return;
+#pragma unroll
+  for (int i = 0; i < E; ++i) A.spec2[l.f * FS2 + Spec3<CT>::at2(l.t + i * TPL, by, j, N, NBy)] = v[i];
 }
 
 // pass 4: inverse along y from the band to every y, for a group of j_z at x
-template <class CT, class TM>
-__global__ __launch_bounds__(256) void k_fft3_y_inv(Fft3Args<CT, TM> A) {
+template <class CT, class TM, int LG>
+__global__ __launch_bounds__((ColShape3<CT, LG>::NT)) void k_fft3_y_inv(Fft3Args<CT, TM> A) {
+  using S = ColShape3<CT, LG>;
+  using F = typename S::F;
+  constexpr int N = F::N, E = F::E, TPL = F::TPL;
+  __shared__ cpx<CT> lds[S::LDS];
+  const Lane3<S> l;
+  cpx<CT> w[F::NTW], v[E];
+  F::load_tw(A.twy, l.t, w);
   if (A.g.skip()) return;
-  extern __shared__ unsigned char smem_raw[];
-  cpx<CT>* buf = reinterpret_cast<cpx<CT>*>(smem_raw);
-  const int Ny = A.Ny, JB = A.cols_per_block, NBz = A.NBz, NBy = A.NBy;
-  cpx<CT>* tmp = buf + 4 * JB * Ny;
-  const int ngroups = (NBz + JB - 1) / JB;
+  const int NBz = A.NBz, NG = Spec3<CT>::groups(NBz), nc = (NBz + S::CW - 1) / S::CW;
   const int item = xcd_item(blockIdx.x, gridDim.x);
-  if (item >= A.Nx * ngroups) return;  // grid padding
-  const int x = item / ngroups, j0 = (item % ngroups) * JB;
-  const int64_t FS1 = (int64_t)A.Nx * Ny * NBz, FS2 = (int64_t)A.Nx * NBy * NBz;
-  for (int i = threadIdx.x; i < 4 * JB * Ny; i += blockDim.x) {
-    const int c = i % JB, rest = i / JB;
-    const int jy = rest % Ny, f = rest / Ny;
-    const int j = j0 + c;
-    cpx<CT> v = {0, 0};
-    const int bi = (jy <= Ny / 4) ? jy : ((Ny - jy <= Ny / 4) ? NBy - (Ny - jy) : -1);
-    if (j < NBz && bi >= 0) v = A.spec2[f * FS2 + ((int64_t)x * NBy + bi) * NBz + j];
-    buf[(f * JB + c) * Ny + jy] = v;
+  if (item >= A.Nx * nc) return;  // grid padding
+  const int x = item / nc, j = (item % nc) * S::CW + l.c;
+  const int64_t FS1 = Spec3<CT>::field(A.Nx, N, NBz), FS2 = Spec3<CT>::field(A.Nx, A.NBy, NBz);
+#pragma unroll
+  for (int i = 0; i < E; ++i) {
+    const int jy = l.t + i * TPL;
+    const int by = (jy <= N / 4) ? jy : ((N - jy <= N / 4) ? A.NBy - (N - jy) : -1);
+    v[i] = (j < NBz && by >= 0) ? A.spec2[l.f * FS2 + Spec3<CT>::at2(x, by, j, A.Nx, A.NBy)] : cpx<CT>{0, 0};
   }
-  __syncthreads();
-  const cpx<CT>* out = lds_fft<CT>(buf, tmp, A.lgy, 4 * JB, +1, A.twy);
-  for (int i = threadIdx.x; i < 4 * JB * Ny; i += blockDim.x) {
-    const int c = i % JB, rest = i / JB;
-    const int y = rest % Ny, f = rest / Ny;
-    const int j = j0 + c;
-    if (j < NBz) A.spec1[f * FS1 + ((int64_t)x * Ny + y) * NBz + j] = out[(f * JB + c) * Ny + y];
-  }
+  cpx<CT>* a = lds + (l.f * S::CW + l.c) * S::PITCH;
+  F::template run<+1>(v, l.t, a, F::WAVE ? a : a + S::LDS / 2, w);
+  if (j >= NBz) return;
+#pragma unroll
+  for (int i = 0; i < E; ++i) A.spec1[l.f * FS1 + Spec3<CT>::at1(x, l.t + i * TPL, j, N, NG)] = v[i];
 }
 
 // pass 5: inverse along z from j_z = 0..N_z/4 (conjugate-symmetric
 // extension, real part at j_z = 0) to real fields; (0,1) and (2,3) packed
-template <class CT, class TM>
-__global__ __launch_bounds__(256) void k_fft3_z_inv(Fft3Args<CT, TM> A) {
+template <class CT, class TM, int LG>
+__global__ __launch_bounds__((ZShape<CT, LG>::NT)) void k_fft3_z_inv(Fft3Args<CT, TM> A) {
+  using S = ZShape<CT, LG>;
+  using F = typename S::F;
+  constexpr int N = F::N, E = F::E, TPL = F::TPL;
+  __shared__ cpx<CT> lds[S::LDS];
+  const int line = threadIdx.x / TPL, t = threadIdx.x & (TPL - 1), hf = line & 1;
+  cpx<CT> w[F::NTW], v[E];
+  F::load_tw(A.twz, t, w);
   if (A.g.skip()) return;
-  extern __shared__ unsigned char smem_raw[];
-  cpx<CT>* buf = reinterpret_cast<cpx<CT>*>(smem_raw);
-  const int R = A.pencils_per_block, Nz = A.Nz, NB = A.NBz;
-  cpx<CT>* tmp = buf + 2 * R * Nz;
-  const int64_t p0 = (int64_t)blockIdx.x * R;
-  const int64_t FS = (int64_t)A.Nx * A.Ny * NB;
-  for (int i = threadIdx.x; i < R * Nz; i += blockDim.x) {
-    const int r = i / Nz, j = i - r * Nz;
-    const int64_t o = (p0 + r) * NB;
-    cpx<CT> v[4] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};
-    if (j < NB) {
-      for (int f = 0; f < 4; ++f) {
-        v[f] = A.spec1[f * FS + o + j];
-        if (j == 0) v[f].y = 0;
+  const int NP = A.Nx * A.Ny, p = blockIdx.x * S::PB + (line >> 1);
+  if (F::WAVE && p >= NP) return;
+  const int64_t NS = (int64_t)NP * N;
+  const int NB = A.NBz, NG = Spec3<CT>::groups(NB);
+  const int64_t FS = Spec3<CT>::field(A.Nx, A.Ny, NB);
+  const int x = p / A.Ny, y = p - x * A.Ny;
+#pragma unroll
+  for (int i = 0; i < E; ++i) {
+    const int j = t + i * TPL;
+    const bool lower = j < NB;
+    const int jj = lower ? j : N - j;
+    v[i] = {0, 0};
+    if (jj < NB) {
+      const int64_t o = 2 * hf * FS + Spec3<CT>::at1(x, y, jj, A.Ny, NG);
+      cpx<CT> a0 = A.spec1[o], a1 = A.spec1[FS + o];
+      if (j == 0) {
+        a0.y = 0;
+        a1.y = 0;
+      } else if (!lower) {
+        a0.y = -a0.y;
+        a1.y = -a1.y;
       }
-    } else if (Nz - j < NB) {
-      for (int f = 0; f < 4; ++f) {
-        v[f] = A.spec1[f * FS + o + (Nz - j)];
-        v[f].y = -v[f].y;
-      }
+      v[i] = {a0.x - a1.y, a0.y + a1.x};  // pack a0 + i a1
     }
-    buf[(2 * r) * Nz + j] = {v[0].x - v[1].y, v[0].y + v[1].x};
-    buf[(2 * r + 1) * Nz + j] = {v[2].x - v[3].y, v[2].y + v[3].x};
   }
-  __syncthreads();
-  const cpx<CT>* out = lds_fft<CT>(buf, tmp, A.lgz, 2 * R, +1, A.twz);
-  const int64_t NS = (int64_t)A.Nx * A.Ny * Nz;
-  for (int i = threadIdx.x; i < R * Nz; i += blockDim.x) {
-    const int r = i / Nz, z = i - r * Nz;
-    const int64_t s = (p0 + r) * Nz + z;
-    const cpx<CT> a = out[(2 * r) * Nz + z];
-    const cpx<CT> b = out[(2 * r + 1) * Nz + z];
-    A.dm[s] = (TM)a.x;
-    A.dm[NS + s] = (TM)a.y;
-    A.dm[2 * NS + s] = (TM)b.x;
-    A.dm[3 * NS + s] = (TM)b.y;
+  cpx<CT>* a = lds + line * N;
+  F::template run<+1>(v, t, a, F::WAVE ? a : a + S::LDS / 2, w);
+  TM* dst = A.dm + 2 * hf * NS + (int64_t)p * N;
+#pragma unroll
+  for (int i = 0; i < E; ++i) {
+    dst[t + i * TPL] = (TM)v[i].x;
+    dst[NS + t + i * TPL] = (TM)v[i].y;
   }
 }
 

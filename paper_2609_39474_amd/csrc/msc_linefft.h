@@ -19,7 +19,9 @@
 // which the whole block takes part.
 #pragma once
 
+#include <cmath>
 #include <type_traits>
+#include <vector>
 
 #include "msc_ldsfft.h"
 
@@ -86,19 +88,28 @@ struct LineFft {
   }
   static constexpr int NTW = tw_before(NST) > 0 ? tw_before(NST) : 1;
 
-  // this thread's twiddles exp(-2 pi i m k / (R Ns)) of every stage, from the
-  // table exp(-2 pi i j / N)
-  template <int P = 1>
-  static __device__ __forceinline__ void load_tw(const cpx<CT>* __restrict__ tw, int t, cpx<CT>* w) {
-    if constexpr (P < NST) {
-      constexpr int R = 1 << lr(P), LNS = P * LE, NB = E / R;
+  // Twiddles exp(-2 pi i m k / (R Ns)) of every stage, entry by entry with t
+  // fastest, so that a wavefront's loads are contiguous: as gathers from the
+  // table of the N roots they were 64 cache lines each and cost more than the
+  // transform (no-op launches of the N = 1024 column pass 11.8 us).  This part
+  // of an axis's table (twiddle_tables) starts at TW_AT.
+  static constexpr int TW_AT = N + (LE == 3 ? LineFft<CT, LG, 2>::NTW * LineFft<CT, LG, 2>::TPL : 0);
+  static void fill_tw(cpx<CT>* table) {
+    for (int p = 1; p < NST; ++p) {
+      const int R = 1 << lr(p), lns = p * LE, nb = E / R;
+      for (int b = 0; b < nb; ++b)
+        for (int m = 1; m < R; ++m)
+          for (int t = 0; t < TPL; ++t) {
+            const int k = (t + b * TPL) & ((1 << lns) - 1);
+            table[TW_AT + (tw_before(p) + b * (R - 1) + m - 1) * TPL + t] = table[m * k * ((N / R) >> lns)];
+          }
+    }
+  }
+  // this thread's, from an axis's table
+  static __device__ __forceinline__ void load_tw(const cpx<CT>* __restrict__ table, int t, cpx<CT>* w) {
+    if constexpr (NST > 1) {
 #pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        const int k = (t + b * TPL) & ((1 << LNS) - 1);
-#pragma unroll
-        for (int m = 1; m < R; ++m) w[tw_before(P) + b * (R - 1) + m - 1] = tw[m * k * (N / R >> LNS)];
-      }
-      load_tw<P + 1>(tw, t, w);
+      for (int e = 0; e < NTW; ++e) w[e] = table[TW_AT + e * TPL + t];
     }
   }
 
@@ -146,6 +157,21 @@ struct LineFft {
   }
 };
 
+// Element (x, j) of one field of the 2D band spectrum: groups of G columns (one
+// 128-byte line), x inside a group, so the column pass, one column per block,
+// reads consecutive lines that G neighbouring columns share.  (With j fastest
+// over the whole band the column's elements lay N_y/4 + 1 apart, 8 x 256 + 8
+// bytes at N = 1024 FP32, so that most of them met in two of an L2's 16
+// channels.)
+template <class CT>
+struct Spec2 {
+  static constexpr int G = 128 / (int)sizeof(cpx<CT>);
+  static __host__ __device__ int64_t field(int Nx, int NB) { return (int64_t)((NB + G - 1) / G) * G * Nx; }
+  static __device__ __forceinline__ int64_t at(int x, int j, int Nx) {
+    return ((int64_t)(j / G) * Nx + x) * G + (j & (G - 1));
+  }
+};
+
 constexpr int ilog2c(int n) { return n <= 1 ? 0 : 1 + ilog2c(n / 2); }
 
 // log2 of the elements per thread where a few lines run alone (the 2D passes):
@@ -161,6 +187,28 @@ void with_lg(int lg, F&& f) {
     f(std::integral_constant<int, LO>{});
   else if constexpr (LO < HI)
     with_lg<LO + 1, HI>(lg, f);
+}
+
+// An axis's table on the host: the N roots exp(-2 pi i j / N), then the
+// transforms' own order of them for four and for eight elements per thread.
+template <class CT>
+std::vector<cpx<CT>> twiddle_tables(int lg) {
+  std::vector<cpx<CT>> table;
+  with_lg<2, 12>(lg, [&](auto c) {
+    constexpr int LG = c.value, N = 1 << LG;
+    using F2 = LineFft<CT, LG, 2>;
+    int size = F2::TW_AT + F2::NTW * F2::TPL;
+    if constexpr (LG >= 3) size = LineFft<CT, LG, 3>::TW_AT + LineFft<CT, LG, 3>::NTW * LineFft<CT, LG, 3>::TPL;
+    table.assign(size, cpx<CT>{0, 0});
+    const double two_pi = 6.283185307179586476925286766559;
+    for (int i = 0; i < N; ++i) {
+      const double ang = -two_pi * (double)i / (double)N;
+      table[i] = {(CT)std::cos(ang), (CT)std::sin(ang)};
+    }
+    F2::fill_tw(table.data());
+    if constexpr (LG >= 3) LineFft<CT, LG, 3>::fill_tw(table.data());
+  });
+  return table;
 }
 
 }  // namespace msc

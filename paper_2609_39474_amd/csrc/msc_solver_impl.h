@@ -75,7 +75,6 @@ class Solver : public SolverBase {
       sync();
       choose_sweep();
       ensure_partials(sweep_grid_max());
-      if (spec && corrector_supported()) set_fft_attrs();
       if (gexec) (void)hipGraphExecDestroy(gexec);
       if (graph) (void)hipGraphDestroy(graph);
       gexec = nullptr;
@@ -1238,17 +1237,16 @@ class Solver : public SolverBase {
     if (corrector_supported()) {
       if (D == 2) {
         const int NB = G.N2 / 4 + 1;
-        spec = keep((cpx<CT>*)dalloc(sizeof(cpx<CT>) * 3 * (int64_t)G.N0 * NB));
-        spec_alt = keep((cpx<CT>*)dalloc(sizeof(cpx<CT>) * 3 * (int64_t)G.N0 * NB));
+        spec = keep((cpx<CT>*)dalloc(sizeof(cpx<CT>) * 3 * Spec2<CT>::field(G.N0, NB)));
+        spec_alt = keep((cpx<CT>*)dalloc(sizeof(cpx<CT>) * 3 * Spec2<CT>::field(G.N0, NB)));
         tw[0] = make_twiddles(G.N0);
         tw[2] = make_twiddles(G.N2);
       } else {
         const int NBz = G.n[2] / 4 + 1, NBy = 2 * (G.n[1] / 4) + 1;
-        spec = keep((cpx<CT>*)dalloc(sizeof(cpx<CT>) * 4 * (int64_t)G.n[0] * G.n[1] * NBz));
-        spec2 = keep((cpx<CT>*)dalloc(sizeof(cpx<CT>) * 4 * (int64_t)G.n[0] * NBy * NBz));
+        spec = keep((cpx<CT>*)dalloc(sizeof(cpx<CT>) * 4 * Spec3<CT>::field(G.n[0], G.n[1], NBz)));
+        spec2 = keep((cpx<CT>*)dalloc(sizeof(cpx<CT>) * 4 * Spec3<CT>::field(G.n[0], NBy, NBz)));
         for (int a = 0; a < 3; ++a) tw[a] = make_twiddles(G.n[a]);
       }
-      set_fft_attrs();
     }
     if (wallkin() && wall_supported()) wall_allocate();
     if ((fullsym() || wallkin()) && fs_supported()) {
@@ -1297,15 +1295,10 @@ class Solver : public SolverBase {
 
   template <class CX = CT>
   cpx<CX>* make_twiddles(int N, std::vector<void*>* owner = nullptr) {
-    std::vector<cpx<CX>> t(N);
-    const double two_pi = 6.283185307179586476925286766559;
-    for (int i = 0; i < N; ++i) {
-      const double ang = -two_pi * (double)i / (double)N;
-      t[i] = {(CX)std::cos(ang), (CX)std::sin(ang)};
-    }
-    cpx<CX>* d = (cpx<CX>*)dalloc(sizeof(cpx<CX>) * N);
+    const std::vector<cpx<CX>> t = twiddle_tables<CX>(ilog2(N));
+    cpx<CX>* d = (cpx<CX>*)dalloc(sizeof(cpx<CX>) * t.size());
     (owner ? owner : &allocs)->push_back((void*)d);
-    MSC_HIPCK(hipMemcpyAsync(d, t.data(), sizeof(cpx<CX>) * N, hipMemcpyHostToDevice, st));
+    MSC_HIPCK(hipMemcpyAsync(d, t.data(), sizeof(cpx<CX>) * t.size(), hipMemcpyHostToDevice, st));
     sync();  // t goes out of scope
     return d;
   }
@@ -1551,16 +1544,15 @@ class Solver : public SolverBase {
         } else {
           using C2 = cpx<double>;
           if (D == 2) {
-            adj_x.spec1 = (C2*)get(sizeof(C2) * 3 * (size_t)G.N0 * (G.N2 / 4 + 1));
+            adj_x.spec1 = (C2*)get(sizeof(C2) * 3 * (size_t)Spec2<double>::field(G.N0, G.N2 / 4 + 1));
             adj_x.tw[0] = make_twiddles<double>(G.N0, &adj_allocs);
             adj_x.tw[2] = make_twiddles<double>(G.N2, &adj_allocs);
           } else {
             const int NBz = G.n[2] / 4 + 1, NBy = 2 * (G.n[1] / 4) + 1;
-            adj_x.spec1 = (C2*)get(sizeof(C2) * 4 * (size_t)G.n[0] * G.n[1] * NBz);
-            adj_x.spec2 = (C2*)get(sizeof(C2) * 4 * (size_t)G.n[0] * NBy * NBz);
+            adj_x.spec1 = (C2*)get(sizeof(C2) * 4 * (size_t)Spec3<double>::field(G.n[0], G.n[1], NBz));
+            adj_x.spec2 = (C2*)get(sizeof(C2) * 4 * (size_t)Spec3<double>::field(G.n[0], NBy, NBz));
             for (int a = 0; a < 3; ++a) adj_x.tw[a] = make_twiddles<double>(G.n[a], &adj_allocs);
           }
-          set_fft_attrs<double, double>();
         }
       }
     }
@@ -2035,79 +2027,25 @@ class Solver : public SolverBase {
     return Ac;
   }
 
-  // 3D launch shapes: pencils per block of the z passes, j_z columns per
-  // block of the y and x passes
-  int fft3_pencils_per_block(size_t c = sizeof(cpx<CT>)) const {
-    int R = (int)std::max<size_t>(1, (size_t)65536 / (4 * G.n[2] * c));
-    int p = 1;
-    while (p * 2 <= R) p *= 2;
-    if (tune.fft3_pencils > 0) {
-      int q = 1;
-      while (q * 2 <= tune.fft3_pencils) q *= 2;
-      return std::min(p, q);
-    }
-    // at most four pencils per block: more, smaller blocks hide the latency
-    // of the LDS passes better (measured at N = 128: 7% per step over 16)
-    p = std::min(p, 4);
-    while (p > 1 && ((int64_t)G.n[0] * G.n[1]) / p < 256) p >>= 1;
-    return p;
-  }
-  int fft3_cols_per_block(size_t c = sizeof(cpx<CT>)) const {
-    const int Nmax = std::max(G.n[0], G.n[1]);
-    int J = (int)std::max<size_t>(1, (size_t)98304 / (8 * Nmax * c));
-    J = std::min(J, 8);
-    if (tune.fft3_cols > 0)
-      J = std::min(J, tune.fft3_cols);
-    else
-      J = std::min(J, 2);  // as for the pencils: smaller blocks, more of them per CU
-                           // (N = 128 march: FP64 0.835 -> 0.807 ms per step, FP32
-                           // 0.558 -> 0.546 against four columns)
-    return std::max(J, 1);
-  }
-
   // Blocks of a kernel that the device holds at once (occupancy per CU times
-  // the CU count) for a block size and dynamic LDS size, cached: the grid of
-  // the grid-resident passes (any grid size gives the same results).
+  // the CU count) for a block size, cached: the grid of the grid-resident
+  // passes (any grid size gives the same results).
   struct Resident {
     const void* k;
-    int threads;
-    size_t lds;
-    int blocks;
+    int threads, blocks;
   };
   std::vector<Resident> resident_cache;
-  int resident_blocks(const void* k, int threads, size_t lds) {
+  int resident_blocks(const void* k, int threads) {
     for (const auto& e : resident_cache)
-      if (e.k == k && e.threads == threads && e.lds == lds) return e.blocks;
+      if (e.k == k && e.threads == threads) return e.blocks;
     int dev = 0, cus = 0, per_cu = 0;
     MSC_HIPCK(hipGetDevice(&dev));
     MSC_HIPCK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    MSC_HIPCK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, threads, lds));
+    MSC_HIPCK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, threads, 0));
     const int n = std::max(1, per_cu) * std::max(1, cus);
-    resident_cache.push_back({k, threads, lds, n});
+    resident_cache.push_back({k, threads, n});
     return n;
   }
-
-  template <class CX = CT, class TX = TM>
-  void set_fft_attrs() {
-    const size_t c = sizeof(cpx<CX>);
-    if constexpr (D == 3) {
-      const int zb = (int)(4 * fft3_pencils_per_block(c) * G.n[2] * c);
-      const int Nmax = std::max(G.n[0], G.n[1]);
-      const int cb = (int)(8 * fft3_cols_per_block(c) * Nmax * c);
-      MSC_HIPCK(hipFuncSetAttribute((const void*)k_fft3_z_fwd<L, T, CX, TX>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, zb));
-      MSC_HIPCK(hipFuncSetAttribute((const void*)k_fft3_z_inv<CX, TX>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, zb));
-      MSC_HIPCK(hipFuncSetAttribute((const void*)k_fft3_y_fwd<CX, TX>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, cb));
-      MSC_HIPCK(hipFuncSetAttribute((const void*)k_fft3_y_inv<CX, TX>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, cb));
-      MSC_HIPCK(hipFuncSetAttribute((const void*)k_fft3_x_solve<CX, TX>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, cb));
-      resident_blocks((const void*)k_fft3_z_fwd<L, T, CX, TX>, 256, zb);
-    }
-  }
-
 
   // Full-symbol launch shapes: rows per block of the row passes (LDS-limited,
   // >= 512 blocks where the grid allows), j_y columns per block of the
@@ -2272,7 +2210,6 @@ class Solver : public SolverBase {
         });
       MSC_HIPCK(hipGetLastError());
     } else {
-      const size_t cb = sizeof(cpx<CX>);
       Fft3Args<CX, TX> F{};
       F.g = CorrGuard{c, n, ell};
       F.do_accept = Ac ? 1 : 0;
@@ -2280,13 +2217,8 @@ class Solver : public SolverBase {
       F.Nx = G.n[0];
       F.Ny = G.n[1];
       F.Nz = G.n[2];
-      F.lgx = ilog2(F.Nx);
-      F.lgy = ilog2(F.Ny);
-      F.lgz = ilog2(F.Nz);
       F.NBz = F.Nz / 4 + 1;
       F.NBy = 2 * (F.Ny / 4) + 1;
-      F.pencils_per_block = fft3_pencils_per_block(cb);
-      F.cols_per_block = fft3_cols_per_block(cb);
       F.Pr = B.in;
       F.dm = B.out;
       F.spec1 = B.spec1;
@@ -2297,27 +2229,37 @@ class Solver : public SolverBase {
       F.a = a;
       F.nu = nu;
       F.inv_ns = 1.0 / (double)G.NS;
-      const int R = F.pencils_per_block, JB = F.cols_per_block;
-      const size_t zb = 4 * (size_t)R * F.Nz * cb;
-      const size_t yb = 8 * (size_t)JB * F.Ny * cb;
-      const size_t xb = 8 * (size_t)JB * F.Nx * cb;
-      const int ng = (F.NBz + JB - 1) / JB;
-      // z passes: pencil groups of R; the forward pass (which takes the
-      // acceptance decision) at most one block per resident slot, each
-      // looping over groups (measured at N = 128 FP64: full launches 46.5 ->
-      // 42.9 us, decision-only ones 8.1 -> 4.9 us; the same loop made the
-      // inverse pass slower, 34.5 -> 38.3 us, so it keeps one group per block)
-      const int gz = (int)(((int64_t)F.Nx * F.Ny) / R);
-      const int gzf = std::min(gz, resident_blocks((const void*)k_fft3_z_fwd<L, T, CX, TX>, 256, zb));
-      hipLaunchKernelGGL((k_fft3_z_fwd<L, T, CX, TX>), dim3(gzf), dim3(256), zb, st, F, acc, fin);
+      constexpr int LM = sizeof(CX) == 8 ? 10 : 11;  // the longest lines that fit (fft_fits)
+      auto col_grid = [&](int planes, int cw) { return dim3(pad8(planes * ((F.NBz + cw - 1) / cw))); };
+      // z passes: the forward one (which decides) at most one block per
+      // resident slot, each looping over pencil groups
+      with_lg<2, LM>(ilog2(F.Nz), [&](auto lg) {
+        using S = ZShape<CX, lg.value>;
+        const int gz = (F.Nx * F.Ny + S::PB - 1) / S::PB;
+        const int gr = std::min(gz, resident_blocks((const void*)k_fft3_z_fwd<L, T, CX, TX, lg.value>, S::NT));
+        hipLaunchKernelGGL((k_fft3_z_fwd<L, T, CX, TX, lg.value>), dim3(gr), dim3(S::NT), 0, st, F, acc, fin);
+      });
       MSC_HIPCK(hipGetLastError());
-      hipLaunchKernelGGL((k_fft3_y_fwd<CX, TX>), dim3(pad8(F.Nx * ng)), dim3(256), yb, st, F);
+      with_lg<2, LM>(ilog2(F.Ny), [&](auto lg) {
+        using S = ColShape3<CX, lg.value>;
+        hipLaunchKernelGGL((k_fft3_y_fwd<CX, TX, lg.value>), col_grid(F.Nx, S::CW), dim3(S::NT), 0, st, F);
+      });
       MSC_HIPCK(hipGetLastError());
-      hipLaunchKernelGGL((k_fft3_x_solve<CX, TX>), dim3(pad8(F.NBy * ng)), dim3(256), xb, st, F);
+      with_lg<2, LM>(ilog2(F.Nx), [&](auto lg) {
+        using S = ColShape3<CX, lg.value>;
+        hipLaunchKernelGGL((k_fft3_x_solve<CX, TX, lg.value>), col_grid(F.NBy, S::CW), dim3(S::NT), 0, st, F);
+      });
       MSC_HIPCK(hipGetLastError());
-      hipLaunchKernelGGL((k_fft3_y_inv<CX, TX>), dim3(pad8(F.Nx * ng)), dim3(256), yb, st, F);
+      with_lg<2, LM>(ilog2(F.Ny), [&](auto lg) {
+        using S = ColShape3<CX, lg.value>;
+        hipLaunchKernelGGL((k_fft3_y_inv<CX, TX, lg.value>), col_grid(F.Nx, S::CW), dim3(S::NT), 0, st, F);
+      });
       MSC_HIPCK(hipGetLastError());
-      hipLaunchKernelGGL((k_fft3_z_inv<CX, TX>), dim3(gz), dim3(256), zb, st, F);
+      with_lg<2, LM>(ilog2(F.Nz), [&](auto lg) {
+        using S = ZShape<CX, lg.value>;
+        hipLaunchKernelGGL((k_fft3_z_inv<CX, TX, lg.value>), dim3((F.Nx * F.Ny + S::PB - 1) / S::PB), dim3(S::NT), 0,
+                           st, F);
+      });
       MSC_HIPCK(hipGetLastError());
     }
   }

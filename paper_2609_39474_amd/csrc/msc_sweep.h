@@ -228,13 +228,13 @@ struct SweepArgs {
   double inv1pa2_prev, inv_dt, inv_2dt;
   // fused forward row transform (2D, tiles spanning whole rows, Algorithm 1
   // with the shadow corrector): the band spectrum of P r goes to spec
-  // ([field][x][j <= N_y/4], as the first transform pass writes it) instead
+  // (j <= N_y/4, Spec2 layout, as the first transform pass writes it) instead
   // of P r to Pr
   int fuse_rows, lgr, NBr;
   cpx<TM>* spec;
   const cpx<TM>* twr;
   // SW_DTS_LIFT_ROWS: the solved band spectrum of the previous correction
-  // ([field][x][j <= N_y/4]), inverted along y by the sweep to give dm
+  // (Spec2 layout), inverted along y by the sweep to give dm
   const cpx<TM>* spec_in;
   // D2Q9 lid-driven cavity: wall rows after streaming (every mode)
   int walls;
@@ -658,16 +658,17 @@ __device__ __forceinline__ void row_spectrum(const SweepArgs<T, TM>& A, cpx<CT>*
   for (int i = 0; i < 4; ++i) ln[t + i * F::TPL] = v[i];
   wave_fence();
   const int NB = A.NBr;
-  const int64_t FS = (int64_t)A.N0 * NB, o = (int64_t)xd * NB;
+  const int64_t FS = Spec2<CT>::field(A.N0, NB);
   auto store = [&](int j, cpx<CT> z) {
+    const int64_t o = Spec2<CT>::at(xd, j, A.N0);
     if (line) {
-      A.spec[2 * FS + o + j] = z;
+      A.spec[2 * FS + o] = z;
       return;
     }
     // unpack: F0 = (Z(j) + conj Z(-j))/2, F1 = (Z(j) - conj Z(-j))/(2i)
     const cpx<CT> zc = ln[(T2 - j) & (T2 - 1)];
-    A.spec[o + j] = {(CT)0.5 * (z.x + zc.x), (CT)0.5 * (z.y - zc.y)};
-    A.spec[FS + o + j] = {(CT)0.5 * (z.y + zc.y), (CT)0.5 * (zc.x - z.x)};
+    A.spec[o] = {(CT)0.5 * (z.x + zc.x), (CT)0.5 * (z.y - zc.y)};
+    A.spec[FS + o] = {(CT)0.5 * (z.y + zc.y), (CT)0.5 * (zc.x - z.x)};
   };
   store(t, v[0]);
   if (t == 0) store(F::TPL, v[1]);

@@ -52,7 +52,7 @@ __global__ __launch_bounds__(3 * T2) void k_sweep_rows(SweepArgs<T, TM> A) {
   using F = LineFft<CT, LG, 2>;
   cpx<CT> tw[F::NTW];
   // (the table is there only for sweeps that transform rows)
-  if (DUAL && A.fuse_rows) F::load_tw(A.twr, tid & (F::TPL - 1), tw);
+  if (DUAL && A.fuse_rows && tid < (ROWINV ? 6 : 2) * F::TPL) F::load_tw(A.twr, tid & (F::TPL - 1), tw);
   if constexpr (ROWINV) {
     // inverse transform along y of the band spectrum rows of the three source
     // planes (the conjugate-symmetric extension of each field's half band,
@@ -60,23 +60,26 @@ __global__ __launch_bounds__(3 * T2) void k_sweep_rows(SweepArgs<T, TM> A) {
     const int line = tid / F::TPL, t = tid & (F::TPL - 1);
     if (line < 6) {
       const int NB = A.NBr;
-      const int64_t FS = (int64_t)N0 * NB, o = (int64_t)((x0 - 1 + (line >> 1)) & (N0 - 1)) * NB;
+      const int64_t FS = Spec2<CT>::field(N0, NB);
+      const int xl = (x0 - 1 + (line >> 1)) & (N0 - 1);
       // element j of the line, j <= N_y/4
       auto elem = [&](int j) -> cpx<CT> {
+        const int64_t o = Spec2<CT>::at(xl, j, N0);
         if (line & 1) {
-          const cpx<CT> a2 = A.spec_in[2 * FS + o + j];
+          const cpx<CT> a2 = A.spec_in[2 * FS + o];
           return {a2.x, j == 0 ? (CT)0 : a2.y};
         }
-        const cpx<CT> a0 = A.spec_in[o + j], a1 = A.spec_in[FS + o + j];
+        const cpx<CT> a0 = A.spec_in[o], a1 = A.spec_in[FS + o];
         return j == 0 ? cpx<CT>{a0.x, a1.x} : cpx<CT>{a0.x - a1.y, a0.y + a1.x};
       };
       // its conjugate-symmetric partner N_y - j
       auto conj_elem = [&](int j) -> cpx<CT> {
+        const int64_t o = Spec2<CT>::at(xl, j, N0);
         if (line & 1) {
-          const cpx<CT> a2 = A.spec_in[2 * FS + o + j];
+          const cpx<CT> a2 = A.spec_in[2 * FS + o];
           return {a2.x, -a2.y};
         }
-        const cpx<CT> a0 = A.spec_in[o + j], a1 = A.spec_in[FS + o + j];
+        const cpx<CT> a0 = A.spec_in[o], a1 = A.spec_in[FS + o];
         return {a0.x + a1.y, a1.x - a0.y};
       };
       cpx<CT> v[4] = {elem(t), {0, 0}, {0, 0}, conj_elem(F::TPL - t)};
