@@ -43,19 +43,15 @@ template <class T, class CT, class TM>
 struct FsArgs {
   CorrGuard g;
   int do_accept;  // the rows pass decides acceptance (Algorithm 1 mode)
-  int Nx, Ny, lgx, lgy;
+  int Nx, Ny;
   int NH;  // N_y/2 + 1 retained j_y
-  int rows_per_block, cols_per_block;
   const TM* r;             // Q x Nx x Ny residual of the last sweep
-  cpx<CT>* spec;           // Q x Nx x NH
+  cpx<CT>* spec;           // Q half spectra (Spec2)
   const cpx<CT>* twx;      // Nx
   const cpx<CT>* twy;      // Ny
   double a, wp, wm, inv_ns;
   FBufs<T> fb;             // population buffers (output through the roles) ...
   T* out;                  // ... or this buffer when g.ctl is null
-  // plain solve: out = F^{-1}[(I - Z J)^{-1} F[r]] itself (the column pass
-  // keeps df^, the inverse rows overwrite out), e.g. as a preconditioner
-  int plain;
 };
 
 // Eq. (full-symbol) at one wavevector, FP64: y holds r^ on entry and
@@ -247,237 +243,213 @@ __device__ inline void fs_solve(const double* kpi, double (*y)[2], double a, dou
   }
 }
 
+// Row passes: the (Q + 1)/2 packed lines of one row per block (of more rows
+// where one row's lines would not fill the wavefronts).
+template <class CT, int LG>
+struct FsRows {
+  using F = LineFft<CT, LG, line_le(LG)>;
+  static_assert(F::WAVE, "lines of at most 512");
+  static constexpr int NL = 5, R = F::TPL >= 32 ? 1 : 32 / F::TPL;
+  static constexpr int LINES = NL * R, NT = (LINES * F::TPL + 63) / 64 * 64;
+};
+
 // Pass 1: forward transform along y of the Q residual rows of each x
 // (fields 2p and 2p+1 packed in one complex line; the last odd field alone),
 // half spectrum j_y = 0 .. N_y/2 kept.
-template <class L, class T, class CT, class TM>
-__global__ __launch_bounds__(256) void k_fs_rows_fwd(FsArgs<T, CT, TM> A, AcceptArgs<L, T> Ac, FinishArgs Fin) {
-  constexpr int Q = L::Q, NL = (Q + 1) / 2;
+template <class L, class T, class CT, class TM, int LG>
+__global__ __launch_bounds__((FsRows<CT, LG>::NT)) void k_fs_rows_fwd(FsArgs<T, CT, TM> A, AcceptArgs<L, T> Ac,
+                                                                     FinishArgs Fin) {
+  using S = FsRows<CT, LG>;
+  using F = typename S::F;
+  constexpr int Q = L::Q, N = F::N, E = F::E, TPL = F::TPL;
+  static_assert((Q + 1) / 2 == S::NL, "packed lines of a row");
+  __shared__ cpx<CT> lds[S::LINES * N];
+  const int line = threadIdx.x / TPL, t = threadIdx.x & (TPL - 1);
+  const int p = line % S::NL, x = blockIdx.x * S::R + line / S::NL;
+  cpx<CT> w[F::NTW], v[E];
+  F::load_tw(A.twy, t, w);
   if (A.do_accept) {
-    __shared__ double red[256];
+    __shared__ double red[S::NT / 64];
     const int dec = finish_block(Fin, red);
     if (dec != DEC_RUNNING) {
-      if (dec == DEC_ACCEPTED) {
-        const int64_t s0 = (int64_t)blockIdx.x * A.rows_per_block * A.Ny;
-        accept_sites<L, T>(Ac, s0 + threadIdx.x, s0 + (int64_t)A.rows_per_block * A.Ny, blockDim.x);
-      }
+      if (dec == DEC_ACCEPTED)
+        accept_sites<L, T>(Ac, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, Ac.NS,
+                           (int64_t)gridDim.x * blockDim.x);
       return;
     }
   } else if (A.g.skip()) {
     return;
   }
-  extern __shared__ unsigned char smem_raw[];
-  cpx<CT>* buf = reinterpret_cast<cpx<CT>*>(smem_raw);
-  const int Ny = A.Ny, R = A.rows_per_block;
-  cpx<CT>* tmp = buf + NL * R * Ny;
-  const int x0 = blockIdx.x * R;
-  const int64_t NS = (int64_t)A.Nx * Ny;
-  for (int i = threadIdx.x; i < R * Ny; i += blockDim.x) {
-    const int rr = i / Ny, y = i - rr * Ny;
-    const int64_t s = (int64_t)(x0 + rr) * Ny + y;
+  if (line >= S::LINES || x >= A.Nx) return;
+  const int64_t NS = (int64_t)A.Nx * N, s0 = (int64_t)x * N;
+  const bool two = 2 * p + 1 < Q;
 #pragma unroll
-    for (int p = 0; p < NL; ++p) {
-      const CT re = (CT)A.r[(2 * p) * NS + s];
-      const CT im = (2 * p + 1 < Q) ? (CT)A.r[(2 * p + 1) * NS + s] : (CT)0;
-      buf[(NL * rr + p) * Ny + y] = {re, im};
-    }
+  for (int i = 0; i < E; ++i) {
+    const int64_t s = s0 + t + i * TPL;
+    v[i] = {(CT)A.r[(2 * p) * NS + s], two ? (CT)A.r[(2 * p + 1) * NS + s] : (CT)0};
   }
-  __syncthreads();
-  const cpx<CT>* out = lds_fft<CT>(buf, tmp, A.lgy, NL * R, -1, A.twy);
-  const int NH = A.NH;
-  const int64_t FS = (int64_t)A.Nx * NH;
-  for (int i = threadIdx.x; i < R * NH; i += blockDim.x) {
-    const int rr = i / NH, j = i - rr * NH;
-    const int64_t o = (int64_t)(x0 + rr) * NH + j;
+  cpx<CT>* ln = lds + line * N;
+  F::template run<-1>(v, t, ln, ln, w);
 #pragma unroll
-    for (int p = 0; p < NL; ++p) {
-      const cpx<CT> z = out[(NL * rr + p) * Ny + j];
-      if (2 * p + 1 < Q) {
-        const cpx<CT> zc = out[(NL * rr + p) * Ny + ((Ny - j) & (Ny - 1))];
-        // F_a = (Z(j) + conj Z(-j))/2, F_b = (Z(j) - conj Z(-j))/(2i)
-        A.spec[(2 * p) * FS + o] = {(CT)0.5 * (z.x + zc.x), (CT)0.5 * (z.y - zc.y)};
-        A.spec[(2 * p + 1) * FS + o] = {(CT)0.5 * (z.y + zc.y), (CT)0.5 * (zc.x - z.x)};
-      } else {
-        A.spec[(2 * p) * FS + o] = z;
-      }
+  for (int i = 0; i < E; ++i) ln[t + i * TPL] = v[i];
+  wave_fence();
+  const int64_t FS = Spec2<CT>::field(A.Nx, A.NH);
+  auto store = [&](int j, cpx<CT> z) {
+    const int64_t o = 2 * p * FS + Spec2<CT>::at(x, j, A.Nx);
+    if (!two) {
+      A.spec[o] = z;
+      return;
     }
+    // F_a = (Z(j) + conj Z(-j))/2, F_b = (Z(j) - conj Z(-j))/(2i)
+    const cpx<CT> zc = ln[(N - j) & (N - 1)];
+    A.spec[o] = {(CT)0.5 * (z.x + zc.x), (CT)0.5 * (z.y - zc.y)};
+    A.spec[FS + o] = {(CT)0.5 * (z.y + zc.y), (CT)0.5 * (zc.x - z.x)};
+  };
+#pragma unroll
+  for (int i = 0; i < E / 2; ++i) store(t + i * TPL, v[i]);
+  if (t == 0) store(N / 2, v[E / 2]);
+}
+
+// df^ - r^ of one wavevector with the 1/N_sites of the inverse; z[q * stride]
+// holds r^ of field q on entry.
+template <class L, class CT, class TA>
+__device__ __forceinline__ void fs_wavevector(const TA& A, int jx, int jy, cpx<CT>* z, int64_t stride) {
+  constexpr int Q = L::Q;
+  const double kpi[2] = {2.0 * signed_index(jx, A.Nx) / A.Nx, 2.0 * jy / A.Ny};
+  double v[Q][2];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    v[q][0] = (double)z[q * stride].x;
+    v[q][1] = (double)z[q * stride].y;
+  }
+  fs_solve<L>(kpi, v, A.a, A.wp, A.wm);
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const cpx<CT> r = z[q * stride];
+    z[q * stride] = {(CT)((v[q][0] - (double)r.x) * A.inv_ns), (CT)((v[q][1] - (double)r.y) * A.inv_ns)};
   }
 }
 
-// Pass 2: for a group of j_y columns, forward transform along x, the solve of
-// Eq. (full-symbol) at every wavevector of the group, inverse transform
-// along x, in place in the half spectrum.
-template <class L, class T, class CT, class TM>
-__global__ __launch_bounds__(256) void k_fs_cols_solve(FsArgs<T, CT, TM> A) {
-  constexpr int Q = L::Q;
+// Pass 2: one retained j_y column per block: forward transform along x of its Q
+// lines, the solve of Eq. (full-symbol) at every wavevector, inverse
+// transform along x, in place in the half spectrum.  320 threads: the solve's
+// registers allow two wavefronts per SIMD.
+template <class L, class T, class CT, class TM, int LG>
+__global__ __launch_bounds__(320) void k_fs_cols_solve(FsArgs<T, CT, TM> A) {
+  using F = LineFft<CT, LG, line_le(LG)>;
+  constexpr int Q = L::Q, N = F::N, E = F::E, TPL = F::TPL, LPB = 320 / TPL;
+  __shared__ cpx<CT> lds[Q * N];
   if (A.g.skip()) return;
-  extern __shared__ unsigned char smem_raw[];
-  cpx<CT>* buf = reinterpret_cast<cpx<CT>*>(smem_raw);
-  const int Nx = A.Nx, JB = A.cols_per_block, NH = A.NH;
-  cpx<CT>* tmp = buf + Q * JB * Nx;
-  const int cbk = xcd_item(blockIdx.x, gridDim.x);
-  if (cbk * JB >= NH) return;  // grid padding
-  const int j0 = cbk * JB;
-  const int64_t FS = (int64_t)Nx * NH;
-  // transform t = q*JB + c holds column j0 + c of field q
-  for (int i = threadIdx.x; i < Q * JB * Nx; i += blockDim.x) {
-    const int c = i % JB;
-    const int rest = i / JB;
-    const int x = rest % Nx, q = rest / Nx;
-    const int j = j0 + c;
-    buf[(q * JB + c) * Nx + x] = (j < NH) ? A.spec[q * FS + (int64_t)x * NH + j] : cpx<CT>{0, 0};
+  const int jy = xcd_item(blockIdx.x, gridDim.x);
+  if (jy >= A.NH) return;  // grid padding
+  const int t = threadIdx.x & (TPL - 1);
+  const int64_t FS = Spec2<CT>::field(N, A.NH);
+  cpx<CT> w[F::NTW];
+  F::load_tw(A.twx, t, w);
+  for (int q = threadIdx.x / TPL; q < Q; q += LPB) {
+    cpx<CT> v[E];
+#pragma unroll
+    for (int i = 0; i < E; ++i) v[i] = A.spec[q * FS + Spec2<CT>::at(t + i * TPL, jy, N)];
+    cpx<CT>* ln = lds + q * N;
+    F::template run<-1>(v, t, ln, ln, w);
+#pragma unroll
+    for (int i = 0; i < E; ++i) ln[t + i * TPL] = v[i];
   }
   __syncthreads();
-  cpx<CT>* F = lds_fft<CT>(buf, tmp, A.lgx, Q * JB, -1, A.twx);
-  cpx<CT>* G = (F == buf) ? tmp : buf;
-  for (int i = threadIdx.x; i < JB * Nx; i += blockDim.x) {
-    const int c = i / Nx, jx = i - c * Nx;
-    const int jy = j0 + c;
-    if (jy < NH) {
-      const double kpi[2] = {2.0 * signed_index(jx, Nx) / Nx, 2.0 * jy / A.Ny};
-      double v[Q][2];
-#pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        const cpx<CT> z = F[(q * JB + c) * Nx + jx];
-        v[q][0] = (double)z.x;
-        v[q][1] = (double)z.y;
-      }
-      fs_solve<L>(kpi, v, A.a, A.wp, A.wm);
-      // df^ - r^ (r^ read again from LDS), or df^ for a plain solve, with
-      // the 1/N_sites of the inverse
-#pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        const cpx<CT> z = F[(q * JB + c) * Nx + jx];
-        const double sr = A.plain ? 0.0 : (double)z.x, si = A.plain ? 0.0 : (double)z.y;
-        G[(q * JB + c) * Nx + jx] = {(CT)((v[q][0] - sr) * A.inv_ns), (CT)((v[q][1] - si) * A.inv_ns)};
-      }
-    } else {
-#pragma unroll
-      for (int q = 0; q < Q; ++q) G[(q * JB + c) * Nx + jx] = {(CT)0, (CT)0};
-    }
-  }
+  for (int jx = threadIdx.x; jx < N; jx += 320) fs_wavevector<L, CT>(A, jx, jy, lds + jx, N);
   __syncthreads();
-  cpx<CT>* H = lds_fft<CT>(G, F, A.lgx, Q * JB, +1, A.twx);
-  for (int i = threadIdx.x; i < Q * JB * Nx; i += blockDim.x) {
-    const int c = i % JB;
-    const int rest = i / JB;
-    const int x = rest % Nx, q = rest / Nx;
-    const int j = j0 + c;
-    if (j < NH) A.spec[q * FS + (int64_t)x * NH + j] = H[(q * JB + c) * Nx + x];
+  F::load_tw(A.twx, t, w);  // (not held over the solve)
+  for (int q = threadIdx.x / TPL; q < Q; q += LPB) {
+    cpx<CT> v[E];
+    cpx<CT>* ln = lds + q * N;
+#pragma unroll
+    for (int i = 0; i < E; ++i) v[i] = ln[t + i * TPL];
+    wave_fence();
+    F::template run<+1>(v, t, ln, ln, w);
+#pragma unroll
+    for (int i = 0; i < E; ++i) A.spec[q * FS + Spec2<CT>::at(t + i * TPL, jy, N)] = v[i];
   }
 }
 
-// Split form of pass 2 (more parallel at N <= 512, where one block per
-// retained column leaves most compute units idle): the x transforms of LB
-// (field, j_y) lines per block, then the solve with one wavevector per thread,
-// then the inverse x transforms.  Same arithmetic as the fused pass.
-template <class L, class T, class CT, class TM>
-__global__ __launch_bounds__(256) void k_fs_cols_fft(FsArgs<T, CT, TM> A, int sign) {
-  constexpr int Q = L::Q;
+// Split form of pass 2 (more parallel at N_x = 512, where one block per
+// retained column holds nine long lines): the x transforms, then the solve
+// with one wavevector per thread, then the inverse x transforms.  Same
+// arithmetic as the fused pass.
+template <class L, class T, class CT, class TM, int LG, int SIGN>
+__global__ __launch_bounds__(256) void k_fs_cols_fft(FsArgs<T, CT, TM> A) {
+  using F = LineFft<CT, LG, line_le(LG)>;
+  constexpr int Q = L::Q, N = F::N, E = F::E, TPL = F::TPL, LPB = 256 / TPL;
+  __shared__ cpx<CT> lds[LPB * N];
   if (A.g.skip()) return;
-  extern __shared__ unsigned char smem_raw[];
-  cpx<CT>* buf = reinterpret_cast<cpx<CT>*>(smem_raw);
-  const int Nx = A.Nx, NH = A.NH, LB = A.cols_per_block;
-  cpx<CT>* tmp = buf + LB * Nx;
-  const int t0 = xcd_item(blockIdx.x, gridDim.x) * LB, nlines = Q * NH;
-  if (t0 >= nlines) return;  // grid padding
-  const int64_t FS = (int64_t)Nx * NH;
-  // line t = q * NH + j: element x at spec[q][x][j]
-  for (int i = threadIdx.x; i < LB * Nx; i += blockDim.x) {
-    const int c = i % LB, x = i / LB;
-    const int t = t0 + c;
-    cpx<CT> v = {0, 0};
-    if (t < nlines) v = A.spec[(t / NH) * FS + (int64_t)x * NH + (t % NH)];
-    buf[c * Nx + x] = v;
-  }
-  __syncthreads();
-  const cpx<CT>* out = lds_fft<CT>(buf, tmp, A.lgx, LB, sign, A.twx);
-  for (int i = threadIdx.x; i < LB * Nx; i += blockDim.x) {
-    const int c = i % LB, x = i / LB;
-    const int t = t0 + c;
-    if (t < nlines) A.spec[(t / NH) * FS + (int64_t)x * NH + (t % NH)] = out[c * Nx + x];
-  }
+  const int b = threadIdx.x / TPL, t = threadIdx.x & (TPL - 1);
+  const int item = xcd_item(blockIdx.x, gridDim.x) * LPB + b;  // line of field item / NH
+  if (item >= Q * A.NH) return;
+  const int q = item / A.NH, jy = item - q * A.NH;
+  cpx<CT>* s = A.spec + q * Spec2<CT>::field(N, A.NH);
+  cpx<CT> w[F::NTW], v[E];
+  F::load_tw(A.twx, t, w);
+#pragma unroll
+  for (int i = 0; i < E; ++i) v[i] = s[Spec2<CT>::at(t + i * TPL, jy, N)];
+  F::template run<SIGN>(v, t, lds + b * N, lds + b * N, w);
+#pragma unroll
+  for (int i = 0; i < E; ++i) s[Spec2<CT>::at(t + i * TPL, jy, N)] = v[i];
 }
 
 template <class L, class T, class CT, class TM>
 __global__ __launch_bounds__(64) void k_fs_solve_k(FsArgs<T, CT, TM> A) {
-  constexpr int Q = L::Q;
   if (A.g.skip()) return;
-  const int Nx = A.Nx, NH = A.NH;
-  const int64_t FS = (int64_t)Nx * NH;
-  const int64_t nk = FS;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nk; i += (int64_t)gridDim.x * blockDim.x) {
-    const int jx = (int)(i / NH), jy = (int)(i - (int64_t)jx * NH);
-    const double kpi[2] = {2.0 * signed_index(jx, Nx) / Nx, 2.0 * jy / A.Ny};
-    double v[Q][2];
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      const cpx<CT> z = A.spec[q * FS + i];
-      v[q][0] = (double)z.x;
-      v[q][1] = (double)z.y;
-    }
-    fs_solve<L>(kpi, v, A.a, A.wp, A.wm);
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      const cpx<CT> z = A.spec[q * FS + i];
-      const double sr = A.plain ? 0.0 : (double)z.x, si = A.plain ? 0.0 : (double)z.y;
-      A.spec[q * FS + i] = {(CT)((v[q][0] - sr) * A.inv_ns), (CT)((v[q][1] - si) * A.inv_ns)};
-    }
+  constexpr int G = Spec2<CT>::G;
+  const int64_t FS = Spec2<CT>::field(A.Nx, A.NH);
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < FS; i += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t xg = i / G;
+    const int jx = (int)(xg % A.Nx), jy = (int)(xg / A.Nx) * G + (int)(i & (G - 1));
+    if (jy < A.NH) fs_wavevector<L, CT>(A, jx, jy, A.spec + i, FS);
   }
 }
 
 // Pass 3: inverse transform along y from the half spectrum to real rows
 // (Z(N_y - j) = conj Z(j); the j = 0 and j = N_y/2 terms of a real row are
 // real) and f <- f_T + (df - r) in place in the sweep's output buffer.
-template <class L, class T, class CT, class TM>
-__global__ __launch_bounds__(256) void k_fs_rows_inv(FsArgs<T, CT, TM> A) {
-  constexpr int Q = L::Q, NL = (Q + 1) / 2;
+template <class L, class T, class CT, class TM, int LG>
+__global__ __launch_bounds__((FsRows<CT, LG>::NT)) void k_fs_rows_inv(FsArgs<T, CT, TM> A) {
+  using S = FsRows<CT, LG>;
+  using F = typename S::F;
+  constexpr int Q = L::Q, N = F::N, E = F::E, TPL = F::TPL;
+  __shared__ cpx<CT> lds[S::LINES * N];
+  const int line = threadIdx.x / TPL, t = threadIdx.x & (TPL - 1);
+  const int p = line % S::NL, x = blockIdx.x * S::R + line / S::NL;
+  cpx<CT> w[F::NTW], v[E];
+  F::load_tw(A.twy, t, w);
   if (A.g.skip()) return;
   T* __restrict__ dst = A.out;
   if (A.g.ctl) dst = A.fb.p[A.g.ctl->roles[A.g.n & 1].slot_w[A.g.ell & 1]];
-  extern __shared__ unsigned char smem_raw[];
-  cpx<CT>* buf = reinterpret_cast<cpx<CT>*>(smem_raw);
-  const int Ny = A.Ny, R = A.rows_per_block, NH = A.NH;
-  cpx<CT>* tmp = buf + NL * R * Ny;
-  const int x0 = blockIdx.x * R;
-  const int64_t FS = (int64_t)A.Nx * NH;
-  for (int i = threadIdx.x; i < R * Ny; i += blockDim.x) {
-    const int rr = i / Ny, j = i - rr * Ny;
-    const int64_t o = (int64_t)(x0 + rr) * NH;
-    const bool lower = j < NH;
-    const int jj = lower ? j : Ny - j;
-    const bool real_term = (j == 0) || (2 * j == Ny);
+  if (line >= S::LINES || x >= A.Nx) return;
+  const int64_t FS = Spec2<CT>::field(A.Nx, A.NH);
+  const bool two = 2 * p + 1 < Q;
 #pragma unroll
-    for (int p = 0; p < NL; ++p) {
-      cpx<CT> a0 = A.spec[(2 * p) * FS + o + jj];
-      cpx<CT> a1 = (2 * p + 1 < Q) ? A.spec[(2 * p + 1) * FS + o + jj] : cpx<CT>{0, 0};
-      if (real_term) {
-        a0.y = 0;
-        a1.y = 0;
-      } else if (!lower) {
-        a0.y = -a0.y;
-        a1.y = -a1.y;
-      }
-      // pack a0 + i a1
-      buf[(NL * rr + p) * Ny + j] = {a0.x - a1.y, a0.y + a1.x};
+  for (int i = 0; i < E; ++i) {
+    const int j = t + i * TPL;
+    const bool lower = 2 * j <= N, real_term = (j == 0) || (2 * j == N);
+    const int64_t o = 2 * p * FS + Spec2<CT>::at(x, lower ? j : N - j, A.Nx);
+    cpx<CT> a0 = A.spec[o];
+    cpx<CT> a1 = two ? A.spec[FS + o] : cpx<CT>{0, 0};
+    if (real_term) {
+      a0.y = 0;
+      a1.y = 0;
+    } else if (!lower) {
+      a0.y = -a0.y;
+      a1.y = -a1.y;
     }
+    v[i] = {a0.x - a1.y, a0.y + a1.x};  // pack a0 + i a1
   }
-  __syncthreads();
-  const cpx<CT>* out = lds_fft<CT>(buf, tmp, A.lgy, NL * R, +1, A.twy);
-  const int64_t NS = (int64_t)A.Nx * Ny;
-  for (int i = threadIdx.x; i < R * Ny; i += blockDim.x) {
-    const int rr = i / Ny, y = i - rr * Ny;
-    const int64_t s = (int64_t)(x0 + rr) * Ny + y;
+  cpx<CT>* ln = lds + line * N;
+  F::template run<+1>(v, t, ln, ln, w);
+  const int64_t NS = (int64_t)A.Nx * N, s0 = (int64_t)x * N;
 #pragma unroll
-    for (int p = 0; p < NL; ++p) {
-      const cpx<CT> z = out[(NL * rr + p) * Ny + y];
-      const int64_t ia = (2 * p) * NS + s;
-      dst[ia] = A.plain ? (T)z.x : (T)((CT)dst[ia] + z.x);
-      if (2 * p + 1 < Q) {
-        const int64_t ib = (2 * p + 1) * NS + s;
-        dst[ib] = A.plain ? (T)z.y : (T)((CT)dst[ib] + z.y);
-      }
-    }
+  for (int i = 0; i < E; ++i) {
+    const int64_t ia = 2 * p * NS + s0 + t + i * TPL;
+    dst[ia] = (T)((CT)dst[ia] + v[i].x);
+    if (two) dst[NS + ia] = (T)((CT)dst[NS + ia] + v[i].y);
   }
 }
 

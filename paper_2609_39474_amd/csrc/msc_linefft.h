@@ -11,7 +11,7 @@
 // positions fold into constants, the first stage has no twiddles, and the
 // twiddles of the others can be loaded before the data arrives.  One line of
 // 256 alone takes 0.44 us in FP64 and 0.35 us in FP32, against 2.05 and 1.92
-// us with a run-time length and every stage through LDS (lds_fft).
+// us with a run-time length and every stage through LDS.
 //
 // Lines that fit one wavefront (TPL <= 64, TPL threads aligned inside a
 // wavefront) need no barrier: LDS operations of a wavefront complete in order.
@@ -23,7 +23,7 @@
 #include <type_traits>
 #include <vector>
 
-#include "msc_ldsfft.h"
+#include "msc_cpx.h"
 
 namespace msc {
 

@@ -531,210 +531,140 @@ class Solver : public SolverBase {
   void wall_allocate() {
     const int64_t n = (int64_t)Q * G.NS;
     wk_m = P.wall_restart > 0 ? P.wall_restart : 50;
+    std::fill(wk_pred, wk_pred + kWallPred, 8);
     wk_V = keep((double*)dalloc(sizeof(double) * (wk_m + 1) * n));
     wk_R = keep((double*)dalloc(sizeof(double) * n));
-    wk_Y = keep((double*)dalloc(sizeof(double) * n));
-    wk_Z = keep((double*)dalloc(sizeof(double) * n));
     wk_D = keep((double*)dalloc(sizeof(double) * n));
-    wk_W = keep((double*)dalloc(sizeof(double) * n));
     wk_vc = keep((double*)dalloc(sizeof(double) * n));
-    wk_mu = keep((double*)dalloc(sizeof(double) * 3 * G.NS));
+    wk_spec = keep((cpx<double>*)dalloc(sizeof(cpx<double>) * 3 * Spec2<double>::field(G.N0, G.N2 / 2 + 1)));
     wk_mref = keep((double*)dalloc(sizeof(double) * 3 * G.NS));
     wk_sref = keep((double*)dalloc(sizeof(double) * 3 * G.NS));
-    wk_part = keep((double*)dalloc(sizeof(double) * kDotBlocks * (wk_m + 2)));
+    // the state word, then the dot-product partials (one entry of N_x per vector)
+    wk_part = keep((double*)dalloc(sizeof(double) * (1 + (size_t)G.N0 * (wk_m + 2))));
     wk_coef = keep((double*)dalloc(sizeof(double) * (wk_m + 2)));
-    const size_t small = (size_t)wk_m * wk_m + 2 * wk_m + (wk_m + 1) + (wk_m + 2) + 1 + wk_m;
-    wk_small = keep((double*)dalloc(sizeof(double) * small));
-    MSC_HIPCK(hipHostMalloc((void**)&wk_part_h, sizeof(double) * kDotBlocks * (wk_m + 2), hipHostMallocDefault));
-    MSC_HIPCK(hipHostMalloc((void**)&wk_coef_h, sizeof(double) * (wk_m + 2), hipHostMallocDefault));
-    MSC_HIPCK(hipHostMalloc((void**)&wk_small_h, sizeof(double) * small, hipHostMallocDefault));
+    // Hd (m x m), cs, sn (m each), g (m + 1), hcol (m + 2)
+    wk_small = keep((double*)dalloc(sizeof(double) * ((size_t)wk_m * wk_m + 4 * wk_m + 3)));
+    MSC_HIPCK(hipHostMalloc((void**)&wk_part_h, sizeof(double) * (1 + G.N0), hipHostMallocDefault));
   }
 
-  int vec_grid() const {
-    const int64_t n = (int64_t)Q * G.NS;
-    return (int)std::min<int64_t>((n + 255) / 256, 2048);
-  }
-
-  // <V_i, w> for i < nv, summed on the host in block order
-  void wall_dots(const double* V, int nv, const double* w, double* out) {
-    const int64_t n = (int64_t)Q * G.NS;
-    hipLaunchKernelGGL(k_dots<double>, dim3(kDotBlocks), dim3(256), 0, st, V, n, nv, w, n, wk_part, 0);
-    MSC_HIPCK(hipGetLastError());
-    MSC_HIPCK(hipMemcpyAsync(wk_part_h, wk_part, sizeof(double) * kDotBlocks * nv, hipMemcpyDeviceToHost, st));
-    sync();
-    for (int i = 0; i < nv; ++i) {
-      double acc = 0.0;
-      for (int b = 0; b < kDotBlocks; ++b) acc += wk_part_h[(int64_t)i * kDotBlocks + b];
-      out[i] = acc;
+  WallArgs wall_args() const {
+    WallArgs A{};
+    A.Nx = G.N0;
+    A.Ny = G.N2;
+    A.NS = G.NS;
+    A.a = wk_aA;
+    A.g = (1.0 - 0.5 * wk_aA) / (1.0 + 0.5 * wk_aA);
+    A.mref = wk_rest ? nullptr : wk_mref;
+    A.sref = wk_rest ? nullptr : wk_sref;
+    A.vc = wk_vc;
+    A.spec = wk_spec;
+    if constexpr (std::is_same<CT, double>::value) {
+      A.twx = tw[0];
+      A.twy = tw[2];
     }
+    A.state = reinterpret_cast<WallState*>(wk_part);
+    A.part = wk_part + 1;
+    A.m = wk_m;
+    A.Hd = wk_small;
+    A.cs = A.Hd + (size_t)wk_m * wk_m;
+    A.sn = A.cs + wk_m;
+    A.gv = A.sn + wk_m;
+    return A;
   }
 
-  void upload_coef(const double* c, int nv) {
-    for (int i = 0; i < nv; ++i) wk_coef_h[i] = c[i];
-    MSC_HIPCK(hipMemcpyAsync(wk_coef, wk_coef_h, sizeof(double) * nv, hipMemcpyHostToDevice, st));
-  }
-
-  void lincomb(double* out, const double* x, double alpha, const double* y, double beta) {
-    hipLaunchKernelGGL(k_lincomb<0>, dim3(vec_grid()), dim3(256), 0, st, out, x, alpha, y, beta,
-                       (int64_t)Q * G.NS);
-    MSC_HIPCK(hipGetLastError());
-  }
-
-  // w = (I - L) z with the current operator (Eq. wall-global-jacobian)
-  void wall_apply(const double* z, double* w) {
-    const int g = ew_grid();
-    hipLaunchKernelGGL(k_wall_mu<0>, dim3(g), dim3(256), 0, st, z, wk_mu, G.NS, 1.0 / (1.0 + 0.5 * wk_aA));
-    MSC_HIPCK(hipGetLastError());
-    hipLaunchKernelGGL(k_wall_apply<0>, dim3(g), dim3(256), 0, st, z, (const double*)wk_mu,
-                       wk_rest ? (const double*)nullptr : (const double*)wk_mref,
-                       wk_rest ? (const double*)nullptr : (const double*)wk_sref, wk_aA, G.N0, G.N2, w);
-    MSC_HIPCK(hipGetLastError());
-  }
-
-  // out = M^{-1} in: the periodic full-symbol inverse at rest (omega = 1, a_A)
-  void wall_precondition(const double* in, double* out) {
-    if constexpr (std::is_same<T, double>::value && std::is_same<TM, double>::value)
-      enqueue_fullsym(nullptr, 0, 0, wk_aA, nullptr, nullptr, true, true, (T*)out, (const TM*)in, 1);
-  }
-
-  // Restarted GMRES(m), right-preconditioned, classical Gram-Schmidt (with
-  // one re-orthogonalisation when krylov_tol < 1e-8; a single projection
-  // otherwise, which halves the passes over the basis): delta ~ (I - L)^{-1}
-  // rhs to the relative residual krylov_tol.  The basis is stored in FP32 when
-  // krylov_tol >= 1e-5 (half the bytes of the passes over it; its rounding,
-  // ~1e-7 relative, stays far below such tolerances), else in FP64; the new
-  // vector, the coefficients and every sum are FP64.  The orthogonalisation
-  // coefficients, the Hessenberg columns and the Givens rotations stay on the
-  // device (k_gs_first, k_gs_second); the host reads the residual estimate
-  // every kCheck iterations and the small triangular system once per cycle.
-  // Returns the iteration count; rel receives the final true relative
-  // residual.
-  static constexpr int kCheck = 4;
-  int wall_gmres(const double* rhs, double* delta, double& rel) {
+  // Restarted GMRES(m), right-preconditioned (msc_walls.h), classical
+  // Gram-Schmidt (with one re-orthogonalisation when krylov_tol < 1e-8; a
+  // single projection otherwise, which halves the passes over the basis):
+  // delta ~ (I - L)^{-1} rhs to the relative residual krylov_tol, beta0 =
+  // |rhs|; then f_T <- f_T + (delta - rhs) = f + delta, f the sweep's input.
+  // The basis is stored in FP32 when krylov_tol >= 1e-5 (half the bytes of the
+  // passes over it; its rounding, ~1e-7 relative, stays far below such
+  // tolerances), else in FP64; the new vector, the coefficients and every sum
+  // are FP64.  The host enqueues as many iterations as the last solve took and
+  // the solution's assembly, which the device skips unless the estimate has
+  // converged, and reads the state once.  ell: the inner iteration.
+  void wall_solve(const double* rhs, double beta0, double* fT, int ell) {
     const double tol = P.krylov_tol > 0.0 ? P.krylov_tol : 1e-12;
-    return tol >= 1e-5 ? wall_gmres_t<float>(rhs, delta, rel) : wall_gmres_t<double>(rhs, delta, rel);
+    if (!(beta0 > 0.0) || !std::isfinite(beta0)) return;  // delta = 0
+    int& pred = wk_pred[std::min(ell, kWallPred) - 1];
+    with_lg<2, 8>(ilog2(G.N2), [&](auto lgy) {
+      with_lg<2, 8>(ilog2(G.N0), [&](auto lgx) {
+        if (tol >= 1e-5)
+          wall_solve_t<lgx.value, lgy.value, float>(rhs, beta0, fT, tol, pred);
+        else
+          wall_solve_t<lgx.value, lgy.value, double>(rhs, beta0, fT, tol, pred);
+      });
+    });
   }
 
-  template <class VT>
-  int wall_gmres_t(const double* rhs, double* delta, double& rel) {
+  template <int LGX, int LGY, class VT>
+  void wall_solve_t(const double* rhs, double beta0, double* fT, double tol, int& pred) {
     const int64_t n = (int64_t)Q * G.NS;
-    const int m = wk_m;
-    const double tol = P.krylov_tol > 0.0 ? P.krylov_tol : 1e-12;
+    const int m = wk_m, rows = G.N0;
     const int max_restarts = 40;
-    VT* V = reinterpret_cast<VT*>(wk_V);
-    double b2 = 0.0;
-    wall_dots(rhs, 1, rhs, &b2);
-    const double beta0 = std::sqrt(b2);
-    lincomb(delta, rhs, 0.0, nullptr, 0.0);
-    rel = 0.0;
-    if (!(beta0 > 0.0)) return 0;
-    if (!std::isfinite(beta0)) {
-      rel = beta0;
-      return 0;
-    }
-    // device scratch of the cycle: Hd (m x m, row stride m), cs, sn, g,
-    // hcol, scale, resid
-    double* Hd = wk_small;
-    double* cs = Hd + (size_t)m * m;
-    double* sn = cs + m;
-    double* g = sn + m;
-    double* hcol = g + (m + 1);
-    double* scale = hcol + (m + 2);
-    double* resid = scale + 1;
-    lincomb(wk_R, rhs, 1.0, nullptr, 0.0);
-    double beta = beta0;
-    int iters = 0;
-    std::vector<double> y(m);
     const bool reorth = tol < 1e-8;
-    if (!reorth) MSC_HIPCK(hipMemsetAsync(hcol, 0, sizeof(double) * (m + 2), st));
+    VT* V = reinterpret_cast<VT*>(wk_V);
+    WallArgs A = wall_args();
+    A.stop = tol * beta0;
+    double* hcol = reorth ? A.gv + (m + 1) : nullptr;
+    const int vgrid = (int)std::min<int64_t>((n + 255) / 256, 2048);
+    auto cols = [&](int run_on) {
+      hipLaunchKernelGGL((k_wall_cols<LGX>), dim3(pad8(G.N2 / 2 + 1)), dim3(256), 0, st, A, run_on);
+    };
+    auto orth = [&](int j, const double* src, double scale0) {
+      hipLaunchKernelGGL((k_wall_orth<LGY, VT>), dim3(rows + 1), dim3(512), 0, st, A, V, j, (const double*)hcol, src,
+                         scale0);
+    };
+    double beta = beta0, rel = 0.0;
+    int iters = 0;
+    bool updated = false;
     for (int rs = 0; rs < max_restarts; ++rs) {
-      hipLaunchKernelGGL(k_scale_to<VT>, dim3(vec_grid()), dim3(256), 0, st, V, wk_vc, (const double*)wk_R,
-                         1.0 / beta, n);
-      MSC_HIPCK(hipGetLastError());
-      for (int i = 0; i <= m; ++i) wk_small_h[i] = (i == 0) ? beta : 0.0;
-      MSC_HIPCK(hipMemcpyAsync(g, wk_small_h, sizeof(double) * (m + 1), hipMemcpyHostToDevice, st));
-      int jend = 0;
+      orth(0, rs == 0 ? rhs : (const double*)wk_R, 1.0 / beta);
+      int j = 0;
       bool done = false;
-      for (int j = 0; j < m; ++j) {
-        VT* vj1 = V + (int64_t)(j + 1) * n;
-        // w = (I - L) M^{-1} v_j, from the FP64 copy of v_j
-        wall_precondition(wk_vc, wk_Z);
-        wall_apply(wk_Z, wk_W);
-        if (reorth) {
-          hipLaunchKernelGGL(k_dots<VT>, dim3(kDotBlocks), dim3(256), 0, st, (const VT*)V, n, j + 1,
-                             (const double*)wk_W, n, wk_part, 0);
-          hipLaunchKernelGGL(k_gs_first<0>, dim3(1), dim3(1024), 0, st, (const double*)wk_part, j + 1, wk_coef,
-                             hcol);
-          hipLaunchKernelGGL(k_axpy_multi<VT>, dim3(vec_grid()), dim3(256), 0, st, wk_W, (const VT*)V, n, j + 1,
-                             (const double*)wk_coef, n);
-        }
-        hipLaunchKernelGGL(k_dots<VT>, dim3(kDotBlocks), dim3(256), 0, st, (const VT*)V, n, j + 1,
-                           (const double*)wk_W, n, wk_part, 1);
-        hipLaunchKernelGGL(k_gs_second<0>, dim3(1), dim3(1024), 0, st, (const double*)wk_part, j, m,
-                           wk_coef, (const double*)hcol, Hd, cs, sn, g, scale, resid);
-        hipLaunchKernelGGL(k_axpy_scale<VT>, dim3(vec_grid()), dim3(256), 0, st, vj1, wk_vc, (const double*)wk_W,
-                           (const VT*)V, n, j + 1, (const double*)wk_coef, (const double*)scale, n);
-        MSC_HIPCK(hipGetLastError());
-        ++iters;
-        jend = j + 1;
-        if ((j + 1) % kCheck == 0 || j == m - 1) {
-          MSC_HIPCK(hipMemcpyAsync(wk_small_h, resid + j, sizeof(double), hipMemcpyDeviceToHost, st));
-          sync();
-          const double res = wk_small_h[0];
-          if (res <= tol * beta0 || !std::isfinite(res)) {
-            done = true;
-            break;
+      WallState ws{};
+      do {
+        const int upto = std::min(m, j == 0 ? pred : j + 2);
+        for (; j < upto; ++j) {
+          cols(0);
+          hipLaunchKernelGGL((k_wall_rows<LGY, VT>), dim3(rows), dim3(512), 0, st, A, (const VT*)V, j);
+          if (reorth) {
+            hipLaunchKernelGGL(k_gs_first<0>, dim3(1), dim3(1024), 0, st, (const double*)A.part, rows, j + 1, wk_coef,
+                               hcol);
+            hipLaunchKernelGGL(k_axpy_multi<VT>, dim3(vgrid), dim3(256), 0, st, wk_vc, (const VT*)V, n, j + 1,
+                               (const double*)wk_coef, n);
+            hipLaunchKernelGGL((k_wall_dots<LGY, VT>), dim3(rows), dim3(512), 0, st, A, (const VT*)V, j);
           }
+          orth(j + 1, nullptr, 0.0);
         }
-      }
-      // y = R^{-1} g (upper triangular, jend x jend), delta += M^{-1} V y;
-      // the columns after the first converged or broken-down one are unused
-      const size_t hsz = (size_t)m * m + 2 * m + (m + 1) + (m + 2) + 1 + m;
-      MSC_HIPCK(hipMemcpyAsync(wk_small_h, Hd, sizeof(double) * hsz, hipMemcpyDeviceToHost, st));
-      sync();
-      const double* Hh = wk_small_h;
-      const double* gh = wk_small_h + (size_t)m * m + 2 * m;
-      const double* rh = gh + (m + 1) + (m + 2) + 1;
-      for (int i = 0; i < jend; ++i) {
-        if (!(std::fabs(Hh[(size_t)i * m + i]) > 0.0)) {
-          jend = i;
-          break;
-        }
-        if (rh[i] <= tol * beta0) {
-          jend = i + 1;
-          break;
-        }
-      }
-      for (int i = jend - 1; i >= 0; --i) {
-        double acc = gh[i];
-        for (int k = i + 1; k < jend; ++k) acc -= Hh[(size_t)i * m + k] * y[k];
-        y[i] = acc / Hh[(size_t)i * m + i];
-      }
-      upload_coef(y.data(), jend);
-      hipLaunchKernelGGL(k_combine<VT>, dim3(vec_grid()), dim3(256), 0, st, wk_Y, (const VT*)V, n, jend,
-                         (const double*)wk_coef, n);
-      MSC_HIPCK(hipGetLastError());
-      wall_precondition(wk_Y, wk_Z);
-      lincomb(delta, delta, 1.0, wk_Z, 1.0);
-      // true residual
-      wall_apply(delta, wk_Y);
-      lincomb(wk_R, rhs, 1.0, wk_Y, -1.0);
+        const int force = (j == m) ? m : 0;
+        hipLaunchKernelGGL((k_wall_combine<LGY, VT>), dim3(rows), dim3(512), 0, st, A, (const VT*)V, force);
+        cols(force ? 2 : 1);
+        hipLaunchKernelGGL((k_wall_finish<LGY>), dim3(rows), dim3(512), 0, st, A, rhs, wk_D, wk_R, fT, rs == 0 ? 1 : 0,
+                           force);
+        MSC_HIPCK(hipGetLastError());
+        MSC_HIPCK(hipMemcpyAsync(wk_part_h, wk_part, sizeof(double) * (1 + rows), hipMemcpyDeviceToHost, st));
+        sync();
+        std::memcpy(&ws, wk_part_h, sizeof(ws));
+        done = ws.done != 0;
+      } while (!done && j < m);
+      const int took = done ? ws.jend : m;
+      iters += took;
+      if (rs == 0) pred = std::max(1, took);
       double r2 = 0.0;
-      wall_dots(wk_R, 1, wk_R, &r2);
+      for (int x = 0; x < rows; ++x) r2 += wk_part_h[1 + x];
       beta = std::sqrt(r2);
       rel = beta / beta0;
+      updated = done;
       if (done || rel <= tol || !(beta > 0.0)) break;
+    }
+    if (!updated) {
+      hipLaunchKernelGGL(k_wall_update<0>, dim3(vgrid), dim3(256), 0, st, fT, (const double*)wk_D, rhs, n);
+      MSC_HIPCK(hipGetLastError());
     }
     kr_solves += 1;
     kr_iters += iters;
     kr_worst = std::max(kr_worst, rel);
-    return iters;
-  }
-
-  // f_T <- f_T + (delta - r) = f + delta, f the sweep's input
-  void wall_update(double* fT, const double* delta, const double* r) {
-    lincomb(wk_Y, delta, 1.0, r, -1.0);
-    lincomb(fT, fT, 1.0, wk_Y, 1.0);
   }
 
   // Algorithm 2 driven from the host: each inner iteration is the sweep (with
@@ -811,9 +741,7 @@ class Solver : public SolverBase {
               n_grow = 0;
               Rref = R;
             }
-            double rel = 0.0;
-            wall_gmres(rfs, wk_D, rel);
-            wall_update(fT, wk_D, rfs);
+            wall_solve(rfs, R * std::sqrt((double)Q * (double)NS), fT, ell);
           }
         }
         copy_stats(out, stat_base, nsteps);
@@ -843,9 +771,7 @@ class Solver : public SolverBase {
         launch_sweep_timed(SW_DTS, S, 0);
         const double Rv = reduce_partials(S);
         if (R) *R = Rv;
-        double rel = 0.0;
-        wall_gmres(rfs, wk_D, rel);
-        wall_update(B, wk_D, rfs);
+        wall_solve(rfs, Rv * std::sqrt((double)Q * (double)G.NS), B, 1);
         if (fnext) download_pop(B, fnext);
         sync();
         if (dm_out) std::memset(dm_out, 0, sizeof(double) * (D + 1) * G.NS);
@@ -1033,24 +959,24 @@ class Solver : public SolverBase {
   cpx<CT>* spec_alt = nullptr;  // 2D: second band spectrum (inverse rows in the sweep)
   TM* rfs = nullptr;           // full symbol / wall corrector: residual of every field (Q x NS)
   // wall-bounded kinetic corrector (Algorithm 2): Krylov basis and work
-  // vectors (FP64, Q x NS each), the reference field of the current operator
-  // and the assembly coefficient a_A, dot-product partials and coefficients
+  // vectors (FP64, Q x NS each), the moment spectra, the reference field of the
+  // current operator and the assembly coefficient a_A, the state word with
+  // the dot-product partials, and the cycle's bookkeeping
   double* wk_V = nullptr;
   double* wk_R = nullptr;
-  double* wk_Y = nullptr;
-  double* wk_Z = nullptr;
   double* wk_D = nullptr;
-  double* wk_W = nullptr;   // the new Krylov vector before its orthogonalisation
-  double* wk_vc = nullptr;  // FP64 copy of the newest basis vector (preconditioner input)
-  double* wk_mu = nullptr;
+  double* wk_vc = nullptr;  // FP64 copy of the newest basis vector
+  cpx<double>* wk_spec = nullptr;
   double* wk_mref = nullptr;
   double* wk_sref = nullptr;
   double* wk_part = nullptr;
   double* wk_part_h = nullptr;
   double* wk_coef = nullptr;
-  double* wk_coef_h = nullptr;
-  double* wk_small = nullptr;    // GMRES cycle bookkeeping on the device
-  double* wk_small_h = nullptr;  // its pinned host mirror
+  double* wk_small = nullptr;
+  // iterations enqueued before the host looks, by inner iteration: what that
+  // inner iteration's solve took in the previous step
+  static constexpr int kWallPred = 16;
+  int wk_pred[kWallPred];
   int wk_m = 50;
   double wk_aA = 0.0;
   bool wk_rest = true;
@@ -1251,10 +1177,11 @@ class Solver : public SolverBase {
     if (wallkin() && wall_supported()) wall_allocate();
     if ((fullsym() || wallkin()) && fs_supported()) {
       rfs = keep((TM*)dalloc(sizeof(TM) * (int64_t)Q * NS));
-      spec_fs = keep((cpx<CT>*)dalloc(sizeof(cpx<CT>) * (int64_t)Q * G.N0 * (G.N2 / 2 + 1)));
       if (!tw[0]) tw[0] = make_twiddles(G.N0);
       if (!tw[2]) tw[2] = make_twiddles(G.N2);
-      set_fs_attrs();
+      if (fullsym()) {
+        spec_fs = keep((cpx<CT>*)dalloc(sizeof(cpx<CT>) * Q * Spec2<CT>::field(G.N0, G.N2 / 2 + 1)));
+      }
     }
   }
 
@@ -1283,11 +1210,7 @@ class Solver : public SolverBase {
     if (run_flags_h) (void)hipHostFree(run_flags_h);
     run_flags_h = nullptr;
     if (wk_part_h) (void)hipHostFree(wk_part_h);
-    if (wk_coef_h) (void)hipHostFree(wk_coef_h);
-    if (wk_small_h) (void)hipHostFree(wk_small_h);
     wk_part_h = nullptr;
-    wk_coef_h = nullptr;
-    wk_small_h = nullptr;
     ctl_h = nullptr;
     stats_h = nullptr;
     partials_h = nullptr;
@@ -2047,66 +1970,21 @@ class Solver : public SolverBase {
     return n;
   }
 
-  // Full-symbol launch shapes: rows per block of the row passes (LDS-limited,
-  // >= 512 blocks where the grid allows), j_y columns per block of the
-  // column pass (>= 256 blocks where possible).  At N <= 512 every pass is
-  // latency-bound, so these keep one row / one column per block there.
-  int fs_rows_per_block() const {
-    const size_t c = sizeof(cpx<CT>);
-    int R = (int)std::max<size_t>(1, (size_t)65536 / (2 * ((Q + 1) / 2) * G.N2 * c));
-    int p = 1;
-    while (p * 2 <= R) p *= 2;
-    while (p > 1 && G.N0 / p < 512) p >>= 1;
-    return std::min(p, G.N0);
-  }
-  int fs_cols_per_block() const {
-    const size_t c = sizeof(cpx<CT>);
-    int J = (int)std::max<size_t>(1, (size_t)98304 / (2 * Q * G.N0 * c));
-    J = std::min(J, 8);
-    const int NH = G.N2 / 2 + 1;
-    while (J > 1 && (NH + J - 1) / J < 256) J >>= 1;
-    return std::max(J, 1);
-  }
-  size_t fs_rows_lds() const { return (size_t)2 * ((Q + 1) / 2) * fs_rows_per_block() * G.N2 * sizeof(cpx<CT>); }
-  size_t fs_cols_lds() const { return (size_t)2 * Q * fs_cols_per_block() * G.N0 * sizeof(cpx<CT>); }
-  // split column pass: lines per block of the x transforms
-  int fs_lines_per_block() const { return std::max(1, std::min(8, 2048 / G.N0)); }
-  size_t fs_lines_lds() const { return (size_t)2 * fs_lines_per_block() * G.N0 * sizeof(cpx<CT>); }
-
-  void set_fs_attrs() {
-    if constexpr (D == 2 && !DV) {
-      MSC_HIPCK(hipFuncSetAttribute((const void*)k_fs_rows_fwd<L, T, CT, TM>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)fs_rows_lds()));
-      MSC_HIPCK(hipFuncSetAttribute((const void*)k_fs_rows_inv<L, T, CT, TM>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)fs_rows_lds()));
-      MSC_HIPCK(hipFuncSetAttribute((const void*)k_fs_cols_fft<L, T, CT, TM>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)fs_lines_lds()));
-      MSC_HIPCK(hipFuncSetAttribute((const void*)k_fs_cols_solve<L, T, CT, TM>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)fs_cols_lds()));
-    }
-  }
-
   // The full-symbol correction of Eq. (full-symbol) for (step n, sweep ell),
   // guarded on the device like the shadow passes.  head: the rows pass (with
   // Ac and Fin, it decides acceptance first); tail: the column pass and the
   // inverse rows pass, which leave f_{l+1} in the sweep's output buffer (out
   // when c is null).
   void enqueue_fullsym(const DevCtl* c, int n, int ell, double a, const AcceptArgs<L, T>* Ac,
-                       const FinishArgs* Fin, bool head, bool tail, T* out, const TM* rin = nullptr,
-                       int plain = 0) {
+                       const FinishArgs* Fin, bool head, bool tail, T* out) {
     if constexpr (D == 2 && !DV) {
       FsArgs<T, CT, TM> F{};
       F.g = CorrGuard{c, n, ell};
       F.do_accept = (Ac && Fin) ? 1 : 0;
       F.Nx = G.N0;
       F.Ny = G.N2;
-      F.lgx = ilog2(G.N0);
-      F.lgy = ilog2(G.N2);
       F.NH = G.N2 / 2 + 1;
-      F.rows_per_block = fs_rows_per_block();
-      F.cols_per_block = fs_cols_per_block();
-      F.r = rin ? rin : rfs;
-      F.plain = plain;
+      F.r = rfs;
       F.spec = spec_fs;
       F.twx = tw[0];
       F.twy = tw[2];
@@ -2116,39 +1994,45 @@ class Solver : public SolverBase {
       F.inv_ns = 1.0 / (double)G.NS;
       F.fb = fb;
       F.out = out;
-      const int rgrid = G.N0 / F.rows_per_block;
+      constexpr int LM = sizeof(CT) == 8 ? 8 : 9;  // the longest lines that fit (fs_supported)
       if (head) {
-        AcceptArgs<L, T> none{};
-        const FinishArgs nofin{};
-        hipLaunchKernelGGL((k_fs_rows_fwd<L, T, CT, TM>), dim3(rgrid), dim3(256), fs_rows_lds(), st, F,
-                           Ac ? *Ac : none, Fin ? *Fin : nofin);
+        const AcceptArgs<L, T> acc = Ac ? *Ac : AcceptArgs<L, T>{};
+        const FinishArgs fin = Fin ? *Fin : FinishArgs{};
+        with_lg<2, LM>(ilog2(G.N2), [&](auto lg) {
+          using S = FsRows<CT, lg.value>;
+          hipLaunchKernelGGL((k_fs_rows_fwd<L, T, CT, TM, lg.value>), dim3((G.N0 + S::R - 1) / S::R), dim3(S::NT), 0,
+                             st, F, acc, fin);
+        });
         MSC_HIPCK(hipGetLastError());
       }
       if (tail) {
-        const int cgrid = pad8((F.NH + F.cols_per_block - 1) / F.cols_per_block);  // XCD-aware order
         // split column pass where it is faster (measured: N_x = 512, 12% per
         // iteration; at N_x <= 256 the extra launches cost more than the
         // parallelism gains)
         const bool split = (tune.fs_split == 1) || (tune.fs_split == 0 && G.N0 >= 512);
-        if (split) {
-          FsArgs<T, CT, TM> Fl = F;
-          Fl.cols_per_block = fs_lines_per_block();
-          const int lgrid = pad8((Q * F.NH + Fl.cols_per_block - 1) / Fl.cols_per_block);
-          const int64_t nk = (int64_t)G.N0 * F.NH;
-          const int sgrid = (int)std::min<int64_t>((nk + 63) / 64, 4096);
-          hipLaunchKernelGGL((k_fs_cols_fft<L, T, CT, TM>), dim3(lgrid), dim3(256), fs_lines_lds(), st, Fl, -1);
-          hipLaunchKernelGGL((k_fs_solve_k<L, T, CT, TM>), dim3(sgrid), dim3(64), 0, st, F);
-          hipLaunchKernelGGL((k_fs_cols_fft<L, T, CT, TM>), dim3(lgrid), dim3(256), fs_lines_lds(), st, Fl, +1);
-        } else {
-          hipLaunchKernelGGL((k_fs_cols_solve<L, T, CT, TM>), dim3(cgrid), dim3(256), fs_cols_lds(), st, F);
-        }
+        with_lg<2, LM>(ilog2(G.N0), [&](auto lg) {
+          if (split) {
+            constexpr int LPB = 256 / LineFft<CT, lg.value, line_le(lg.value)>::TPL;
+            const int lgrid = pad8((Q * F.NH + LPB - 1) / LPB);  // XCD-aware order
+            const int64_t nk = Spec2<CT>::field(G.N0, F.NH);
+            hipLaunchKernelGGL((k_fs_cols_fft<L, T, CT, TM, lg.value, -1>), dim3(lgrid), dim3(256), 0, st, F);
+            hipLaunchKernelGGL((k_fs_solve_k<L, T, CT, TM>), dim3((int)std::min<int64_t>((nk + 63) / 64, 4096)),
+                               dim3(64), 0, st, F);
+            hipLaunchKernelGGL((k_fs_cols_fft<L, T, CT, TM, lg.value, +1>), dim3(lgrid), dim3(256), 0, st, F);
+          } else {
+            hipLaunchKernelGGL((k_fs_cols_solve<L, T, CT, TM, lg.value>), dim3(pad8(F.NH)), dim3(320), 0, st, F);
+          }
+        });
         MSC_HIPCK(hipGetLastError());
-        hipLaunchKernelGGL((k_fs_rows_inv<L, T, CT, TM>), dim3(rgrid), dim3(256), fs_rows_lds(), st, F);
+        with_lg<2, LM>(ilog2(G.N2), [&](auto lg) {
+          using S = FsRows<CT, lg.value>;
+          hipLaunchKernelGGL((k_fs_rows_inv<L, T, CT, TM, lg.value>), dim3((G.N0 + S::R - 1) / S::R), dim3(S::NT), 0,
+                             st, F);
+        });
         MSC_HIPCK(hipGetLastError());
       }
     } else {
-      (void)c, (void)n, (void)ell, (void)a, (void)Ac, (void)Fin, (void)head, (void)tail, (void)out, (void)rin,
-          (void)plain;
+      (void)c, (void)n, (void)ell, (void)a, (void)Ac, (void)Fin, (void)head, (void)tail, (void)out;
     }
   }
 
