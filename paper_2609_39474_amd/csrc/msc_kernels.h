@@ -209,16 +209,38 @@ __global__ void k_init_feq(const double* __restrict__ p, const double* __restric
   }
 }
 
-// P f in FP64 (Eq. moments), written to m.
+// P f in FP64 (Eq. moments), written to m; with partials also per-block sums
+// of the squares of every stored value (a non-finite one makes its sum
+// non-finite), from the same read of the populations.
 template <class L, class T>
-__global__ void k_moments(const T* __restrict__ f, double* __restrict__ m, int64_t NS) {
+__global__ __launch_bounds__(256) void k_moments(const T* __restrict__ f, double* __restrict__ m, int64_t NS,
+                                                 double* __restrict__ partials) {
+  __shared__ double red[4];
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  double acc = 0.0;
   for (int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; s < NS; s += stride) {
     double M[4];
     site_moments<L, T>(f, NS, s, M);
 #pragma unroll
     for (int b = 0; b <= L::D; ++b) m[b * NS + s] = M[b];
+    if (partials) {
+#pragma unroll
+      for (int k = 0; k < L::Q; ++k) {
+        const double v = (double)f[(int64_t)k * NS + s];
+        acc += v * v;
+      }
+      if constexpr (PopDev<T>::value) {
+#pragma unroll
+        for (int b = 0; b <= L::D; ++b) acc += M[b] * M[b];
+      }
+    }
   }
+  if (!partials) return;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  if (threadIdx.x == 0) partials[blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
 }
 
 // out = fT + E dm (Eq. lift, Eq. shadow-update) with the same arithmetic the
@@ -336,25 +358,6 @@ __global__ __launch_bounds__(256) void k_absmax(const double* __restrict__ v, in
   __syncthreads();
   for (int w = 128; w > 0; w >>= 1) {
     if ((int)threadIdx.x < w) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + w]);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) partials[blockIdx.x] = red[0];
-}
-
-// Per-block partial sums of v^2 (a non-finite entry makes the sum non-finite).
-template <class T>
-__global__ __launch_bounds__(256) void k_sumsq(const T* __restrict__ v, int64_t n, double* partials) {
-  __shared__ double red[256];
-  double acc = 0.0;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-    const double x = (double)v[i];
-    acc += x * x;
-  }
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
     __syncthreads();
   }
   if (threadIdx.x == 0) partials[blockIdx.x] = red[0];

@@ -109,6 +109,7 @@ class Solver : public SolverBase {
       double* pd = nullptr;
       double* ud = nullptr;
       if (on_device) {
+        after_default_stream();
         pd = const_cast<double*>(phat0);
         ud = const_cast<double*>(u0);
       } else {
@@ -135,7 +136,7 @@ class Solver : public SolverBase {
       MSC_HIPCK(hipGetLastError());
       reset_history_from_current();
       sync();
-      n_next = 0;
+      for (auto& t : tw_host) t = {};
       return MSC_OK;
     });
   }
@@ -162,9 +163,7 @@ class Solver : public SolverBase {
       }
       int n_dev = n_next, ell_dev = 1;
       int64_t bdf_dev = bdf_count;
-      int batch = 1;
       msc_status rc = MSC_OK;
-      if (recording) pull_ctl();
       while (n_dev < n_end) {
         // while recording, one step per synchronisation so that the state at
         // each step's start can be checkpointed
@@ -199,8 +198,7 @@ class Solver : public SolverBase {
           for (int ell = ell0; ell <= ell1; ++ell)
             enqueue_iteration(n, ell, q, order, a, use_sched, stat_base, ell == ell1, recon, a_prev, defer);
         }
-        MSC_HIPCK(hipMemcpyAsync(ctl_h, ctl, sizeof(DevCtl), hipMemcpyDeviceToHost, st));
-        sync();
+        fetch_ctl(nsteps);
         const uint64_t ph = ctl_h->phase;
         const int pn = phase_n(ph), pell = phase_ell(ph);
         const uint32_t ps = phase_state(ph);
@@ -217,6 +215,7 @@ class Solver : public SolverBase {
           copy_stats(out, stat_base, pn - stat_base + 1);
           n_next = pn;
           bdf_count = bdf_dev;
+          batch = 1;
           sched_pos += (pn - stat_base);
           sync();
           return rc;
@@ -248,7 +247,6 @@ class Solver : public SolverBase {
   // -------------------------------------------------------- explicit march --
   msc_status explicit_step(int64_t nsteps) override {
     return guard([&]() -> msc_status {
-      pull_ctl();
       T* A = fb.p[cur_roles().slot_hist[0]];
       T* B = fb.p[cur_roles().slot_w[0]];
       SweepArgs<T, TM> S = sweep_args(0.0);
@@ -284,10 +282,8 @@ class Solver : public SolverBase {
       }
       if (cur != A) std::swap(cur_roles().slot_hist[0], cur_roles().slot_w[0]);
       MSC_HIPCK(hipMemcpyAsync(ctl, ctl_h, sizeof(DevCtl), hipMemcpyHostToDevice, st));
-      reset_history_from_current();
       // non-finite check on the final state
-      const double ss = pop_sumsq(fb.p[cur_roles().slot_hist[0]]);
-      if (!std::isfinite(ss)) {
+      if (!std::isfinite(reset_history_from_current(true))) {
         last_error = "non-finite population after the explicit march";
         return MSC_ERR_NONFINITE;
       }
@@ -391,11 +387,15 @@ class Solver : public SolverBase {
   // -------------------------------------------------------------- outputs --
   msc_status moments(double* phat, double* u, bool on_device) override {
     return guard([&]() {
-      pull_ctl();
+      if (on_device) after_default_stream();
       const double* m = mb[cur_roles().slot_m[0]];
       const hipMemcpyKind kind = on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-      if (phat) MSC_HIPCK(hipMemcpyAsync(phat, m, sizeof(double) * G.NS, kind, st));
-      if (u) MSC_HIPCK(hipMemcpyAsync(u, m + G.NS, sizeof(double) * D * G.NS, kind, st));
+      if (phat && u == phat + G.NS) {
+        MSC_HIPCK(hipMemcpyAsync(phat, m, sizeof(double) * (D + 1) * G.NS, kind, st));
+      } else {
+        if (phat) MSC_HIPCK(hipMemcpyAsync(phat, m, sizeof(double) * G.NS, kind, st));
+        if (u) MSC_HIPCK(hipMemcpyAsync(u, m + G.NS, sizeof(double) * D * G.NS, kind, st));
+      }
       sync();
       return MSC_OK;
     });
@@ -423,7 +423,6 @@ class Solver : public SolverBase {
 
   msc_status get_populations(double* f) override {
     return guard([&]() {
-      pull_ctl();
       download_pop(fb.p[cur_roles().slot_hist[0]], f);
       return MSC_OK;
     });
@@ -431,7 +430,6 @@ class Solver : public SolverBase {
 
   msc_status set_populations(const double* f) override {
     return guard([&]() {
-      pull_ctl();
       if (DV) sig = sigma_for({f});
       upload_pop(f, fb.p[cur_roles().slot_hist[0]]);
       reset_history_from_current();
@@ -444,7 +442,6 @@ class Solver : public SolverBase {
   msc_status sweep(const double* f, const double* h_in, double a, double* fT, double* Pr_out,
                    double* R) override {
     return guard([&]() {
-      pull_ctl();
       T* A = fb.p[cur_roles().slot_w[0]];
       T* B = fb.p[cur_roles().slot_w[1]];
       const float sig_state = sig;  // the work buffers may take another scale
@@ -474,7 +471,6 @@ class Solver : public SolverBase {
         last_error = "the shadow corrector is not available for this lattice/grid";
         return MSC_ERR_UNSUPPORTED;
       }
-      pull_ctl();
       T* A = fb.p[cur_roles().slot_w[0]];
       T* B = fb.p[cur_roles().slot_w[1]];
       const float sig_state = sig;
@@ -507,7 +503,6 @@ class Solver : public SolverBase {
   msc_status correct_fullsym(const double* f, const double* h_in, double a, double* fnext, double* dm_out,
                              double* R) {
     return guard([&]() -> msc_status {
-      pull_ctl();
       T* A = fb.p[cur_roles().slot_w[0]];
       T* B = fb.p[cur_roles().slot_w[1]];
       upload_pop(f, A);
@@ -528,23 +523,23 @@ class Solver : public SolverBase {
   }
 
   // ------------------------------------------- wall-bounded correction --
-  void wall_allocate() {
+  template <class W>
+  void wall_parts(W&& want) {
     const int64_t n = (int64_t)Q * G.NS;
     wk_m = P.wall_restart > 0 ? P.wall_restart : 50;
     std::fill(wk_pred, wk_pred + kWallPred, 8);
-    wk_V = keep((double*)dalloc(sizeof(double) * (wk_m + 1) * n));
-    wk_R = keep((double*)dalloc(sizeof(double) * n));
-    wk_D = keep((double*)dalloc(sizeof(double) * n));
-    wk_vc = keep((double*)dalloc(sizeof(double) * n));
-    wk_spec = keep((cpx<double>*)dalloc(sizeof(cpx<double>) * 3 * Spec2<double>::field(G.N0, G.N2 / 2 + 1)));
-    wk_mref = keep((double*)dalloc(sizeof(double) * 3 * G.NS));
-    wk_sref = keep((double*)dalloc(sizeof(double) * 3 * G.NS));
+    want(wk_V, sizeof(double) * (wk_m + 1) * n);
+    want(wk_R, sizeof(double) * n);
+    want(wk_D, sizeof(double) * n);
+    want(wk_vc, sizeof(double) * n);
+    want(wk_spec, sizeof(cpx<double>) * 3 * Spec2<double>::field(G.N0, G.N2 / 2 + 1));
+    want(wk_mref, sizeof(double) * 3 * G.NS);
+    want(wk_sref, sizeof(double) * 3 * G.NS);
     // the state word, then the dot-product partials (one entry of N_x per vector)
-    wk_part = keep((double*)dalloc(sizeof(double) * (1 + (size_t)G.N0 * (wk_m + 2))));
-    wk_coef = keep((double*)dalloc(sizeof(double) * (wk_m + 2)));
+    want(wk_part, sizeof(double) * (1 + (size_t)G.N0 * (wk_m + 2)));
+    want(wk_coef, sizeof(double) * (wk_m + 2));
     // Hd (m x m), cs, sn (m each), g (m + 1), hcol (m + 2)
-    wk_small = keep((double*)dalloc(sizeof(double) * ((size_t)wk_m * wk_m + 4 * wk_m + 3)));
-    MSC_HIPCK(hipHostMalloc((void**)&wk_part_h, sizeof(double) * (1 + G.N0), hipHostMallocDefault));
+    want(wk_small, sizeof(double) * ((size_t)wk_m * wk_m + 4 * wk_m + 3));
   }
 
   WallArgs wall_args() const {
@@ -700,9 +695,8 @@ class Solver : public SolverBase {
           double Rref = 0.0, Rprev = 0.0;
           for (int ell = 1; ell <= P.k_max; ++ell) {
             enqueue_iteration(n, ell, q, order, a, use_sched, stat_base, true);
-            MSC_HIPCK(hipMemcpyAsync(ctl_h, ctl, sizeof(DevCtl), hipMemcpyDeviceToHost, st));
             MSC_HIPCK(hipMemcpyAsync(&Rdev, Rhist + (ell - 1), sizeof(double), hipMemcpyDeviceToHost, st));
-            sync();
+            fetch_ctl(nsteps);
             const uint32_t ps = phase_state(ctl_h->phase);
             if (ps == PH_ACCEPTED) {
               bdf_count += 1;
@@ -759,7 +753,6 @@ class Solver : public SolverBase {
                            double* R) {
     return guard([&]() -> msc_status {
       if constexpr (std::is_same<T, double>::value) {
-        pull_ctl();
         T* A = fb.p[cur_roles().slot_w[0]];
         T* B = fb.p[cur_roles().slot_w[1]];
         upload_pop(f, A);
@@ -805,7 +798,7 @@ class Solver : public SolverBase {
 
   msc_status get_state(double* state, int64_t* bc) override {
     return guard([&]() {
-      pull_ctl();
+      complete_history();
       const int64_t FQ = (int64_t)Q * G.NS, FM = (int64_t)(D + 1) * G.NS;
       for (int i = 0; i < 3; ++i) download_pop(fb.p[cur_roles().slot_hist[i]], state + i * FQ);
       MSC_HIPCK(hipMemcpyAsync(state + 3 * FQ, mb[cur_roles().slot_m[0]], sizeof(double) * FM,
@@ -820,7 +813,6 @@ class Solver : public SolverBase {
 
   msc_status set_state(const double* state, int64_t bc) override {
     return guard([&]() {
-      pull_ctl();
       const int64_t FQ = (int64_t)Q * G.NS, FM = (int64_t)(D + 1) * G.NS;
       if (DV) sig = sigma_for({state, state + FQ, state + 2 * FQ});
       for (int i = 0; i < 3; ++i) upload_pop(state + i * FQ, fb.p[cur_roles().slot_hist[i]]);
@@ -829,6 +821,7 @@ class Solver : public SolverBase {
       MSC_HIPCK(hipMemcpyAsync(mb[cur_roles().slot_m[1]], state + 3 * FQ + FM, sizeof(double) * FM,
                                hipMemcpyHostToDevice, st));
       sync();
+      lazy_history = false;
       bdf_count = bc;
       return MSC_OK;
     });
@@ -865,6 +858,7 @@ class Solver : public SolverBase {
       int kmax = 1;
       for (int r = 0; r < nsteps; ++r) kmax = std::max(kmax, records[records.size() - 1 - r].K);
       ensure_adjoint_buffers(kmax);
+      if (on_device) after_default_stream();
       const int64_t SZ = state_size();
       double* cur = adj_lam[0];
       double* nxt = adj_lam[1];
@@ -885,6 +879,7 @@ class Solver : public SolverBase {
   msc_status init_adjoint(const double* phat0, const double* u0, const double* lam, double* lam_phat0,
                           double* lam_u0, bool on_device) override {
     return guard([&]() -> msc_status {
+      if (on_device) after_default_stream();
       const int64_t NS = G.NS, SZ = state_size();
       const double *pd = phat0, *ud = u0, *ld = lam;
       double *lp = lam_phat0, *lu = lam_u0;
@@ -988,23 +983,29 @@ class Solver : public SolverBase {
   double* partials_h = nullptr;
   double* presum = nullptr;                   // folded partials for large sweep grids
   static constexpr int kFusedParts = 4096;    // decision kernels sum at most this many partials
-  int nparts_cap = 0;
+  int nparts_cap = 0, nparts_h = 0;
   DevCtl* ctl = nullptr;
   DevCtl* ctl_h = nullptr;
   double* Rhist = nullptr;
-  StepStat* stats_d = nullptr;
+  StepStat* stats_d = nullptr;  // of the current call
   StepStat* stats_h = nullptr;
+  StepStat* stats_long = nullptr;
+  std::vector<StepStat> stats_long_h;
   int stats_cap = 0;
   int32_t* sched_d = nullptr;
   int sched_cap = 0;
   std::vector<int32_t> sched_h, sched_host_view;
   int64_t sched_pos = 0;
   cpx<CT>* tw[3] = {nullptr, nullptr, nullptr};
+  std::vector<cpx<CT>> tw_host[3];
   double* stage = nullptr;
   std::vector<void*> allocs;
 
+  hipEvent_t order_ev = nullptr;  // see after_default_stream
   int n_next = 0;
   int64_t bdf_count = 0;
+  bool lazy_history = false;  // complete_history has copies to make
+  int batch = 1;  // physical steps enqueued before the next synchronisation
   int last_iters = 4;
   float sig = 1.0f;  // scale of FP16 deviation storage (unused otherwise)
 
@@ -1079,12 +1080,27 @@ class Solver : public SolverBase {
 
   void sync() { MSC_HIPCK(hipStreamSynchronize(st)); }
 
+  // A context without a caller's stream works on one of its own, which nothing
+  // orders after the default stream, where such a caller's program fills the
+  // tensors it passes and where memory that its allocator hands out again may
+  // still be in use.  Called where device memory comes in from the caller.
+  void after_default_stream() {
+    if (P.stream) return;
+    const hipError_t q = hipStreamQuery(nullptr);
+    if (q == hipSuccess) return;
+    (void)hipGetLastError();  // (not ready is no error here)
+    if (!order_ev) MSC_HIPCK(hipEventCreateWithFlags(&order_ev, hipEventDisableTiming));
+    MSC_HIPCK(hipEventRecord(order_ev, nullptr));
+    MSC_HIPCK(hipStreamWaitEvent(st, order_ev, 0));
+  }
+
   void* dalloc(size_t bytes) {
     void* p = nullptr;
     if (bytes == 0) bytes = 1;
     if (P.alloc_fn) {
       p = P.alloc_fn(bytes, P.alloc_user);
       if (!p) throw OomError{};
+      after_default_stream();
     } else {
       hipError_t e = hipMalloc(&p, bytes);
       if (e == hipErrorOutOfMemory) throw OomError{};
@@ -1142,47 +1158,90 @@ class Solver : public SolverBase {
     return (size_t)4 * G.n[2] * c <= 131072 && (size_t)8 * Nmax * c <= 131072;
   }
 
+  // The context's buffers: the small ones share one device allocation (256-byte
+  // aligned parts), because a context per solve is ordinary use and each
+  // allocation is a call into the caller's allocator; the large ones have their
+  // own, so that an allocator finds room for them in what it holds.
+  static constexpr size_t kOwnBlock = (size_t)8 << 20;
+  struct Part {
+    void* p;  // the pointer to set
+    size_t bytes;
+  };
   void allocate() {
     const int64_t NS = G.NS;
-    const size_t fbytes = pop_bytes();
-    for (int i = 0; i < 5; ++i) fb.p[i] = keep((T*)dalloc(fbytes));
-    for (int i = 0; i < 3; ++i) mb[i] = keep((double*)dalloc(sizeof(double) * (D + 1) * NS));
-    h = keep((double*)dalloc(sizeof(double) * (D + 1) * NS));
-    h_alt = keep((double*)dalloc(sizeof(double) * (D + 1) * NS));
-    Pr = keep((TM*)dalloc(sizeof(TM) * (D + 1) * NS));
-    dm = keep((TM*)dalloc(sizeof(TM) * (D + 1) * NS));
-    MSC_HIPCK(hipMemsetAsync(h, 0, sizeof(double) * (D + 1) * NS, st));
-    MSC_HIPCK(hipMemsetAsync(h_alt, 0, sizeof(double) * (D + 1) * NS, st));
-    MSC_HIPCK(hipMemsetAsync(dm, 0, sizeof(TM) * (D + 1) * NS, st));
-    ctl = keep((DevCtl*)dalloc(sizeof(DevCtl)));
-    MSC_HIPCK(hipHostMalloc((void**)&ctl_h, sizeof(DevCtl), hipHostMallocDefault));
-    Rhist = keep((double*)dalloc(sizeof(double) * std::max(P.k_max, 1)));
-    presum = keep((double*)dalloc(sizeof(double)));
+    std::vector<Part> parts;
+    auto want = [&](auto*& p, size_t bytes) { parts.push_back({&p, bytes}); };
+    const size_t fields = sizeof(double) * (D + 1) * NS;
+    want(h, fields);
+    want(h_alt, fields);
+    want(dm, sizeof(TM) * (D + 1) * NS);
+    for (int i = 0; i < 5; ++i) want(fb.p[i], pop_bytes());
+    for (int i = 0; i < 3; ++i) want(mb[i], fields);
+    want(Pr, sizeof(TM) * (D + 1) * NS);
+    want(ctl, kCtlBytes);
+    want(Rhist, sizeof(double) * std::max(P.k_max, 1));
+    want(presum, sizeof(double));
     choose_sweep();
-    ensure_partials(sweep_grid_max());
+    nparts_cap = std::max(sweep_grid_max(), 1024);
+    want(partials, sizeof(double) * nparts_cap);
+    const bool fs = (fullsym() || wallkin()) && fs_supported();
+    bool axis[3] = {false, false, false};
     if (corrector_supported()) {
       if (D == 2) {
-        const int NB = G.N2 / 4 + 1;
-        spec = keep((cpx<CT>*)dalloc(sizeof(cpx<CT>) * 3 * Spec2<CT>::field(G.N0, NB)));
-        spec_alt = keep((cpx<CT>*)dalloc(sizeof(cpx<CT>) * 3 * Spec2<CT>::field(G.N0, NB)));
-        tw[0] = make_twiddles(G.N0);
-        tw[2] = make_twiddles(G.N2);
+        const size_t bytes = sizeof(cpx<CT>) * 3 * Spec2<CT>::field(G.N0, G.N2 / 4 + 1);
+        want(spec, bytes);
+        want(spec_alt, bytes);
       } else {
         const int NBz = G.n[2] / 4 + 1, NBy = 2 * (G.n[1] / 4) + 1;
-        spec = keep((cpx<CT>*)dalloc(sizeof(cpx<CT>) * 4 * Spec3<CT>::field(G.n[0], G.n[1], NBz)));
-        spec2 = keep((cpx<CT>*)dalloc(sizeof(cpx<CT>) * 4 * Spec3<CT>::field(G.n[0], NBy, NBz)));
-        for (int a = 0; a < 3; ++a) tw[a] = make_twiddles(G.n[a]);
+        want(spec, sizeof(cpx<CT>) * 4 * Spec3<CT>::field(G.n[0], G.n[1], NBz));
+        want(spec2, sizeof(cpx<CT>) * 4 * Spec3<CT>::field(G.n[0], NBy, NBz));
+        axis[1] = true;
       }
+      axis[0] = axis[2] = true;
     }
-    if (wallkin() && wall_supported()) wall_allocate();
-    if ((fullsym() || wallkin()) && fs_supported()) {
-      rfs = keep((TM*)dalloc(sizeof(TM) * (int64_t)Q * NS));
-      if (!tw[0]) tw[0] = make_twiddles(G.N0);
-      if (!tw[2]) tw[2] = make_twiddles(G.N2);
-      if (fullsym()) {
-        spec_fs = keep((cpx<CT>*)dalloc(sizeof(cpx<CT>) * Q * Spec2<CT>::field(G.N0, G.N2 / 2 + 1)));
+    if (fs) {
+      want(rfs, sizeof(TM) * (int64_t)Q * NS);
+      if (fullsym()) want(spec_fs, sizeof(cpx<CT>) * Q * Spec2<CT>::field(G.N0, G.N2 / 2 + 1));
+      axis[0] = axis[2] = true;
+    }
+    for (int i = 0; i < 3; ++i)
+      if (axis[i]) {
+        tw_host[i] = twiddle_tables<CT>(ilog2(i == 0 ? G.N0 : (i == 1 ? G.N1 : G.N2)));
+        want(tw[i], sizeof(cpx<CT>) * tw_host[i].size());
       }
+    if (wallkin() && wall_supported()) wall_parts(want);
+
+    size_t total = 0;
+    for (const Part& q : parts)
+      if (q.bytes < kOwnBlock) total += (q.bytes + 255) / 256 * 256;
+    char* base = keep((char*)dalloc(total));
+    for (size_t i = 0; i < parts.size(); ++i) {
+      const Part& q = parts[i];
+      char* at = base;
+      if (q.bytes < kOwnBlock)
+        base += (q.bytes + 255) / 256 * 256;
+      else
+        at = keep((char*)dalloc(q.bytes));
+      std::memcpy(q.p, &at, sizeof(at));
     }
+    // the history terms and the correction start at zero (one fill where they
+    // share the block)
+    const size_t tmb = sizeof(TM) * (D + 1) * NS;
+    if (fields < kOwnBlock) {
+      MSC_HIPCK(hipMemsetAsync(h, 0, (char*)dm - (char*)h + tmb, st));
+    } else {
+      MSC_HIPCK(hipMemsetAsync(h, 0, fields, st));
+      MSC_HIPCK(hipMemsetAsync(h_alt, 0, fields, st));
+      MSC_HIPCK(hipMemsetAsync(dm, 0, tmb, st));
+    }
+    // (the host tables are kept until the copies are done: init waits)
+    for (int i = 0; i < 3; ++i)
+      if (axis[i])
+        MSC_HIPCK(hipMemcpyAsync(tw[i], tw_host[i].data(), sizeof(cpx<CT>) * tw_host[i].size(),
+                                 hipMemcpyHostToDevice, st));
+    MSC_HIPCK(hipHostMalloc((void**)&ctl_h, kCtlBytes, hipHostMallocDefault));
+    if (wallkin() && wall_supported())
+      MSC_HIPCK(hipHostMalloc((void**)&wk_part_h, sizeof(double) * (1 + G.N0), hipHostMallocDefault));
   }
 
   void release() {
@@ -1195,6 +1254,8 @@ class Solver : public SolverBase {
       (void)hipEventDestroy(e.b);
     }
     for (auto& e : ev_free) (void)hipEventDestroy(e);
+    if (order_ev) (void)hipEventDestroy(order_ev);
+    order_ev = nullptr;
     ev_live.clear();
     ev_free.clear();
     if (st) (void)hipStreamSynchronize(st);
@@ -1205,23 +1266,21 @@ class Solver : public SolverBase {
     for (void* p : allocs) dfree(p);
     allocs.clear();
     if (ctl_h) (void)hipHostFree(ctl_h);
-    if (stats_h) (void)hipHostFree(stats_h);
     if (partials_h) (void)hipHostFree(partials_h);
     if (run_flags_h) (void)hipHostFree(run_flags_h);
     run_flags_h = nullptr;
     if (wk_part_h) (void)hipHostFree(wk_part_h);
     wk_part_h = nullptr;
     ctl_h = nullptr;
-    stats_h = nullptr;
     partials_h = nullptr;
   }
 
-  template <class CX = CT>
-  cpx<CX>* make_twiddles(int N, std::vector<void*>* owner = nullptr) {
-    const std::vector<cpx<CX>> t = twiddle_tables<CX>(ilog2(N));
-    cpx<CX>* d = (cpx<CX>*)dalloc(sizeof(cpx<CX>) * t.size());
-    (owner ? owner : &allocs)->push_back((void*)d);
-    MSC_HIPCK(hipMemcpyAsync(d, t.data(), sizeof(cpx<CX>) * t.size(), hipMemcpyHostToDevice, st));
+  // FP64 twiddle tables of the adjoint's transforms
+  cpx<double>* adj_twiddles(int N) {
+    const std::vector<cpx<double>> t = twiddle_tables<double>(ilog2(N));
+    cpx<double>* d = (cpx<double>*)dalloc(sizeof(cpx<double>) * t.size());
+    adj_allocs.push_back((void*)d);
+    MSC_HIPCK(hipMemcpyAsync(d, t.data(), sizeof(cpx<double>) * t.size(), hipMemcpyHostToDevice, st));
     sync();  // t goes out of scope
     return d;
   }
@@ -1234,17 +1293,43 @@ class Solver : public SolverBase {
   void ensure_partials(int n) {
     if (n <= nparts_cap) return;
     partials = keep((double*)dalloc(sizeof(double) * n));
-    if (partials_h) (void)hipHostFree(partials_h);
-    MSC_HIPCK(hipHostMalloc((void**)&partials_h, sizeof(double) * n, hipHostMallocDefault));
     nparts_cap = n;
   }
 
+  // pinned host memory for n partials (diagnostics and checks only)
+  double* host_partials(int n) {
+    if (n > nparts_h) {
+      if (partials_h) (void)hipHostFree(partials_h);
+      partials_h = nullptr;
+      nparts_h = std::max(n, 1024);
+      MSC_HIPCK(hipHostMalloc((void**)&partials_h, sizeof(double) * nparts_h, hipHostMallocDefault));
+    }
+    return partials_h;
+  }
+
+  // Step statistics: the first kInlineStats lie behind the control block, so
+  // that one copy brings both; longer calls take buffers of their own.
+  static constexpr int kInlineStats = 64;
+  static constexpr size_t kCtlBytes = sizeof(DevCtl) + kInlineStats * sizeof(StepStat);
   void ensure_stats(int n) {
-    if (n <= stats_cap) return;
-    stats_d = keep((StepStat*)dalloc(sizeof(StepStat) * n));
-    if (stats_h) (void)hipHostFree(stats_h);
-    MSC_HIPCK(hipHostMalloc((void**)&stats_h, sizeof(StepStat) * n, hipHostMallocDefault));
-    stats_cap = n;
+    if (n <= kInlineStats) {
+      stats_d = reinterpret_cast<StepStat*>(ctl + 1);
+      stats_h = reinterpret_cast<StepStat*>(ctl_h + 1);
+      return;
+    }
+    if (n > stats_cap) {
+      stats_long = keep((StepStat*)dalloc(sizeof(StepStat) * n));
+      stats_long_h.resize(n);
+      stats_cap = n;
+    }
+    stats_d = stats_long;
+    stats_h = stats_long_h.data();
+  }
+  // the control block and, of a short call, its n steps' statistics; waits
+  void fetch_ctl(int n) {
+    const size_t more = n <= kInlineStats ? n * sizeof(StepStat) : 0;
+    MSC_HIPCK(hipMemcpyAsync(ctl_h, ctl, sizeof(DevCtl) + more, hipMemcpyDeviceToHost, st));
+    sync();
   }
 
   void ensure_sched(int n) {
@@ -1256,8 +1341,10 @@ class Solver : public SolverBase {
   void copy_stats(msc_step_stats* out, int base, int count) {
     (void)base;
     if (!out || count <= 0) return;
-    MSC_HIPCK(hipMemcpyAsync(stats_h, stats_d, sizeof(StepStat) * count, hipMemcpyDeviceToHost, st));
-    sync();
+    if (stats_d == stats_long) {
+      MSC_HIPCK(hipMemcpyAsync(stats_h, stats_d, sizeof(StepStat) * count, hipMemcpyDeviceToHost, st));
+      sync();
+    }
     for (int i = 0; i < count; ++i) {
       out[i].q = stats_h[i].q;
       out[i].iters = stats_h[i].iters;
@@ -1269,26 +1356,39 @@ class Solver : public SolverBase {
     }
   }
 
-  // Buffer roles of the next step to run (host copy; pull_ctl first).
+  // Buffer roles of the next step to run.  Between calls the host's copy of the
+  // control block equals the device's: every call that changes it ends with a
+  // copy one way or the other.
   Roles& cur_roles() { return ctl_h->roles[n_next & 1]; }
 
-  void pull_ctl() {
-    MSC_HIPCK(hipMemcpyAsync(ctl_h, ctl, sizeof(DevCtl), hipMemcpyDeviceToHost, st));
-    sync();
+  // m^n = P f^n and the BDF history reset (next step BDF1, whose trial uses
+  // f^n alone): m^{n-1} = m^n, f^{n-1} = f^{n-2} = f^n, which are left to
+  // complete_history, because the march never reads a state older than its
+  // step count.  Returns sum f^2 (non-finite if a value is) where asked.
+  double reset_history_from_current(bool check = false) {
+    const T* f = fb.p[cur_roles().slot_hist[0]];
+    const int grid = check ? 1024 : ew_grid();
+    if (check) ensure_partials(grid);
+    hipLaunchKernelGGL((k_moments<L, T>), dim3(grid), dim3(256), 0, st, f, mb[cur_roles().slot_m[0]], G.NS,
+                       check ? partials : nullptr);
+    MSC_HIPCK(hipGetLastError());
+    bdf_count = 0;
+    lazy_history = true;
+    return check ? sum_partials_host(grid) : 0.0;
   }
 
-  // m^n = P f^n, m^{n-1} = m^n, f^{n-1} = f^{n-2} = f^n, BDF history reset
-  // (next step BDF1, whose trial uses f^n alone).
-  void reset_history_from_current() {
-    for (int i = 1; i < 3; ++i)
-      MSC_HIPCK(hipMemcpyAsync(fb.p[cur_roles().slot_hist[i]], fb.p[cur_roles().slot_hist[0]], pop_bytes(),
+  // The states older than the march's step count since the last reset.
+  void complete_history() {
+    if (!lazy_history) return;
+    lazy_history = false;
+    if (bdf_count >= 2) return;
+    const Roles& ro = cur_roles();
+    for (int i = (int)bdf_count + 1; i < 3; ++i)
+      MSC_HIPCK(hipMemcpyAsync(fb.p[ro.slot_hist[i]], fb.p[ro.slot_hist[bdf_count]], pop_bytes(),
                                hipMemcpyDeviceToDevice, st));
-    hipLaunchKernelGGL((k_moments<L, T>), dim3(ew_grid()), dim3(256), 0, st, fb.p[cur_roles().slot_hist[0]],
-                       mb[cur_roles().slot_m[0]], G.NS);
-    MSC_HIPCK(hipGetLastError());
-    MSC_HIPCK(hipMemcpyAsync(mb[cur_roles().slot_m[1]], mb[cur_roles().slot_m[0]], sizeof(double) * (D + 1) * G.NS,
-                             hipMemcpyDeviceToDevice, st));
-    bdf_count = 0;
+    if (bdf_count == 0)
+      MSC_HIPCK(hipMemcpyAsync(mb[ro.slot_m[1]], mb[ro.slot_m[0]], sizeof(double) * (D + 1) * G.NS,
+                               hipMemcpyDeviceToDevice, st));
   }
 
   // bytes of one population buffer: Q N_sites values, plus the FP32 moments
@@ -1348,11 +1448,12 @@ class Solver : public SolverBase {
       MSC_HIPCK(hipMemcpyAsync(stg, f, sizeof(double) * Q * G.NS, hipMemcpyHostToDevice, st));
       hipLaunchKernelGGL((k_pop_maxdev<L>), dim3(grid), dim3(256), 0, st, (const double*)stg, G.NS, partials);
       MSC_HIPCK(hipGetLastError());
-      MSC_HIPCK(hipMemcpyAsync(partials_h, partials, sizeof(double) * 2 * grid, hipMemcpyDeviceToHost, st));
+      const double* ph = host_partials(2 * grid);
+      MSC_HIPCK(hipMemcpyAsync((void*)ph, partials, sizeof(double) * 2 * grid, hipMemcpyDeviceToHost, st));
       sync();
       for (int i = 0; i < grid; ++i) {
-        md = std::max(md, partials_h[2 * i]);
-        mm = std::max(mm, partials_h[2 * i + 1]);
+        md = std::max(md, ph[2 * i]);
+        mm = std::max(mm, ph[2 * i + 1]);
       }
     }
     return choose_sigma(md, mm);
@@ -1363,39 +1464,27 @@ class Solver : public SolverBase {
     ensure_partials(grid);
     hipLaunchKernelGGL(k_absmax<0>, dim3(grid), dim3(256), 0, st, v, n, partials);
     MSC_HIPCK(hipGetLastError());
-    MSC_HIPCK(hipMemcpyAsync(partials_h, partials, sizeof(double) * grid, hipMemcpyDeviceToHost, st));
+    const double* ph = host_partials(grid);
+    MSC_HIPCK(hipMemcpyAsync((void*)ph, partials, sizeof(double) * grid, hipMemcpyDeviceToHost, st));
     sync();
     double m = 0.0;
-    for (int i = 0; i < grid; ++i) m = std::max(m, partials_h[i]);
+    for (int i = 0; i < grid; ++i) m = std::max(m, ph[i]);
     return m;
   }
 
-  double pop_sumsq(const T* p) {
-    double s = sumsq(p, (int64_t)Q * G.NS);
-    if (DV) s += sumsq(dev_moments(p, Q, G.NS), (int64_t)(D + 1) * G.NS);
-    return s;
-  }
-
-  template <class X>
-  double sumsq(const X* v, int64_t n) {
-    const int grid = 1024;
-    ensure_partials(grid);
-    hipLaunchKernelGGL((k_sumsq<X>), dim3(grid), dim3(256), 0, st, v, n, partials);
-    MSC_HIPCK(hipGetLastError());
-    MSC_HIPCK(hipMemcpyAsync(partials_h, partials, sizeof(double) * grid, hipMemcpyDeviceToHost, st));
+  // the first n partials' sum, in order
+  double sum_partials_host(int n) {
+    double* h = host_partials(n);
+    MSC_HIPCK(hipMemcpyAsync(h, partials, sizeof(double) * n, hipMemcpyDeviceToHost, st));
     sync();
     double s = 0.0;
-    for (int i = 0; i < grid; ++i) s += partials_h[i];
+    for (int i = 0; i < n; ++i) s += h[i];
     return s;
   }
 
   double reduce_partials(const SweepArgs<T, TM>& S) {
-    const int nb = sweep_grid();
-    MSC_HIPCK(hipMemcpyAsync(partials_h, S.partials, sizeof(double) * nb, hipMemcpyDeviceToHost, st));
-    sync();
-    double s = 0.0;
-    for (int i = 0; i < nb; ++i) s += partials_h[i];
-    return std::sqrt(s / ((double)Q * (double)G.NS));
+    (void)S;
+    return std::sqrt(sum_partials_host(sweep_grid()) / ((double)Q * (double)G.NS));
   }
 
   // ------------------------------------------------------ adjoint pieces --
@@ -1468,13 +1557,13 @@ class Solver : public SolverBase {
           using C2 = cpx<double>;
           if (D == 2) {
             adj_x.spec1 = (C2*)get(sizeof(C2) * 3 * (size_t)Spec2<double>::field(G.N0, G.N2 / 4 + 1));
-            adj_x.tw[0] = make_twiddles<double>(G.N0, &adj_allocs);
-            adj_x.tw[2] = make_twiddles<double>(G.N2, &adj_allocs);
+            adj_x.tw[0] = adj_twiddles(G.N0);
+            adj_x.tw[2] = adj_twiddles(G.N2);
           } else {
             const int NBz = G.n[2] / 4 + 1, NBy = 2 * (G.n[1] / 4) + 1;
             adj_x.spec1 = (C2*)get(sizeof(C2) * 4 * (size_t)Spec3<double>::field(G.n[0], G.n[1], NBz));
             adj_x.spec2 = (C2*)get(sizeof(C2) * 4 * (size_t)Spec3<double>::field(G.n[0], NBy, NBz));
-            for (int a = 0; a < 3; ++a) adj_x.tw[a] = make_twiddles<double>(G.n[a], &adj_allocs);
+            for (int a = 0; a < 3; ++a) adj_x.tw[a] = adj_twiddles(G.n[a]);
           }
         }
       }
