@@ -265,11 +265,10 @@ msc_status msc_set_state(msc_ctx* c, const double* state, int64_t bdf_count);
  * adjoint; it differentiates the discrete map, acceptance counts held fixed.
  *
  * msc_set_recording(c, 1) clears earlier records and makes every later
- * msc_bdf2_step keep, per accepted step, a device checkpoint of the state at
- * the step's start (the five arrays of msc_get_state in the storage
- * precision, m in FP64), its BDF count and its inner count K_n.  While
- * recording, msc_bdf2_step synchronises once per physical step.  A step that
- * fails is not recorded.  msc_set_recording(c, 0) stops and frees the
+ * msc_bdf2_step keep, per accepted step, a device checkpoint of what the
+ * step starts from (the populations of its trial in the storage precision,
+ * shared with the call's other records, and the history term h in FP64), its
+ * BDF count and its inner count K_n.  A step that fails is not recorded.  msc_set_recording(c, 0) stops and frees the
  * records; a new context does not record.  msc_recorded_steps returns their
  * number. */
 msc_status msc_set_recording(msc_ctx* c, int32_t enable);

@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstring>
 #include <initializer_list>
+#include <memory>
 #include <string>
 #include <type_traits>
 #include <vector>
@@ -149,6 +150,7 @@ class Solver : public SolverBase {
       ensure_stats(nsteps);
       const int stat_base = n_next;
       const int n_end = n_next + nsteps;
+      RecordScope recs(*this);  // drops the records of steps that were not accepted
       // schedule replay for these steps
       const bool use_sched = sched_pos < (int64_t)sched_h.size();
       if (use_sched) {
@@ -165,10 +167,7 @@ class Solver : public SolverBase {
       int64_t bdf_dev = bdf_count;
       msc_status rc = MSC_OK;
       while (n_dev < n_end) {
-        // while recording, one step per synchronisation so that the state at
-        // each step's start can be checkpointed
-        const int B = recording ? 1 : std::min(batch, n_end - n_dev);
-        if (recording && ell_dev == 1) take_checkpoint(n_dev, bdf_dev);
+        const int B = std::min(batch, n_end - n_dev);
         for (int i = 0; i < B; ++i) {
           const int n = n_dev + i;
           const int64_t bc = bdf_dev + i;
@@ -190,20 +189,24 @@ class Solver : public SolverBase {
           // within one call, each step's acceptance leaves m^{n+1} to the next
           // step's setup sweep (which reads the same populations anyway); the
           // call's last step reconstructs it so that the state is complete
-          // when the call returns, and recording keeps every step complete for
-          // its checkpoint
-          const bool recon = !recording && n > stat_base;
+          // when the call returns
+          const bool recon = n > stat_base;
           const double a_prev = (bc - 1 == 0) ? 1.0 / P.dt : 3.0 / (2.0 * P.dt);
-          const bool defer = !recording && n < n_end - 1;
+          const bool defer = n < n_end - 1;
+          CkptArgs<T>* rec = nullptr;
+          CkptArgs<T> ck;
+          if (recording && ell0 == 1) {
+            ck = checkpoint_args(n, bc, order, recs.base + (size_t)(n - stat_base), n_end - n);
+            rec = &ck;
+          }
           for (int ell = ell0; ell <= ell1; ++ell)
-            enqueue_iteration(n, ell, q, order, a, use_sched, stat_base, ell == ell1, recon, a_prev, defer);
+            enqueue_iteration(n, ell, q, order, a, use_sched, stat_base, ell == ell1, recon, a_prev, defer, rec);
         }
         fetch_ctl(nsteps);
         const uint64_t ph = ctl_h->phase;
         const int pn = phase_n(ph), pell = phase_ell(ph);
         const uint32_t ps = phase_state(ph);
         if (ps == PH_FAILED) {
-          if (recording && !records.empty() && records.back().K == 0) drop_last_record();
           bdf_dev += (pn - n_dev);
           rc = (ctl_h->fail_code == 5) ? MSC_ERR_NONCONVERGED : MSC_ERR_NONFINITE;
           last_error = std::string(rc == MSC_ERR_NONCONVERGED ? "nonconvergent" : "non-finite residual") +
@@ -213,6 +216,7 @@ class Solver : public SolverBase {
           ctl_h->fail_code = 0;
           MSC_HIPCK(hipMemcpyAsync(ctl, ctl_h, sizeof(DevCtl), hipMemcpyHostToDevice, st));
           copy_stats(out, stat_base, pn - stat_base + 1);
+          recs.accept(pn - stat_base);
           n_next = pn;
           bdf_count = bdf_dev;
           batch = 1;
@@ -221,7 +225,6 @@ class Solver : public SolverBase {
           return rc;
         }
         if (ps == PH_ACCEPTED) {
-          if (recording && !records.empty() && records.back().K == 0) records.back().K = pell;
           bdf_dev += (pn - n_dev + 1);
           n_dev = pn + 1;
           ell_dev = 1;
@@ -237,6 +240,7 @@ class Solver : public SolverBase {
         }
       }
       copy_stats(out, stat_base, nsteps);
+      recs.accept(nsteps);
       n_next = n_end;
       bdf_count = bdf_dev;
       if (use_sched) sched_pos += nsteps;
@@ -860,18 +864,23 @@ class Solver : public SolverBase {
       ensure_adjoint_buffers(kmax);
       if (on_device) after_default_stream();
       const int64_t SZ = state_size();
-      double* cur = adj_lam[0];
-      double* nxt = adj_lam[1];
-      MSC_HIPCK(hipMemcpyAsync(cur, lam, sizeof(double) * SZ,
-                               on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, st));
-      for (int r = 0; r < nsteps; ++r) {
-        backward_step(records[records.size() - 1 - r], cur, nxt);
-        std::swap(cur, nxt);
+      // device memory of the caller is read by the first step and written by
+      // the last, with the two buffers in between (a step's in and out differ)
+      const double* cur = lam;
+      if (!on_device) {
+        MSC_HIPCK(hipMemcpyAsync(adj_lam[1], lam, sizeof(double) * SZ, hipMemcpyHostToDevice, st));
+        cur = adj_lam[1];
       }
-      MSC_HIPCK(hipMemcpyAsync(lam, cur, sizeof(double) * SZ,
-                               on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, st));
+      for (int r = 0; r < nsteps; ++r) {
+        double* nxt = (on_device && r > 0 && r == nsteps - 1) ? lam : adj_lam[r & 1];
+        backward_step(records[records.size() - 1 - r], cur, nxt);
+        cur = nxt;
+      }
+      if (cur != lam)
+        MSC_HIPCK(hipMemcpyAsync(lam, cur, sizeof(double) * SZ,
+                                 on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, st));
       sync();
-      for (int r = 0; r < nsteps; ++r) drop_last_record();
+      records.resize(records.size() - nsteps);
       return MSC_OK;
     });
   }
@@ -1038,26 +1047,36 @@ class Solver : public SolverBase {
   int64_t t_count[2] = {0, 0};
 
   // adjoint records and buffers
+  // A recorded step.  Each keeps f^n and h; the older populations of its trial
+  // are f^n of the call's earlier records, and only a call's first records keep
+  // their own (other entry points may change the state between calls).
   struct Record {
-    void* mem;   // f^n, f^{n-1}, f^{n-2} (storage format), then m^n, m^{n-1} (FP64)
-    int64_t bc;  // BDF steps accepted before this step
-    int K;       // inner sweeps at acceptance; 0 while the step is in flight
-    float sig;   // deviation-storage scale of the checkpointed populations
+    std::shared_ptr<void> mem;  // the slab it lies in
+    const T* f[3];              // f^n, f^{n-1}, f^{n-2} (storage format), null beyond the order
+    const double* h;            // history term h_q
+    int64_t bc;                 // BDF steps accepted before this step
+    int K;                      // inner sweeps at acceptance; 0 while the step is in flight
+    float sig;                  // deviation-storage scale of the populations
   };
+  // slab of the records being made: its next free byte and its end
+  std::shared_ptr<void> slab;
+  char* slab_at = nullptr;
+  char* slab_end = nullptr;
   bool recording = false;
   std::vector<Record> records;
   std::vector<void*> adj_allocs;
   double* adj_lam[2] = {nullptr, nullptr};  // state-layout adjoints (in, out)
-  double* adj_LT = nullptr;
-  double* adj_LF = nullptr;
-  double* adj_carry = nullptr;
+  double* adj_L[2] = {nullptr, nullptr};    // LF of the transposed sweeps in turn
   double* adj_lh = nullptr;
-  double* adj_h = nullptr;
-  double* adj_fT = nullptr;
-  double* adj_it = nullptr;  // FP64 inner iterates f^(1..K) of the step being reversed
-  int adj_it_cap = 0;
+  // trial f^(1) and FP64 sweep outputs f_T of sweeps 1 .. K-1 of the step being
+  // reversed, and their corrections dm of sweeps 1 .. K-1 or (adj_rows) the
+  // solved band spectra of these, then of two transposed corrections
+  double* adj_it = nullptr;
+  double* adj_dm = nullptr;
+  cpx<double>* adj_spec = nullptr;
+  int adj_it_cap = 0, adj_dm_cap = 0, adj_spec_cap = 0;
   // FP64 transform buffers: P r of a recomputed sweep, or y = E^T Lambda, in
-  // adj_y; dm, or z = Sh^T y, out in adj_z
+  // adj_y; z = Sh^T y out in adj_z
   double* adj_y = nullptr;
   double* adj_z = nullptr;
   XformBufs<double, double> adj_x{};
@@ -1259,8 +1278,7 @@ class Solver : public SolverBase {
     ev_live.clear();
     ev_free.clear();
     if (st) (void)hipStreamSynchronize(st);
-    for (auto& r : records) dfree(r.mem);
-    records.clear();
+    clear_records();
     for (void* p : adj_allocs) dfree(p);
     adj_allocs.clear();
     for (void* p : allocs) dfree(p);
@@ -1340,11 +1358,12 @@ class Solver : public SolverBase {
 
   void copy_stats(msc_step_stats* out, int base, int count) {
     (void)base;
-    if (!out || count <= 0) return;
+    if ((!out && !recording) || count <= 0) return;
     if (stats_d == stats_long) {
       MSC_HIPCK(hipMemcpyAsync(stats_h, stats_d, sizeof(StepStat) * count, hipMemcpyDeviceToHost, st));
       sync();
     }
+    if (!out) return;
     for (int i = 0; i < count; ++i) {
       out[i].q = stats_h[i].q;
       out[i].iters = stats_h[i].iters;
@@ -1488,101 +1507,157 @@ class Solver : public SolverBase {
   }
 
   // ------------------------------------------------------ adjoint pieces --
-  size_t record_bytes() const { return 3 * pop_bytes() + 2 * sizeof(double) * (size_t)(D + 1) * G.NS; }
-
-  // Enqueue a copy of the state at the start of step n (ctl_h must be current).
-  void take_checkpoint(int n, int64_t bc) {
-    const Roles& ro = ctl_h->roles[n & 1];
-    Record r{};
-    r.mem = dalloc(record_bytes());
-    r.bc = bc;
-    r.K = 0;
-    r.sig = sig;
-    records.push_back(r);
+  // Arguments of the record of step n, the idx-th in the list, in a slab with
+  // room for it (allocated for up to 32 of the call's remaining steps).  A step
+  // enqueued again, because the march had not reached it, has its record.
+  CkptArgs<T> checkpoint_args(int n, int64_t bc, int order, size_t idx, int remaining) {
     const size_t fq = pop_bytes(), fm = sizeof(double) * (size_t)(D + 1) * G.NS;
-    char* b = (char*)r.mem;
+    const size_t first = rec_base;
+    const int back = (int)std::min<size_t>(idx - first, 2);  // earlier records of this call
+    const int own = std::max(order - back, 0);               // older populations it keeps itself
+    if (idx == records.size()) {
+      const size_t need = fm + (size_t)(1 + own) * fq;
+      if (!slab || slab_at + need > slab_end) {
+        // (a call's second record may keep an older population as well)
+        const size_t bytes = need + (size_t)(std::min(remaining, 32) - 1) * (fm + fq) + (idx == first ? fq : 0);
+        slab = std::shared_ptr<void>(dalloc(bytes), [this](void* p) { dfree(p); });
+        slab_at = (char*)slab.get();
+        slab_end = slab_at + bytes;
+      }
+      Record r{};
+      r.mem = slab;
+      auto take = [&](size_t bytes) {
+        char* p = slab_at;
+        slab_at += bytes;
+        return p;
+      };
+      for (int i = 0; i <= order; ++i) {
+        if (i == 0 || i > back)
+          r.f[i] = (const T*)take(fq);
+        else
+          r.f[i] = records[idx - 1].f[i - 1];
+      }
+      r.h = (const double*)take(fm);
+      r.bc = bc;
+      r.sig = sig;
+      records.push_back(std::move(r));
+    }
+    const Record& r = records[idx];
+    CkptArgs<T> A{};
+    A.ctl = ctl;
+    A.n = n;
+    A.fb = fb;
+    A.h = h_of(n);
     for (int i = 0; i < 3; ++i)
-      MSC_HIPCK(hipMemcpyAsync(b + i * fq, fb.p[ro.slot_hist[i]], fq, hipMemcpyDeviceToDevice, st));
-    for (int i = 0; i < 2; ++i)
-      MSC_HIPCK(hipMemcpyAsync(b + 3 * fq + i * fm, mb[ro.slot_m[i]], fm, hipMemcpyDeviceToDevice, st));
+      if (r.f[i] && (i == 0 || i > back)) A.rf[i] = (uint4*)r.f[i];
+    A.rh = (uint4*)r.h;
+    A.nf = (int64_t)(fq / sizeof(uint4));
+    A.nh = (int64_t)(fm / sizeof(uint4));
+    return A;
   }
 
-  void drop_last_record() {
-    sync();
-    dfree(records.back().mem);
-    records.pop_back();
-  }
+  // The records that one call makes: those of accepted steps stay.
+  size_t rec_base = 0;
+  struct RecordScope {
+    Solver& s;
+    const size_t base;
+    size_t kept = 0;
+    explicit RecordScope(Solver& s_) : s(s_), base(s_.records.size()) { s.rec_base = base; }
+    void accept(int n) {
+      if (!s.recording) return;
+      for (int i = 0; i < n; ++i) s.records[base + i].K = s.stats_h[i].iters;
+      kept = n;
+    }
+    ~RecordScope() {
+      if (s.records.size() > base + kept) {
+        (void)hipStreamSynchronize(s.st);  // work that writes them
+        s.records.resize(base + kept);
+      }
+      s.slab.reset();
+      s.slab_at = s.slab_end = nullptr;
+    }
+  };
 
   void clear_records() {
-    for (auto& r : records) dfree(r.mem);
     records.clear();
+    slab.reset();
   }
 
   void free_adjoint_buffers() {
     for (void* p : adj_allocs) dfree(p);
     adj_allocs.clear();
-    adj_lam[0] = adj_lam[1] = nullptr;
-    adj_LT = adj_LF = adj_carry = adj_lh = adj_h = nullptr;
-    adj_fT = adj_it = nullptr;
-    adj_it_cap = 0;
-    adj_y = adj_z = nullptr;
+    for (int i = 0; i < 2; ++i) adj_lam[i] = adj_L[i] = nullptr;
+    adj_lh = adj_it = adj_dm = adj_y = adj_z = nullptr;
+    adj_spec = nullptr;
+    adj_it_cap = adj_dm_cap = adj_spec_cap = 0;
     adj_x = XformBufs<double, double>{};
   }
 
+  // 2D: the transposed sweep with its row transforms (k_adj_rows), on the grids
+  // whose forward sweeps do theirs
+  bool adj_rows() const { return D == 2 && fuse_inv; }
+
   void ensure_adjoint_buffers(int K) {
     const int64_t NS = G.NS, FQ = (int64_t)Q * NS, FM = (int64_t)(D + 1) * NS;
+    using C2 = cpx<double>;
     auto get = [&](size_t bytes) {
       void* p = dalloc(bytes);
       adj_allocs.push_back(p);
       return p;
     };
-    if (!adj_LT) {
+    const bool shadow = P.corrector == MSC_CORRECTOR_SHADOW;
+    const size_t band = 3 * (size_t)Spec2<double>::field(G.N0, G.N2 / 4 + 1);
+    if (!adj_lh) {
       for (int i = 0; i < 2; ++i) adj_lam[i] = (double*)get(sizeof(double) * state_size());
-      adj_LT = (double*)get(sizeof(double) * FQ);
-      adj_LF = (double*)get(sizeof(double) * FQ);
-      adj_carry = (double*)get(sizeof(double) * FQ);
-      adj_lh = (double*)get(sizeof(double) * FM);
-      adj_h = (double*)get(sizeof(double) * FM);
-      adj_fT = (double*)get(sizeof(double) * FQ);
+      for (int i = 0; i < 2; ++i) adj_L[i] = (double*)get(sizeof(double) * FQ);
       adj_y = (double*)get(sizeof(double) * FM);
       adj_z = (double*)get(sizeof(double) * FM);
-      if (P.corrector == MSC_CORRECTOR_SHADOW) {
+      if (shadow) {
         adj_x.in = adj_y;
         adj_x.out = adj_z;
         if constexpr (std::is_same<CT, double>::value) {
           adj_x.spec1 = spec;
           adj_x.spec2 = spec2;
           for (int i = 0; i < 3; ++i) adj_x.tw[i] = tw[i];
+        } else if (D == 2) {
+          adj_x.spec1 = (C2*)get(sizeof(C2) * band);
+          adj_x.tw[0] = adj_twiddles(G.N0);
+          adj_x.tw[2] = adj_twiddles(G.N2);
         } else {
-          using C2 = cpx<double>;
-          if (D == 2) {
-            adj_x.spec1 = (C2*)get(sizeof(C2) * 3 * (size_t)Spec2<double>::field(G.N0, G.N2 / 4 + 1));
-            adj_x.tw[0] = adj_twiddles(G.N0);
-            adj_x.tw[2] = adj_twiddles(G.N2);
-          } else {
-            const int NBz = G.n[2] / 4 + 1, NBy = 2 * (G.n[1] / 4) + 1;
-            adj_x.spec1 = (C2*)get(sizeof(C2) * 4 * (size_t)Spec3<double>::field(G.n[0], G.n[1], NBz));
-            adj_x.spec2 = (C2*)get(sizeof(C2) * 4 * (size_t)Spec3<double>::field(G.n[0], NBy, NBz));
-            for (int a = 0; a < 3; ++a) adj_x.tw[a] = adj_twiddles(G.n[a]);
-          }
+          const int NBz = G.n[2] / 4 + 1, NBy = 2 * (G.n[1] / 4) + 1;
+          adj_x.spec1 = (C2*)get(sizeof(C2) * 4 * (size_t)Spec3<double>::field(G.n[0], G.n[1], NBz));
+          adj_x.spec2 = (C2*)get(sizeof(C2) * 4 * (size_t)Spec3<double>::field(G.n[0], NBy, NBz));
+          for (int a = 0; a < 3; ++a) adj_x.tw[a] = adj_twiddles(G.n[a]);
         }
       }
+      adj_lh = (double*)get(sizeof(double) * FM);
     }
     if (K > adj_it_cap) {
       adj_it = (double*)get(sizeof(double) * FQ * (size_t)K);
       adj_it_cap = K;
     }
+    if (shadow && adj_rows() && K > adj_spec_cap) {
+      adj_spec = (C2*)get(sizeof(C2) * band * (size_t)(K + 1));
+      adj_spec_cap = K;
+    }
+    if (shadow && !adj_rows() && K > adj_dm_cap) {
+      adj_dm = (double*)get(sizeof(double) * FM * (size_t)K);
+      adj_dm_cap = K;
+    }
   }
 
-  // FP64 dual-time sweep of src into dst (diagnostic mode, no control
-  // block) for the recompute of the adjoint: P r into adj_y.
-  void sweep64(const double* src, double* dst, double a) {
+  // FP64 dual-time sweep number ell of the step being reversed (diagnostic mode,
+  // no control block), from the iterate that it lifts to its output f_T; P r
+  // into adj_y, or its row spectrum into the correction's (adj_rows).
+  void sweep64(int ell, const double* src, double* dst, const double* h64, double a) {
+    const bool shadow = P.corrector == MSC_CORRECTOR_SHADOW, rows = shadow && adj_rows();
     SweepArgs<double, double> S{};
+    const int mode = (!shadow || ell == 1) ? SW_DTS : (rows ? SW_DTS_LIFT_ROWS : SW_DTS_LIFT);
     S.N0 = G.N0;
     S.N1 = G.N1;
     S.N2 = G.N2;
     S.L = strip_L;
-    const TileCfg tm = tile_of(SW_DTS);
+    const TileCfg tm = tile_of(mode);
     S.ntile1 = G.N1 / tm.T1;
     S.ntile2 = G.N2 / tm.T2;
     S.nstrip = G.N0 / strip_L;
@@ -1590,36 +1665,53 @@ class Solver : public SolverBase {
     S.ctl = nullptr;
     S.src = src;
     S.dst = dst;
-    S.h = adj_h;
-    S.dm = adj_z;
+    S.h = const_cast<double*>(h64);  // read in these modes
+    S.dm = (mode == SW_DTS_LIFT) ? adj_dm_of(ell - 1) : nullptr;
     S.Pr = adj_y;
     S.partials = partials;
     S.a = a;
     S.inv1pa2 = 1.0 / (1.0 + a / 2.0);
     S.wp = wp;
     S.wm = wm;
+    if (rows) {
+      S.fuse_rows = 1;
+      S.lgr = ilog2(G.N2);
+      S.NBr = G.N2 / 4 + 1;
+      S.spec = adj_spec_of(ell);
+      S.twr = adj_x.tw[2];
+      if (mode == SW_DTS_LIFT_ROWS) S.spec_in = adj_spec_of(ell - 1);
+    }
     if (D == 2)
-      launch_sweep_d2<double, double>(tile_id, SW_DTS, S, sweep_grid(), st);
-    else if (wide_mode(SW_DTS))
-      launch_sweep_dual_wide<double, double>(SW_DTS, S, sweep_grid(), st);
+      launch_sweep_d2<double, double>(tile_id, mode, S, sweep_grid(mode), st);
+    else if (wide_mode(mode))
+      launch_sweep_dual_wide<double, double>(mode, S, sweep_grid(mode), st);
     else
-      launch_sweep_d3<double, double>(tile_id, SW_DTS, S, sweep_grid(), st);
+      launch_sweep_d3<double, double>(tile_id, mode, S, sweep_grid(mode), st);
     MSC_HIPCK(hipGetLastError());
   }
 
-  // Reverse one recorded step: recompute its inner iterates from the
-  // checkpoint, then run the transposed stages from the last sweep to the
-  // first and through the history combination.  lin is the adjoint of the
-  // state after the step, lout receives the adjoint of the state before it.
+  // dm, or its solved band spectrum, of recomputed sweep ell = 1 .. K-1; spectra
+  // of the transposed corrections in the two after sweep adj_spec_cap - 1
+  double* adj_dm_of(int ell) const { return adj_dm + (size_t)(ell - 1) * (D + 1) * G.NS; }
+  cpx<double>* adj_spec_of(int ell) const {
+    return adj_spec + (size_t)(ell - 1) * 3 * Spec2<double>::field(G.N0, G.N2 / 4 + 1);
+  }
+  cpx<double>* adj_zspec_of(int ell) const { return adj_spec_of(adj_spec_cap + (ell & 1)); }
+
+  // Reverse one recorded step: recompute its inner iterates from the record,
+  // then run the transposed stages from the last sweep to the first and through
+  // the history combination.  lin is the adjoint of the state after the step,
+  // lout (another buffer) receives the adjoint of the state before it.
+  //
+  // A sweep and its correction take two launches each way on the grids of
+  // adj_rows (sweep with row transforms, column pass), else a sweep and the
+  // transform's passes.  N = 256, two inner iterations: 46 us of kernels in 6
+  // launches per step, from 100 us in 15 when lift, E^T, P^T and the history
+  // combination were launches of their own (each field written and read again
+  // between them) and the row transforms too.
   void backward_step(const Record& R, const double* lin, double* lout) {
     const int64_t NS = G.NS, FQ = (int64_t)Q * NS, FM = (int64_t)(D + 1) * NS;
-    const bool shadow = (P.corrector == MSC_CORRECTOR_SHADOW);
-    const size_t pb = pop_bytes();
-    const T* f0 = (const T*)R.mem;
-    const T* f1 = (const T*)((const char*)R.mem + pb);
-    const T* f2 = (const T*)((const char*)R.mem + 2 * pb);
-    const double* m0 = (const double*)((const char*)R.mem + 3 * pb);
-    const double* m1 = m0 + FM;
+    const bool shadow = (P.corrector == MSC_CORRECTOR_SHADOW), rows = shadow && adj_rows();
     const int q = (R.bc == 0) ? 1 : 2;
     const int max_order = (P.extrap_states == 0) ? 2 : P.extrap_states - 1;
     const int order = (int)std::min<int64_t>(R.bc, max_order);
@@ -1628,70 +1720,77 @@ class Solver : public SolverBase {
     auto it = [&](int ell) { return adj_it + (size_t)(ell - 1) * FQ; };
     const int eg = ew_grid();
 
-    // forward recompute of f^(1..K) in FP64
-    hipLaunchKernelGGL((k_extrap_h<L, T>), dim3(eg), dim3(256), 0, st, NS, order, q, P.dt, f0, f1, f2, m0, m1,
-                       R.sig, it(1), adj_h);
+    // forward recompute in FP64: it(1) the trial, it(ell + 1) = f_T of sweep ell
+    hipLaunchKernelGGL((k_adj_trial<L, T>), dim3(eg), dim3(256), 0, st, NS, order, R.f[0], R.f[1], R.f[2], R.sig,
+                       it(1));
     MSC_HIPCK(hipGetLastError());
+    XformBufs<double, double> B = adj_x;
     for (int ell = 1; ell < K; ++ell) {
-      sweep64(it(ell), shadow ? adj_fT : it(ell + 1), a);
-      if (shadow) {
-        enqueue_transform<double, double>(nullptr, 0, 0, a, nullptr, false, adj_x);
-        hipLaunchKernelGGL((k_lift<L, double, double>), dim3(eg), dim3(256), 0, st, (const double*)adj_fT,
-                           (const double*)adj_z, it(ell + 1), NS, 1.0f, 1.0f);
-        MSC_HIPCK(hipGetLastError());
-      }
+      sweep64(ell, it(ell), it(ell + 1), R.h, a);
+      if (!shadow) continue;
+      if (rows)
+        B.spec1 = adj_spec_of(ell);
+      else
+        B.out = adj_dm_of(ell);
+      enqueue_transform<double, double>(nullptr, 0, 0, a, nullptr, false, B, nullptr, rows, rows);
     }
 
     // backward through the inner iterations
-    const double* lf0 = lin;
-    const double* lf1 = lin + FQ;
-    const double* lf2 = lin + 2 * FQ;
-    const double* lm0 = lin + 3 * FQ;
-    const double* lm1 = lin + 3 * FQ + FM;
-    double* LT = adj_LT;
-    double* LF = adj_LF;
-    hipLaunchKernelGGL((k_adj_seed<L>), dim3(eg), dim3(256), 0, st, NS, lf0, lm0, a, LT, adj_lh);
-    MSC_HIPCK(hipGetLastError());
-    const AdjGeom ag{G.N0, G.N1, G.N2, NS};
-    const double* carry = nullptr;
-    for (int ell = K; ell >= 1; --ell) {
-      hipLaunchKernelGGL((k_adj_sweep<L, double>), dim3(eg), dim3(256), 0, st, ag, (const double*)it(ell),
-                         (const double*)adj_h, (const double*)LT, carry, LF, adj_lh, a, wp, wm);
-      MSC_HIPCK(hipGetLastError());
-      if (ell == 1) break;
-      if (shadow) {
-        hipLaunchKernelGGL((k_adj_Et<L, double>), dim3(eg), dim3(256), 0, st, NS, (const double*)LF, adj_y);
-        MSC_HIPCK(hipGetLastError());
-        enqueue_transform<double, double>(nullptr, 0, 0, a, nullptr, true, adj_x);
-        hipLaunchKernelGGL((k_adj_lift<L, double>), dim3(eg), dim3(256), 0, st, NS, (const double*)adj_z,
-                           (const double*)LF, LT, adj_carry);
-        MSC_HIPCK(hipGetLastError());
-        carry = adj_carry;
-      } else {
-        std::swap(LT, LF);
-        carry = nullptr;
-      }
-    }
-    // LF holds the adjoint of the trial f^(1)
-    AdjSetupArgs A{};
-    A.NS = NS;
-    A.Q = Q;
-    A.D1 = D + 1;
+    AdjArgs A{};
+    A.g = AdjGeom{G.N0, G.N1, G.N2, NS};
+    A.h = R.h;
+    A.Lt = lin;
+    A.zt = lin + 3 * FQ;
+    A.zscale = 1.0 / (1.0 + a / 2.0);
+    A.seed = 1;
+    A.y = shadow ? adj_y : nullptr;
+    A.lam_h = adj_lh;
+    A.a = a;
+    A.wp = wp;
+    A.wm = wm;
     A.order = order;
     A.q = q;
     A.dt = P.dt;
-    A.lf1n = lf1;
-    A.lf2n = lf2;
-    A.lm1n = lm1;
-    A.Lam1 = LF;
-    A.lam_h = adj_lh;
+    A.lf1n = lin + FQ;
+    A.lf2n = lin + 2 * FQ;
+    A.lm1n = lin + 3 * FQ + FM;
     A.of0 = lout;
     A.of1 = lout + FQ;
     A.of2 = lout + 2 * FQ;
     A.om0 = lout + 3 * FQ;
     A.om1 = lout + 3 * FQ + FM;
-    hipLaunchKernelGGL(k_adj_setup<0>, dim3(eg), dim3(256), 0, st, A);
-    MSC_HIPCK(hipGetLastError());
+    A.twy = adj_x.tw[2];
+    B = adj_x;
+    for (int ell = K; ell >= 1; --ell) {
+      A.fin = it(ell);
+      A.LF = adj_L[ell & 1];
+      A.last = (ell == 1) ? 1 : 0;
+      if (rows) {
+        A.dm_spec = (ell > 1) ? adj_spec_of(ell - 1) : nullptr;
+        A.y_spec = adj_zspec_of(ell);
+        if constexpr (D == 2)
+          with_lg<2, 8>(ilog2(G.N2), [&](auto lg) {
+            constexpr int T2 = 1 << lg.value;
+            hipLaunchKernelGGL((k_adj_rows<T2>), dim3(G.N0), dim3(adj_rows_threads(T2)), 0, st, A);
+          });
+      } else {
+        A.dm = (shadow && ell > 1) ? adj_dm_of(ell - 1) : nullptr;
+        hipLaunchKernelGGL((k_adj_sweep<L>), dim3(eg), dim3(256), 0, st, A);
+      }
+      MSC_HIPCK(hipGetLastError());
+      if (ell == 1) break;
+      A.Lt = A.LF;
+      A.zt = nullptr;
+      A.zscale = 1.0;
+      A.seed = 0;
+      if (!shadow) continue;
+      B.spec1 = rows ? adj_zspec_of(ell) : adj_x.spec1;
+      enqueue_transform<double, double>(nullptr, 0, 0, a, nullptr, true, B, nullptr, rows, rows);
+      if (rows)
+        A.z_spec = B.spec1;
+      else
+        A.zt = adj_z;
+    }
   }
 
   // ------------------------------------------------------ sweep config --
@@ -1921,7 +2020,8 @@ class Solver : public SolverBase {
   // a_prev, left it); defer: this step's acceptance leaves m^{n+1} to the
   // next step's setup sweep.
   void enqueue_iteration(int n, int ell, int q, int order, double a, bool use_sched, int stat_base,
-                         bool last = false, bool recon = false, double a_prev = 0.0, bool defer = false) {
+                         bool last = false, bool recon = false, double a_prev = 0.0, bool defer = false,
+                         const CkptArgs<T>* rec = nullptr) {
     SweepArgs<T, TM> S = sweep_args(a);
     S.ctl = ctl;
     S.h = h_of(n);
@@ -1972,6 +2072,10 @@ class Solver : public SolverBase {
       if (mode == SW_DTS_LIFT_ROWS) S.spec_in = spec_of(ell - 1);
     }
     launch_sweep_timed(mode, S, 0);
+    if (rec && ell == 1) {
+      hipLaunchKernelGGL((k_checkpoint<T>), dim3(ew_grid()), dim3(256), 0, st, *rec);
+      MSC_HIPCK(hipGetLastError());
+    }
     if (F.nparts > kFusedParts) {
       // many sweep blocks: fold the partials once instead of in every block
       hipLaunchKernelGGL(k_presum<0>, dim3(1), dim3(256), 0, st, (const double*)partials, F.nparts, presum);

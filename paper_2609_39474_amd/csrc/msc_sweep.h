@@ -641,8 +641,8 @@ __host__ __device__ constexpr int sweep_min_waves() {
 // complex line fbuf[0 .. T2), field 2 in the next), band j <= N_y/4 kept (Eq.
 // fft-convention, shadow-mask), into row xd of the band spectrum; by the
 // block's first T2 / 2 threads, after a barrier.
-template <int T2, class T, class TM, class CT>
-__device__ __forceinline__ void row_spectrum(const SweepArgs<T, TM>& A, cpx<CT>* fbuf, int tid, int xd,
+template <int T2, class CT>
+__device__ __forceinline__ void row_spectrum(cpx<CT>* __restrict__ spec, int N0, int NB, cpx<CT>* fbuf, int tid, int xd,
                                              const cpx<CT>* tw) {
 #pragma clang fp contract(on)
   using F = LineFft<CT, ilog2c(T2), 2>;
@@ -657,18 +657,17 @@ __device__ __forceinline__ void row_spectrum(const SweepArgs<T, TM>& A, cpx<CT>*
 #pragma unroll
   for (int i = 0; i < 4; ++i) ln[t + i * F::TPL] = v[i];
   wave_fence();
-  const int NB = A.NBr;
-  const int64_t FS = Spec2<CT>::field(A.N0, NB);
+  const int64_t FS = Spec2<CT>::field(N0, NB);
   auto store = [&](int j, cpx<CT> z) {
-    const int64_t o = Spec2<CT>::at(xd, j, A.N0);
+    const int64_t o = Spec2<CT>::at(xd, j, N0);
     if (line) {
-      A.spec[2 * FS + o] = z;
+      spec[2 * FS + o] = z;
       return;
     }
     // unpack: F0 = (Z(j) + conj Z(-j))/2, F1 = (Z(j) - conj Z(-j))/(2i)
     const cpx<CT> zc = ln[(T2 - j) & (T2 - 1)];
-    A.spec[o] = {(CT)0.5 * (z.x + zc.x), (CT)0.5 * (z.y - zc.y)};
-    A.spec[FS + o] = {(CT)0.5 * (z.y + zc.y), (CT)0.5 * (zc.x - z.x)};
+    spec[o] = {(CT)0.5 * (z.x + zc.x), (CT)0.5 * (z.y - zc.y)};
+    spec[FS + o] = {(CT)0.5 * (z.y + zc.y), (CT)0.5 * (zc.x - z.x)};
   };
   store(t, v[0]);
   if (t == 0) store(F::TPL, v[1]);
@@ -1003,7 +1002,7 @@ __global__ __launch_bounds__(NT, (sweep_min_waves<L, T, MODE, T1>())) void k_swe
           using F = LineFft<CT, ilog2c(T2), 2>;
           cpx<CT> tw[F::NTW];
           F::load_tw(A.twr, tid & (F::TPL - 1), tw);
-          row_spectrum<T2>(A, fbuf, tid, xd, tw);
+          row_spectrum<T2>(A.spec, N0, A.NBr, fbuf, tid, xd, tw);
           __syncthreads();  // fbuf is refilled by the next plane
         }
       }

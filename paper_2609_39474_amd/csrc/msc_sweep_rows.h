@@ -178,7 +178,7 @@ __global__ __launch_bounds__(3 * T2) void k_sweep_rows(SweepArgs<T, TM> A) {
       for (int i = 0; i < NRED; ++i) acc += red[i];
       A.partials[blockIdx.x] = acc;
     }
-    if (A.fuse_rows) row_spectrum<T2>(A, fbuf, tid, x0, tw);
+    if (A.fuse_rows) row_spectrum<T2>(A.spec, N0, A.NBr, fbuf, tid, x0, tw);
   }
 }
 
