@@ -249,6 +249,7 @@ constexpr int adj_rows_threads(int T2) { return T2 >= 32 ? 2 * T2 : 64; }
 
 template <int T2>
 __global__ __launch_bounds__(adj_rows_threads(T2)) void k_adj_rows(AdjArgs A) {
+  fetch_kernargs<sizeof(A)>();
   using L = D2Q9;
   constexpr int Q = L::Q, D = L::D, LG = ilog2c(T2);
   using F = LineFft<double, LG, 2>;

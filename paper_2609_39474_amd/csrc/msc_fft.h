@@ -195,6 +195,7 @@ struct ColsShape {
 template <class L, class T, class CT, class TM, int LG>
 __global__ __launch_bounds__((ColsShape<CT, LG>::NT)) void k_fft2_cols_solve(Fft2Args<CT, TM> A, AcceptArgs<L, T> Ac,
                                                                            FinishArgs Fin) {
+  fetch_kernargs<sizeof(A) + sizeof(Ac) + sizeof(Fin)>();
   using S = ColsShape<CT, LG>;
   using F = typename S::F;
   constexpr int N = F::N, E = F::E, TPL = F::TPL;
@@ -209,21 +210,13 @@ __global__ __launch_bounds__((ColsShape<CT, LG>::NT)) void k_fft2_cols_solve(Fft
   F::load_tw(A.twx, t, w);
 #pragma unroll
   for (int i = 0; i < E; ++i) v[i] = mine ? A.spec[f * FS + Spec2<CT>::at(t + i * TPL, jy, N)] : cpx<CT>{0, 0};
-  if (A.decide) {
-    // Algorithm 1 with the row pass fused into the sweep: decide here; if
-    // accepted, reconstruct m^{n+1} over the whole field instead
-    __shared__ double red[S::NT / 64];
-    const int dec = finish_block(Fin, red);
-    if (dec != DEC_RUNNING) {
-      if (dec == DEC_ACCEPTED)
-        accept_sites<L, T>(Ac, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, Ac.NS,
-                           (int64_t)gridDim.x * blockDim.x);
-      return;
-    }
-  } else if (A.g.skip()) {
+  // Algorithm 1 with the row pass fused into the sweep: the decision is taken
+  // here, behind the forward transform that its loads then overlap
+  FinishPre pre;
+  if (A.decide)
+    pre = finish_begin(Fin);
+  else if (A.g.skip())
     return;
-  }
-  if (jy >= NB) return;  // grid padding
   cpx<CT>* a = lds + (f < 3 ? f : 0) * N;
   cpx<CT>* b = F::WAVE ? a : a + S::LDS / 2;
   if (f < 3) F::template run<-1>(v, t, a, b, w);
@@ -237,7 +230,20 @@ __global__ __launch_bounds__((ColsShape<CT, LG>::NT)) void k_fft2_cols_solve(Fft
     for (int i = 0; i < E; ++i)
       if (in_band(signed_index(t + i * TPL, N), N)) s[t + i * TPL] = v[i];
   }
-  __syncthreads();
+  if (A.decide) {  // (its barrier serves the band too)
+    __shared__ double red[S::NT / 64];
+    const int dec = finish_end(Fin, pre, red);
+    if (dec != DEC_RUNNING) {
+      // if accepted, reconstruct m^{n+1} over the whole field instead
+      if (dec == DEC_ACCEPTED)
+        accept_sites<L, T>(Ac, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, Ac.NS,
+                           (int64_t)gridDim.x * blockDim.x);
+      return;
+    }
+  } else {
+    __syncthreads();
+  }
+  if (jy >= NB) return;  // grid padding
   const double two_pi = 6.283185307179586476925286766559;
   for (int q = threadIdx.x; q <= N / 2; q += S::NT) {
     const int jx = q <= N / 4 ? q : q + N / 2 - 1;

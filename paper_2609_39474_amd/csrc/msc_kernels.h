@@ -104,6 +104,7 @@ __device__ inline void accept_sites(const AcceptArgs<L, T>& A, int64_t s0, int64
 // the reconstruction.
 template <class L, class T>
 __global__ __launch_bounds__(256) void k_accept(AcceptArgs<L, T> A, FinishArgs F) {
+  fetch_kernargs<sizeof(A) + sizeof(F)>();
   __shared__ double red[256];
   if (finish_block(F, red) != DEC_ACCEPTED) return;
   accept_sites<L, T>(A, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, A.NS, (int64_t)gridDim.x * blockDim.x);

@@ -99,10 +99,10 @@ enum { DEC_SKIP = -1, DEC_RUNNING = 0, DEC_ACCEPTED = 1, DEC_FAILED = 2 };
 // ell >= n_min and the residual is finite and below eps (or at the scheduled
 // count in replay mode); a non-finite residual fails the step (Sec. 4.1);
 // reaching K_max fails it as nonconvergent.
-__device__ inline int accept_decision(const FinishArgs& A, double R, int* fail_out) {
+__device__ inline int accept_decision(const FinishArgs& A, double R, int sched, int* fail_out) {
   const int ell = A.ell;
   const bool fin = isfinite(R);
-  const bool pass = A.sched ? (ell == A.sched[A.n - A.stat_base]) : (ell >= A.nmin && fin && R < A.eps);
+  const bool pass = A.sched ? (ell == sched) : (ell >= A.nmin && fin && R < A.eps);
   int fail = 0;
   if (!pass) {
     if (!fin)
@@ -118,8 +118,8 @@ __device__ inline int accept_decision(const FinishArgs& A, double R, int* fail_o
 // rho-observed), on acceptance the rotated roles of step n + 1 (Sec. 3.1,
 // last paragraph: the histories shift; the moment slot that becomes m^{n+1}
 // is the spare, filled by the reconstruction of the same kernel), and the
-// phase word.
-__device__ inline void finish_commit(const FinishArgs& A, double R, int dec, int fail) {
+// phase word.  R0 and o are Rhist[0] and step n's roles as loaded before.
+__device__ inline void finish_commit(const FinishArgs& A, double R, int dec, int fail, double R0, const Roles& o) {
   const int ell = A.ell;
   A.Rhist[ell - 1] = R;
   DevCtl* c = A.ctl;
@@ -127,7 +127,7 @@ __device__ inline void finish_commit(const FinishArgs& A, double R, int dec, int
     StepStat& st = A.stats[A.n - A.stat_base];
     st.q = A.q;
     st.iters = ell;
-    st.R_first = A.Rhist[0];
+    st.R_first = ell == 1 ? R : R0;
     st.R_final = R;
     double rho = __builtin_nan("");
     if (ell >= 3) {
@@ -142,13 +142,15 @@ __device__ inline void finish_commit(const FinishArgs& A, double R, int dec, int
     st.fail = fail;
   }
   if (dec == DEC_ACCEPTED) {
-    const Roles& o = c->roles[A.n & 1];
+    // (written entry by entry, as constants index: the loaded copy stays in
+    // registers)
     Roles& r = c->roles[(A.n + 1) & 1];
-    r.slot_hist[0] = o.slot_w[ell & 1];
+    const bool odd = ell & 1;
+    r.slot_hist[0] = odd ? o.slot_w[1] : o.slot_w[0];
     r.slot_hist[1] = o.slot_hist[0];
     r.slot_hist[2] = o.slot_hist[1];
-    r.slot_w[ell & 1] = o.slot_hist[2];
-    r.slot_w[(ell + 1) & 1] = o.slot_w[(ell + 1) & 1];
+    r.slot_w[0] = odd ? o.slot_w[0] : o.slot_hist[2];
+    r.slot_w[1] = odd ? o.slot_hist[2] : o.slot_w[1];
     r.slot_m[0] = o.slot_m[2];  // becomes m^{n+1}
     r.slot_m[1] = o.slot_m[0];
     r.slot_m[2] = o.slot_m[1];
@@ -161,33 +163,64 @@ __device__ inline void finish_commit(const FinishArgs& A, double R, int dec, int
   }
 }
 
+// Everything that the decision for (step n, sweep ell) reads, in flight at once
+// and, in a kernel that has other loads and work first, behind those: one after
+// the other (phase, partials, schedule, history, roles) each load was a wait of
+// its own (k_accept at N = 256, 256 partials: 3.1 -> 2.4 us).
+struct FinishPre {
+  uint64_t ph;
+  double acc, R0;
+  int sched;
+  Roles ro;
+};
+
+__device__ __forceinline__ FinishPre finish_begin(const FinishArgs& A) {
+  FinishPre p;
+  // (a zero in a vector register: a load at a uniform address would be made
+  // scalar at once, with a wait before the next)
+  int z;
+  asm("v_mov_b32 %0, 0" : "=v"(z));
+  const int i0 = threadIdx.x;
+  p.ph = (&A.ctl->phase)[z];
+  p.acc = 0.0;
+  if (i0 < A.nparts) p.acc = A.partials[i0];
+  p.sched = 0;
+  if (A.sched) p.sched = A.sched[A.n - A.stat_base + z];
+  p.R0 = 0.0;
+  if (blockIdx.x == 0) {  // the block that records the decision
+    p.R0 = A.Rhist[z];
+    p.ro = A.ctl->roles[(A.n & 1) + z];
+  }
+  for (int i = i0 + blockDim.x; i < A.nparts; i += blockDim.x) p.acc += A.partials[i];
+  return p;
+}
+
 // Block-uniform decision for (step n, sweep ell), or DEC_SKIP when the march
 // is not right after that sweep.  The phase word is either still the one the
-// sweep saw or already block 0's record of this very decision.  Uses red[] (one entry per wavefront).
-__device__ inline int finish_block(const FinishArgs& A, double* red) {
-  __shared__ int sh_mine;
-  if (threadIdx.x == 0) {
-    const uint64_t ph = A.ctl->phase;
-    const bool after = phase_n(ph) == A.n && phase_ell(ph) == A.ell && phase_state(ph) != 0;
-    sh_mine = (phase_ready(ph, A.n, A.ell) || after) ? 1 : 0;
-  }
-  __syncthreads();
-  if (!sh_mine) return DEC_SKIP;
+// sweep saw or already block 0's record of this very decision, so every thread
+// of the grid finds the same.  Uses red[] (one entry per wavefront).
+__device__ __forceinline__ int finish_end(const FinishArgs& A, const FinishPre& p, double* red) {
   // fixed-order fold: strided per thread, then within each wavefront by
   // shuffles, then across the (blockDim / 64) wavefronts in order
-  double acc = 0.0;
-  for (int i = threadIdx.x; i < A.nparts; i += blockDim.x) acc += A.partials[i];
+  double acc = p.acc;
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
   __syncthreads();
+  const bool after = phase_n(p.ph) == A.n && phase_ell(p.ph) == A.ell && phase_state(p.ph) != 0;
+  if (!__builtin_amdgcn_readfirstlane(phase_ready(p.ph, A.n, A.ell) || after)) return DEC_SKIP;
   double tot = 0.0;
   for (int wv = 0; wv < (int)(blockDim.x >> 6); ++wv) tot += red[wv];
   const double R = sqrt(tot * A.inv_count);
   int fail = 0;
-  const int dec = accept_decision(A, R, &fail);
-  if (blockIdx.x == 0 && threadIdx.x == 0) finish_commit(A, R, dec, fail);
-  return dec;
+  const int dec = accept_decision(A, R, p.sched, &fail);
+  if (blockIdx.x == 0 && threadIdx.x == 0) finish_commit(A, R, dec, fail, p.R0, p.ro);
+  return __builtin_amdgcn_readfirstlane(dec);
+}
+
+__device__ __forceinline__ int finish_block(const FinishArgs& A, double* red) {
+  const FinishPre p = finish_begin(A);
+  return finish_end(A, p, red);
 }
 
 template <class T, class TM>
@@ -313,20 +346,25 @@ struct SrcPtrs {
 // false when the march is not at that point.
 template <int MODE, class T, class TM>
 __device__ __forceinline__ bool sweep_sources(const SweepArgs<T, TM>& A, SrcPtrs<T>& P, T* __restrict__& dst) {
+  // the roles are read with the phase word, not after the test on it
   const uint64_t ph = A.ctl->phase;
-  if (!phase_ready(ph, A.n, A.ell)) return false;
   const Roles& ro = A.ctl->roles[A.n & 1];
+  const int h0 = ro.slot_hist[0], h1 = ro.slot_hist[1], h2 = ro.slot_hist[2];
+  const int w0 = ro.slot_w[0], w1 = ro.slot_w[1], m0 = ro.slot_m[0], m1 = ro.slot_m[1];
+  asm volatile("" ::"s"(h0), "s"(h1), "s"(h2), "s"(w0), "s"(w1), "s"(m0), "s"(m1));
+  if (!phase_ready(ph, A.n, A.ell)) return false;
+  const int wo = (A.ell & 1) ? w1 : w0, wi = (A.ell & 1) ? w0 : w1;
   if (setup_mode(MODE)) {
-    P.s0 = A.fb.p[ro.slot_hist[0]];
-    P.s1 = A.fb.p[ro.slot_hist[1]];
-    P.s2 = A.fb.p[ro.slot_hist[2]];
-    P.mc = A.recon ? A.h_prev : A.mb[ro.slot_m[0]];
-    P.mp = A.mb[ro.slot_m[1]];
-    P.mw = A.mb[ro.slot_m[0]];
+    P.s0 = A.fb.p[h0];
+    P.s1 = A.fb.p[h1];
+    P.s2 = A.fb.p[h2];
+    P.mw = A.mb[m0];
+    P.mc = A.recon ? A.h_prev : P.mw;
+    P.mp = A.mb[m1];
   } else {
-    P.s0 = A.fb.p[ro.slot_w[(A.ell - 1) & 1]];
+    P.s0 = A.fb.p[wi];
   }
-  dst = A.fb.p[ro.slot_w[A.ell & 1]];
+  dst = A.fb.p[wo];
   return true;
 }
 

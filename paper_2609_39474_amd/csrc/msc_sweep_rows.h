@@ -21,6 +21,7 @@ namespace msc {
 
 template <class T, class TM, int T2, int MODE>
 __global__ __launch_bounds__(3 * T2) void k_sweep_rows(SweepArgs<T, TM> A) {
+  fetch_kernargs<sizeof(A)>();
   using L = D2Q9;
   using CT = typename CompT<T>::type;
   using LT = typename std::conditional<PopDev<T>::value, float, T>::type;
