@@ -18,9 +18,13 @@
 // of the in-place march.
 //
 // Measured per step against the single-step launches: N = 256 FP64 3.19 ->
-// 1.32 us (8 steps per launch), N = 2048 FP64 100 -> 45 us and FP32 44 -> 28 us
-// (4 steps).  Bound by the FP64 instructions of the collisions, 1.5-2.5 times
-// the useful ones with the halo's.
+// 1.26 us (8 steps per launch), N = 2048 FP64 100 -> 45 us and FP32 44 -> 28 us
+// (4 steps).  On large grids bound by the FP64 instructions of the collisions,
+// 1.5-2.5 times the useful ones with the halo's; at N = 256 (one block per
+// compute unit) by a step's chain of barrier, LDS reads (0.3 us of LDS traffic)
+// and dependent sums.  At the operating point the kernel is an instantiation
+// of its own without the population terms (POINT, 97 -> 62 instructions per
+// site): 1.26 -> 1.17 us.
 #pragma once
 
 #include "msc_aa.h"
@@ -36,7 +40,7 @@ struct March2Args {
   double wp, wm;
 };
 
-template <class T>
+template <class T, bool POINT>
 __device__ __forceinline__ void march2_collide(const March2Args<T>& A,
                                                const RawSite<D2Q9, T, typename CompT<T>::type, SW_EXPLICIT>& r,
                                                typename CompT<T>::type* C) {
@@ -46,12 +50,12 @@ __device__ __forceinline__ void march2_collide(const March2Args<T>& A,
   S.wm = A.wm;
   CT f[9];
   double hs[4];
-  collide_raw<D2Q9, T, CT, SW_EXPLICIT>(S, r, f, C, hs);
+  collide_raw<D2Q9, T, CT, SW_EXPLICIT, POINT>(S, r, f, C, hs);
 }
 
 // odd step number E (counted from 0, so S - 1 is the last) and, unless it is
 // the last, the even step after it
-template <class T, int BX, int BY, int S, int NT, int E>
+template <class T, bool POINT, int BX, int BY, int S, int NT, int E>
 __device__ __forceinline__ void march2_pair(const March2Args<T>& A, T (*f)[(BX + 2 * S) * (BY + 2 * S)], int x0,
                                             int y0) {
   using L = D2Q9;
@@ -67,7 +71,7 @@ __device__ __forceinline__ void march2_pair(const March2Args<T>& A, T (*f)[(BX +
 #pragma unroll
       for (int k = 0; k < 9; ++k) r.f0[k] = f[L::opp(k)][c - L::cx(k) * RY - L::cy(k)];
       CT C[9];
-      march2_collide<T>(A, r, C);
+      march2_collide<T, POINT>(A, r, C);
 #pragma unroll
       for (int k = 0; k < 9; ++k) {
         if constexpr (E < S - 1) {
@@ -90,15 +94,15 @@ __device__ __forceinline__ void march2_pair(const March2Args<T>& A, T (*f)[(BX +
 #pragma unroll
       for (int k = 0; k < 9; ++k) r.f0[k] = f[k][c];
       CT C[9];
-      march2_collide<T>(A, r, C);
+      march2_collide<T, POINT>(A, r, C);
 #pragma unroll
       for (int k = 0; k < 9; ++k) f[L::opp(k)][c] = (T)C[k];
     }
-    march2_pair<T, BX, BY, S, NT, E + 2>(A, f, x0, y0);
+    march2_pair<T, POINT, BX, BY, S, NT, E + 2>(A, f, x0, y0);
   }
 }
 
-template <class T, int BX, int BY, int S, int NT>
+template <class T, bool POINT, int BX, int BY, int S, int NT>
 __global__ __launch_bounds__(NT) void k_march2(March2Args<T> A) {
   static_assert(S % 2 == 0, "pairs of steps");
   using L = D2Q9;
@@ -115,11 +119,11 @@ __global__ __launch_bounds__(NT) void k_march2(March2Args<T> A) {
 #pragma unroll
     for (int k = 0; k < 9; ++k) r.f0[k] = A.in[k * NS + s];
     CT C[9];
-    march2_collide<T>(A, r, C);
+    march2_collide<T, POINT>(A, r, C);
 #pragma unroll
     for (int k = 0; k < 9; ++k) f[L::opp(k)][i] = (T)C[k];
   }
-  march2_pair<T, BX, BY, S, NT, 1>(A, f, x0, y0);
+  march2_pair<T, POINT, BX, BY, S, NT, 1>(A, f, x0, y0);
 }
 
 }  // namespace msc

@@ -346,7 +346,11 @@ class Solver : public SolverBase {
   template <int BX, int BY, int SM, int NT>
   void launch_march2_tile(March2Args<T>& A) {
     A.lgty = ilog2(G.N2 / BY);
-    hipLaunchKernelGGL((k_march2<T, BX, BY, SM, NT>), dim3((G.N0 / BX) * (G.N2 / BY)), dim3(NT), 0, st, A);
+    const dim3 grid((G.N0 / BX) * (G.N2 / BY));
+    if (A.wp == 1.0 && A.wm == 1.0)
+      hipLaunchKernelGGL((k_march2<T, true, BX, BY, SM, NT>), grid, dim3(NT), 0, st, A);
+    else
+      hipLaunchKernelGGL((k_march2<T, false, BX, BY, SM, NT>), grid, dim3(NT), 0, st, A);
     MSC_HIPCK(hipGetLastError());
   }
 

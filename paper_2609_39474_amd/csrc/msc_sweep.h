@@ -438,7 +438,11 @@ __device__ __forceinline__ void load_raw(const SweepArgs<T, TM>& A, const SrcPtr
 // macro-reconstruct), form the source (Eq. source-moments) and collide (Eq.
 // collision with Eq. feq and Eq. source-distribution).  hout receives h_q
 // (setup mode).
-template <class L, class T, class TM, int MODE>
+//
+// At the operating point omega+ = omega- = 1 (POINT) the populations leave the
+// explicit update, f' = feq: the same finite values, bit for bit, with half the
+// operations (its sums start at their first term as well).
+template <class L, class T, class TM, int MODE, bool POINT = false>
 __device__ __forceinline__ void collide_raw(const SweepArgs<T, TM>& A, const RawSite<L, T, TM, MODE>& r,
                                             typename CompT<T>::type* f, typename CompT<T>::type* C,
                                             double* hout, double* Mtrial = nullptr, double* mnout = nullptr) {
@@ -570,12 +574,23 @@ __device__ __forceinline__ void collide_raw(const SweepArgs<T, TM>& A, const Raw
       if constexpr (lift_mode(MODE)) M[b] += (KT)r.dmv[b];
     }
   } else {
+    bool begun[4] = {};
 #pragma unroll
     for (int k = 0; k < Q; ++k) {
-      M[0] += (KT)f[k];
+      if (POINT && !begun[0])
+        M[0] = (KT)f[k];
+      else
+        M[0] += (KT)f[k];
+      begun[0] = true;
 #pragma unroll
-      for (int b = 0; b < D; ++b)
-        if (ca<L>(k, b) != 0) M[1 + b] += (KT)ca<L>(k, b) * (KT)f[k];
+      for (int b = 0; b < D; ++b) {
+        if (ca<L>(k, b) == 0) continue;
+        if (POINT && !begun[1 + b])
+          M[1 + b] = (KT)ca<L>(k, b) * (KT)f[k];
+        else
+          M[1 + b] += (KT)ca<L>(k, b) * (KT)f[k];
+        begun[1 + b] = true;
+      }
     }
   }
   if constexpr (DV) {
@@ -626,15 +641,20 @@ __device__ __forceinline__ void collide_raw(const SweepArgs<T, TM>& A, const Raw
     const KT fk = (KT)f[k];
     if (kb == k) {
       // rest direction: only even parts
-      KT ck = gp * fk + wp * (wk * Be);
+      KT ck = POINT ? wk * Be : gp * fk + wp * (wk * Be);
       if (MODE != SW_EXPLICIT) ck += hp * (wk * Ae);
       C[k] = (CT)ck;
       continue;
     }
+    static_assert(!POINT || MODE == SW_EXPLICIT, "the source-free update");
     KT cu = 0, cs = 0;
+    bool first = true;
 #pragma unroll
     for (int b = 0; b < D; ++b) {
-      if (ca<L>(k, b) > 0) {
+      if (POINT && first && ca<L>(k, b) != 0) {
+        cu = ca<L>(k, b) > 0 ? m[1 + b] : -m[1 + b];
+        first = false;
+      } else if (ca<L>(k, b) > 0) {
         cu += m[1 + b];
         if (MODE != SW_EXPLICIT) cs += s[1 + b];
       } else if (ca<L>(k, b) < 0) {
@@ -645,8 +665,8 @@ __device__ __forceinline__ void collide_raw(const SweepArgs<T, TM>& A, const Raw
     const KT fkb = (KT)f[kb];
     const KT fp = (KT)0.5 * (fk + fkb), fm = (KT)0.5 * (fk - fkb);
     const KT ep = wk * (Be + (KT)4.5 * cu * cu), em = (KT)3 * wk * cu;
-    KT ev = gp * fp + wp * ep;
-    KT od = gm * fm + wm * em;
+    KT ev = POINT ? ep : gp * fp + wp * ep;
+    KT od = POINT ? em : gm * fm + wm * em;
     if (MODE != SW_EXPLICIT) {
       ev += hp * (wk * (Ae + (KT)9 * cu * cs));
       od += hm * ((KT)3 * wk * cs);

@@ -33,3 +33,25 @@ def test_steps_per_launch_bit_exact(M, orc, shape, storage):
         fa = _march(M, shape, storage, f0, steps, True, graph)
         fb = _march(M, shape, storage, f0, steps, False, graph)
         np.testing.assert_array_equal(fa, fb)
+
+
+@pytest.mark.parametrize("storage", ["fp64", "fp32"])
+@pytest.mark.parametrize("taus", [(1.0, 1.0), (1.0, 0.8), (0.7, 1.0)])
+@pytest.mark.parametrize("shape", [(16, 16), (256, 256), (512, 512)])
+def test_operating_point_update_bit_exact(M, orc, shape, taus, storage):
+    """The update without populations (both rates 1) and the general one, per
+    tile, against the single-step kernels."""
+    from test_gpu_aa import KEY_EXPLICIT_AA
+
+    f0 = _rand_f(orc, shape, 22)
+    out = []
+    for aa in (1, 0):
+        p = M.make_params(2, shape[0], dt=64.0, eps=1e-6, storage=storage, tau_plus=taus[0], tau_minus=taus[1])
+        p.n[0], p.n[1] = shape
+        s = M.Solver(p, np.zeros(shape), np.zeros((2,) + shape))
+        s.set_tuning(KEY_EXPLICIT_AA, aa)
+        s.set_populations(f0)
+        s.explicit_step(18)
+        out.append(s.populations())
+        s.close()
+    np.testing.assert_array_equal(out[0], out[1])
