@@ -151,6 +151,7 @@ class Solver : public SolverBase {
       const int stat_base = n_next;
       const int n_end = n_next + nsteps;
       RecordScope recs(*this);  // drops the records of steps that were not accepted
+      handed_on.ctl = nullptr;
       // schedule replay for these steps
       const bool use_sched = sched_pos < (int64_t)sched_h.size();
       if (use_sched) {
@@ -199,8 +200,12 @@ class Solver : public SolverBase {
             ck = checkpoint_args(n, bc, order, recs.base + (size_t)(n - stat_base), n_end - n);
             rec = &ck;
           }
+          // the decision on this step's last sweep goes with the next step's
+          // first sweep where that one follows at once and can take it
+          const bool hand_on = i < B - 1 && merge_ok();
           for (int ell = ell0; ell <= ell1; ++ell)
-            enqueue_iteration(n, ell, q, order, a, use_sched, stat_base, ell == ell1, recon, a_prev, defer, rec);
+            enqueue_iteration(n, ell, q, order, a, use_sched, stat_base, ell == ell1, recon, a_prev, defer, rec,
+                              hand_on);
         }
         fetch_ctl(nsteps);
         const uint64_t ph = ctl_h->phase;
@@ -1206,7 +1211,7 @@ class Solver : public SolverBase {
     want(presum, sizeof(double));
     choose_sweep();
     nparts_cap = std::max(sweep_grid_max(), 1024);
-    want(partials, sizeof(double) * nparts_cap);
+    want(partials, 2 * sizeof(double) * nparts_cap);
     const bool fs = (fullsym() || wallkin()) && fs_supported();
     bool axis[3] = {false, false, false};
     if (corrector_supported()) {
@@ -1314,7 +1319,7 @@ class Solver : public SolverBase {
 
   void ensure_partials(int n) {
     if (n <= nparts_cap) return;
-    partials = keep((double*)dalloc(sizeof(double) * n));
+    partials = keep((double*)dalloc(2 * sizeof(double) * n));
     nparts_cap = n;
   }
 
@@ -2025,7 +2030,7 @@ class Solver : public SolverBase {
   // next step's setup sweep.
   void enqueue_iteration(int n, int ell, int q, int order, double a, bool use_sched, int stat_base,
                          bool last = false, bool recon = false, double a_prev = 0.0, bool defer = false,
-                         const CkptArgs<T>* rec = nullptr) {
+                         const CkptArgs<T>* rec = nullptr, bool hand_on = false) {
     SweepArgs<T, TM> S = sweep_args(a);
     S.ctl = ctl;
     S.h = h_of(n);
@@ -2055,7 +2060,7 @@ class Solver : public SolverBase {
     F.Rhist = Rhist;
     F.stats = stats_d;
     F.stat_base = stat_base;
-    F.partials = partials;
+    F.partials = S.partials = parts_of(n);
     int mode;
     if (ell == 1)
       mode = SW_DTS_SETUP;
@@ -2075,10 +2080,19 @@ class Solver : public SolverBase {
       S.twr = tw[2];
       if (mode == SW_DTS_LIFT_ROWS) S.spec_in = spec_of(ell - 1);
     }
+    if (ell == 1 && handed_on.n == n - 1 && handed_on.ctl) {
+      S.merge = 1;
+      S.fin = handed_on;
+    }
+    handed_on.ctl = nullptr;
     launch_sweep_timed(mode, S, 0);
     if (rec && ell == 1) {
       hipLaunchKernelGGL((k_checkpoint<T>), dim3(ew_grid()), dim3(256), 0, st, *rec);
       MSC_HIPCK(hipGetLastError());
+    }
+    if (last && hand_on) {
+      handed_on = F;
+      return;
     }
     if (F.nparts > kFusedParts) {
       // many sweep blocks: fold the partials once instead of in every block
@@ -2124,6 +2138,16 @@ class Solver : public SolverBase {
     }
     enqueue_transform<CT, TM>(ctl, n, ell, a, nullptr, false, B, nullptr, fuse_rows, fuse_inv);
   }
+
+  // The decision left to the next enqueued sweep (ctl null: none).
+  FinishArgs handed_on{};
+  bool merge_ok() const {
+    return D == 2 && tile.T1 == 1 && tile.T2 == G.N2 && tile.T2 >= 64 && strip_setup == 1 && !fullsym() && !wallkin();
+  }
+
+  // partial sums of r^2 of step n's sweeps: a step's first sweep writes its own
+  // while its other blocks still fold those of the step before
+  double* parts_of(int n) const { return partials + (n & 1) * (size_t)nparts_cap; }
 
   // band spectrum of the correction after sweep ell (alternating buffers
   // when the sweep inverts the previous correction's rows while writing its

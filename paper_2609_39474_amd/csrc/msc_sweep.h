@@ -269,6 +269,10 @@ struct SweepArgs {
   // SW_DTS_LIFT_ROWS: the solved band spectrum of the previous correction
   // (Spec2 layout), inverted along y by the sweep to give dm
   const cpx<TM>* spec_in;
+  // setup mode of k_sweep_rows, merge = 1: the sweep also takes the decision on
+  // the previous step's last enqueued sweep (see merged_sources)
+  int merge;
+  FinishArgs fin;
   // D2Q9 lid-driven cavity: wall rows after streaming (every mode)
   int walls;
   double ulid;
@@ -365,6 +369,40 @@ __device__ __forceinline__ bool sweep_sources(const SweepArgs<T, TM>& A, SrcPtrs
     P.s0 = A.fb.p[wi];
   }
   dst = A.fb.p[wo];
+  return true;
+}
+
+// The first sweep of step n with the decision on (n - 1, e), e = A.fin.ell, the
+// sweep enqueued last for its step, taken in the same launch: the sources as
+// they are if that sweep is accepted (rotated here, as finish_commit records
+// them), so that the loads do not wait for the decision.  pending: the decision
+// is this launch's (block 0 may have recorded it already) and has to be
+// awaited before anything is written; otherwise step n - 1 was accepted at an
+// earlier sweep.  false when the march is not at either point.
+template <class T, class TM>
+__device__ __forceinline__ bool merged_sources(const SweepArgs<T, TM>& A, SrcPtrs<T>& P, T* __restrict__& dst,
+                                               bool& pending) {
+  const uint64_t ph = A.ctl->phase;
+  const int e = A.fin.ell, n0 = A.n - 1;
+  const Roles& o = A.ctl->roles[n0 & 1];
+  const Roles& r = A.ctl->roles[A.n & 1];
+  const int oh0 = o.slot_hist[0], oh1 = o.slot_hist[1], oh2 = o.slot_hist[2], ow0 = o.slot_w[0], ow1 = o.slot_w[1],
+            om0 = o.slot_m[0], om2 = o.slot_m[2];
+  const int rh0 = r.slot_hist[0], rh1 = r.slot_hist[1], rh2 = r.slot_hist[2], rw1 = r.slot_w[1], rm0 = r.slot_m[0],
+            rm1 = r.slot_m[1];
+  asm volatile("" ::"s"(oh0), "s"(oh1), "s"(oh2), "s"(ow0), "s"(ow1), "s"(om0), "s"(om2), "s"(rh0), "s"(rh1),
+               "s"(rh2), "s"(rw1), "s"(rm0), "s"(rm1));
+  const bool recorded = phase_n(ph) == n0 && phase_ell(ph) == e && phase_state(ph) != 0;
+  pending = phase_ready(ph, n0, e) || recorded;
+  if (!pending && !phase_ready(ph, A.n, 1)) return false;
+  const int last = (e & 1) ? ow1 : ow0;  // its output: f^n if accepted
+  P.s0 = A.fb.p[pending ? last : rh0];
+  P.s1 = A.fb.p[pending ? oh0 : rh1];
+  P.s2 = A.fb.p[pending ? oh1 : rh2];
+  P.mw = A.mb[pending ? om2 : rm0];
+  P.mc = A.recon ? A.h_prev : P.mw;
+  P.mp = A.mb[pending ? om0 : rm1];
+  dst = A.fb.p[pending ? ((e & 1) ? oh2 : ow1) : rw1];
   return true;
 }
 
