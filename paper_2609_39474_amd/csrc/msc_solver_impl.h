@@ -2096,7 +2096,7 @@ class Solver : public SolverBase {
     }
     if (F.nparts > kFusedParts) {
       // many sweep blocks: fold the partials once instead of in every block
-      hipLaunchKernelGGL(k_presum<0>, dim3(1), dim3(256), 0, st, (const double*)partials, F.nparts, presum);
+      hipLaunchKernelGGL(k_presum<0>, dim3(1), dim3(256), 0, st, F.partials, F.nparts, presum);
       MSC_HIPCK(hipGetLastError());
       F.partials = presum;
       F.nparts = 1;
