@@ -25,6 +25,35 @@
 
 namespace msc {
 
+// sqrt(sum of the grid's partials * inv_count) by the last block to get here, in
+// a fixed order.  Thread 0 of each block has written its partial.
+template <int NT>
+__device__ __forceinline__ void rows_rms(const double* partials, double* rms, unsigned* arrived, double inv_count) {
+  __shared__ double sum[NT];
+  __shared__ int last;
+  const int tid = threadIdx.x, n = gridDim.x;
+  if (tid == 0)
+    last = __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)n - 1;
+  __syncthreads();
+  if (!last) return;  // uniform
+  double acc = 0.0;
+  for (int i = tid; i < n; i += NT)
+    acc += __hip_atomic_load(&partials[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if constexpr (NT % 64 == 0) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+  }
+  sum[tid] = acc;
+  __syncthreads();
+  if (tid == 0) {
+    constexpr int STEP = NT % 64 == 0 ? 64 : 1;
+    double tot = 0.0;
+    for (int i = 0; i < NT; i += STEP) tot += sum[i];
+    *rms = sqrt(tot * inv_count);
+    __hip_atomic_store(arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
 template <class T, class TM, int T2, int MODE>
 __global__ __launch_bounds__(3 * T2) void k_sweep_rows(SweepArgs<T, TM> A) {
   fetch_kernargs<sizeof(A)>();
@@ -203,6 +232,7 @@ __global__ __launch_bounds__(3 * T2) void k_sweep_rows(SweepArgs<T, TM> A) {
       for (int i = 0; i < NRED; ++i) acc += red[i];
       A.partials[blockIdx.x] = acc;
     }
+    if (MODE == SW_DTS && A.rms) rows_rms<3 * T2>(A.partials, A.rms, A.arrived, A.inv_count);
     if (A.fuse_rows) row_spectrum<T2>(A.spec, N0, A.NBr, fbuf, tid, x0, tw);
   }
 }
