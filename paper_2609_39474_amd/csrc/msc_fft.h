@@ -120,6 +120,7 @@ struct RowsShape {
 template <class L, class T, class CT, class TM, int LG>
 __global__ __launch_bounds__((RowsShape<CT, LG>::NT)) void k_fft2_rows_fwd(Fft2Args<CT, TM> A, AcceptArgs<L, T> Ac,
                                                                          FinishArgs Fin) {
+  fetch_kernargs<sizeof(A) + sizeof(Ac) + sizeof(Fin)>();
   using S = RowsShape<CT, LG>;
   using F = typename S::F;
   constexpr int N = F::N, E = F::E, TPL = F::TPL;
@@ -280,6 +281,7 @@ __global__ __launch_bounds__((ColsShape<CT, LG>::NT)) void k_fft2_cols_solve(Fft
 // imaginary parts), field 2 uses the real part of a second one.
 template <class CT, class TM, int LG>
 __global__ __launch_bounds__((RowsShape<CT, LG>::NT)) void k_fft2_rows_inv(Fft2Args<CT, TM> A) {
+  fetch_kernargs<sizeof(A)>();
   using S = RowsShape<CT, LG>;
   using F = typename S::F;
   constexpr int N = F::N, E = F::E, TPL = F::TPL;
@@ -406,6 +408,7 @@ struct ColShape3 {
 template <class L, class T, class CT, class TM, int LG>
 __global__ __launch_bounds__((ZShape<CT, LG>::NT)) void k_fft3_z_fwd(Fft3Args<CT, TM> A, AcceptArgs<L, T> Ac,
                                                                     FinishArgs Fin) {
+  fetch_kernargs<sizeof(A) + sizeof(Ac) + sizeof(Fin)>();
   using S = ZShape<CT, LG>;
   using F = typename S::F;
   constexpr int N = F::N, E = F::E, TPL = F::TPL;
@@ -478,6 +481,7 @@ struct Lane3 {
 // pass 2: forward along y for a group of j_z columns at one x; keep the band
 template <class CT, class TM, int LG>
 __global__ __launch_bounds__((ColShape3<CT, LG>::NT)) void k_fft3_y_fwd(Fft3Args<CT, TM> A) {
+  fetch_kernargs<sizeof(A)>();
   using S = ColShape3<CT, LG>;
   using F = typename S::F;
   constexpr int N = F::N, E = F::E, TPL = F::TPL;
@@ -509,6 +513,7 @@ __global__ __launch_bounds__((ColShape3<CT, LG>::NT)) void k_fft3_y_fwd(Fft3Args
 // FP64 Schur solve on |j_x| <= N_x/4 (zero elsewhere), inverse; in place
 template <class CT, class TM, int LG>
 __global__ __launch_bounds__((ColShape3<CT, LG>::NT)) void k_fft3_x_solve(Fft3Args<CT, TM> A) {
+  fetch_kernargs<sizeof(A)>();
   using S = ColShape3<CT, LG>;
   using F = typename S::F;
   constexpr int N = F::N, E = F::E, TPL = F::TPL, CW = S::CW;
@@ -570,6 +575,7 @@ __global__ __launch_bounds__((ColShape3<CT, LG>::NT)) void k_fft3_x_solve(Fft3Ar
 // pass 4: inverse along y from the band to every y, for a group of j_z at x
 template <class CT, class TM, int LG>
 __global__ __launch_bounds__((ColShape3<CT, LG>::NT)) void k_fft3_y_inv(Fft3Args<CT, TM> A) {
+  fetch_kernargs<sizeof(A)>();
   using S = ColShape3<CT, LG>;
   using F = typename S::F;
   constexpr int N = F::N, E = F::E, TPL = F::TPL;
@@ -600,6 +606,7 @@ __global__ __launch_bounds__((ColShape3<CT, LG>::NT)) void k_fft3_y_inv(Fft3Args
 // extension, real part at j_z = 0) to real fields; (0,1) and (2,3) packed
 template <class CT, class TM, int LG>
 __global__ __launch_bounds__((ZShape<CT, LG>::NT)) void k_fft3_z_inv(Fft3Args<CT, TM> A) {
+  fetch_kernargs<sizeof(A)>();
   using S = ZShape<CT, LG>;
   using F = typename S::F;
   constexpr int N = F::N, E = F::E, TPL = F::TPL;

@@ -259,6 +259,7 @@ struct FsRows {
 template <class L, class T, class CT, class TM, int LG>
 __global__ __launch_bounds__((FsRows<CT, LG>::NT)) void k_fs_rows_fwd(FsArgs<T, CT, TM> A, AcceptArgs<L, T> Ac,
                                                                      FinishArgs Fin) {
+  fetch_kernargs<sizeof(A) + sizeof(Ac) + sizeof(Fin)>();
   using S = FsRows<CT, LG>;
   using F = typename S::F;
   constexpr int Q = L::Q, N = F::N, E = F::E, TPL = F::TPL;
@@ -336,6 +337,7 @@ __device__ __forceinline__ void fs_wavevector(const TA& A, int jx, int jy, cpx<C
 // registers allow two wavefronts per SIMD.
 template <class L, class T, class CT, class TM, int LG>
 __global__ __launch_bounds__(320) void k_fs_cols_solve(FsArgs<T, CT, TM> A) {
+  fetch_kernargs<sizeof(A)>();
   using F = LineFft<CT, LG, line_le(LG)>;
   constexpr int Q = L::Q, N = F::N, E = F::E, TPL = F::TPL, LPB = 320 / TPL;
   __shared__ cpx<CT> lds[Q * N];
@@ -412,6 +414,7 @@ __global__ __launch_bounds__(64) void k_fs_solve_k(FsArgs<T, CT, TM> A) {
 // real) and f <- f_T + (df - r) in place in the sweep's output buffer.
 template <class L, class T, class CT, class TM, int LG>
 __global__ __launch_bounds__((FsRows<CT, LG>::NT)) void k_fs_rows_inv(FsArgs<T, CT, TM> A) {
+  fetch_kernargs<sizeof(A)>();
   using S = FsRows<CT, LG>;
   using F = typename S::F;
   constexpr int Q = L::Q, N = F::N, E = F::E, TPL = F::TPL;

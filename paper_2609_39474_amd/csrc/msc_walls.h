@@ -314,6 +314,7 @@ __device__ __forceinline__ void wall_Lu(const WallArgs& A, const cpx<double>* bu
 template <int LGY, class VT>
 __global__ __launch_bounds__(512) void k_wall_orth(WallArgs A, VT* V, int j, const double* hcol, const double* src,
                                                   double scale0) {
+  fetch_kernargs<sizeof(A)>();
   constexpr int T2 = 1 << LGY;
   __shared__ double vrow[9 * T2];
   __shared__ cpx<double> buf[2 * T2];
@@ -399,6 +400,7 @@ __global__ __launch_bounds__(512) void k_wall_orth(WallArgs A, VT* V, int j, con
 // (only if converged), 2 always.
 template <int LGX>
 __global__ __launch_bounds__(256) void k_wall_cols(WallArgs A, int run_on) {
+  fetch_kernargs<sizeof(A)>();
   constexpr int N = 1 << LGX;
   using F = LineFft<double, LGX, 2>;
   __shared__ cpx<double> lds[3 * N];
@@ -484,6 +486,7 @@ __device__ __forceinline__ void wall_row_dots(const WallArgs& A, const VT* V, in
 // its dot products with V_0 .. V_j and itself.
 template <int LGY, class VT>
 __global__ __launch_bounds__(512) void k_wall_rows(WallArgs A, const VT* V, int j) {
+  fetch_kernargs<sizeof(A)>();
   constexpr int T2 = 1 << LGY;
   __shared__ cpx<double> buf[6 * T2];
   __shared__ double wrow[9 * T2];
