@@ -363,8 +363,9 @@ msc_status msc_set_tuning(msc_ctx* c, int32_t key, int32_t value);
  * The caller keeps ownership of every buffer.
  *
  * Device memory of its own: the per-block partial sums of r^2 live in a
- * fixed array of 65536 doubles (512 KiB) that each GPU holds from the first
- * call on it until the process ends; grids with more sweep blocks than that
+ * fixed array of 65536 doubles (512 KiB, and 2 KiB of counters for grids whose
+ * sweep forms R itself) that each GPU holds from the first call on it until
+ * the process ends; grids with more sweep blocks than that
  * (far beyond N = 16384^2 in 2D) return MSC_ERR_INVALID_ARG.  Every call on
  * one GPU uses that one array, so calls that overlap in time on one GPU (other
  * streams, other threads) race and must be serialised by the caller.
