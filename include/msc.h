@@ -63,8 +63,9 @@ typedef enum msc_corrector {
    * rest for the case's omega+-, a); each inner iteration solves
    * [I - Z(k) J] df^ = r^ on all Q fields and every wavevector and sets
    * f <- f + df, with the raw-residual test of Algorithm 1.  D2Q9 only, FP64
-   * or FP32 storage, extents up to 512 (FP32) / 256 (FP64); J in closed
-   * form (the paper forms it by a forward difference of step 1e-7). */
+   * or FP32 storage, x extent up to 512 (FP32) / 256 (FP64), y extent up to
+   * 1024 / 512; J in closed form (the paper forms it by a forward difference
+   * of step 1e-7). */
   MSC_CORRECTOR_FULL_SYMBOL = 2,
   /* Wall-bounded kinetic correction (Sec. 3.3, Algorithm 2) for
    * MSC_BOUNDARY_CAVITY: each inner iteration solves (I - L) df = r with
@@ -76,7 +77,8 @@ typedef enum msc_corrector {
    * system by restarted GMRES preconditioned with the periodic full-symbol
    * inverse at rest (the paper factors it with a sparse direct solver), to
    * the relative residual krylov_tol.  D2Q9, omega+ = omega- = 1 (Eq.
-   * wall-G holds there), FP64 storage, extents up to 256. */
+   * wall-G holds there), FP64 storage, x extent up to 256, y extent up to
+   * 512. */
   MSC_CORRECTOR_WALL_KINETIC = 3
 } msc_corrector;
 
@@ -171,8 +173,8 @@ msc_status msc_params_default(msc_params* p, int32_t lattice, int32_t n, double 
  * with the shadow corrector for a grid larger than the transform kernels
  * support (2D: x extent up to 2048 in FP32 and 1024 in FP64, y extent up to
  * 4096 and 2048; 3D: every extent up to 2048 and 1024), and with the
- * full-symbol corrector outside D2Q9, FP64/FP32 storage and extents up to
- * 512 (FP32) / 256 (FP64).  *out is owned by the library until msc_free. */
+ * full-symbol and wall correctors outside the lattice, storage and extents
+ * given with them above.  *out is owned by the library until msc_free. */
 msc_status msc_init(const msc_params* p, const double* phat0, const double* u0, msc_ctx** out);
 
 /* Advance nsteps physical steps by Algorithm 1 (or Picard with

@@ -244,13 +244,17 @@ __device__ inline void fs_solve(const double* kpi, double (*y)[2], double a, dou
 }
 
 // Row passes: the (Q + 1)/2 packed lines of one row per block (of more rows
-// where one row's lines would not fill the wavefronts).
+// where one row's lines would not fill the wavefronts).  Eight elements per
+// thread from 512 on: the five lines of 1024 are 640 threads (1280 with four).
 template <class CT, int LG>
 struct FsRows {
-  using F = LineFft<CT, LG, line_le(LG)>;
-  static_assert(F::WAVE, "lines of at most 512");
+  using F = LineFft<CT, LG, LG <= 8 ? 2 : 3>;
   static constexpr int NL = 5, R = F::TPL >= 32 ? 1 : 32 / F::TPL;
   static constexpr int LINES = NL * R, NT = (LINES * F::TPL + 63) / 64 * 64;
+  // lines longer than a wavefront's meet at barriers, in two buffers: then
+  // every thread of the block has a line
+  static constexpr int LDS = LINES * F::N * (F::WAVE ? 1 : 2);
+  static_assert(NT <= 1024 && (F::WAVE || (R == 1 && NT == LINES * F::TPL)), "one block per row");
 };
 
 // Pass 1: forward transform along y of the Q residual rows of each x
@@ -264,7 +268,7 @@ __global__ __launch_bounds__((FsRows<CT, LG>::NT)) void k_fs_rows_fwd(FsArgs<T, 
   using F = typename S::F;
   constexpr int Q = L::Q, N = F::N, E = F::E, TPL = F::TPL;
   static_assert((Q + 1) / 2 == S::NL, "packed lines of a row");
-  __shared__ cpx<CT> lds[S::LINES * N];
+  __shared__ cpx<CT> lds[S::LDS];
   const int line = threadIdx.x / TPL, t = threadIdx.x & (TPL - 1);
   const int p = line % S::NL, x = blockIdx.x * S::R + line / S::NL;
   cpx<CT> w[F::NTW], v[E];
@@ -289,11 +293,16 @@ __global__ __launch_bounds__((FsRows<CT, LG>::NT)) void k_fs_rows_fwd(FsArgs<T, 
     const int64_t s = s0 + t + i * TPL;
     v[i] = {(CT)A.r[(2 * p) * NS + s], two ? (CT)A.r[(2 * p + 1) * NS + s] : (CT)0};
   }
-  cpx<CT>* ln = lds + line * N;
-  F::template run<-1>(v, t, ln, ln, w);
+  cpx<CT>* a = lds + line * N;
+  cpx<CT>* b = F::WAVE ? a : a + S::LDS / 2;
+  F::template run<-1>(v, t, a, b, w);
+  cpx<CT>* ln = (F::NX & 1) ? b : a;
 #pragma unroll
   for (int i = 0; i < E; ++i) ln[t + i * TPL] = v[i];
-  wave_fence();
+  if constexpr (F::WAVE)
+    wave_fence();
+  else
+    __syncthreads();
   const int64_t FS = Spec2<CT>::field(A.Nx, A.NH);
   auto store = [&](int j, cpx<CT> z) {
     const int64_t o = 2 * p * FS + Spec2<CT>::at(x, j, A.Nx);
@@ -418,7 +427,7 @@ __global__ __launch_bounds__((FsRows<CT, LG>::NT)) void k_fs_rows_inv(FsArgs<T, 
   using S = FsRows<CT, LG>;
   using F = typename S::F;
   constexpr int Q = L::Q, N = F::N, E = F::E, TPL = F::TPL;
-  __shared__ cpx<CT> lds[S::LINES * N];
+  __shared__ cpx<CT> lds[S::LDS];
   const int line = threadIdx.x / TPL, t = threadIdx.x & (TPL - 1);
   const int p = line % S::NL, x = blockIdx.x * S::R + line / S::NL;
   cpx<CT> w[F::NTW], v[E];
@@ -445,8 +454,8 @@ __global__ __launch_bounds__((FsRows<CT, LG>::NT)) void k_fs_rows_inv(FsArgs<T, 
     }
     v[i] = {a0.x - a1.y, a0.y + a1.x};  // pack a0 + i a1
   }
-  cpx<CT>* ln = lds + line * N;
-  F::template run<+1>(v, t, ln, ln, w);
+  cpx<CT>* a = lds + line * N;
+  F::template run<+1>(v, t, a, F::WAVE ? a : a + S::LDS / 2, w);
   const int64_t NS = (int64_t)A.Nx * N, s0 = (int64_t)x * N;
 #pragma unroll
   for (int i = 0; i < E; ++i) {

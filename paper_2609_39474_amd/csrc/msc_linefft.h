@@ -20,10 +20,12 @@
 #pragma once
 
 #include <cmath>
+#include <string>
 #include <type_traits>
 #include <vector>
 
 #include "msc_cpx.h"
+#include "msc_solver.h"
 
 namespace msc {
 
@@ -180,13 +182,28 @@ constexpr int ilog2c(int n) { return n <= 1 ? 0 : 1 + ilog2c(n / 2); }
 // 1024 does not (radix 4 on four wavefronts 1.27, radix 8 on two 1.83 us).
 constexpr int line_le(int lg) { return (lg <= 8 || lg == 10) ? 2 : 3; }
 
-// f(integral_constant<int, lg>) for LO <= lg <= HI
+// log2 of the longest lines that each family of passes is instantiated for, CT
+// the transforms' real type.  The corrector's support tests and the launches
+// both go by these, so that an extent that is accepted has its passes.
+template <class CT>
+struct LineMax {
+  static constexpr int W = sizeof(CT) == 8 ? 1 : 0;
+  static constexpr int rows2 = 12 - W, cols2 = 11 - W;     // 2D shadow passes (along y, along x)
+  static constexpr int line3 = 11 - W;                     // 3D shadow passes (every axis)
+  static constexpr int fs_rows = 10 - W, fs_cols = 9 - W;  // full symbol
+  static constexpr int wall_rows = 9, wall_cols = 8;       // wall corrector (FP64)
+};
+
+// f(integral_constant<int, lg>) for LO <= lg <= HI; a length outside that range
+// has no pass, which is an error of the caller's and no launch left out
 template <int LO, int HI, class F>
 void with_lg(int lg, F&& f) {
   if (lg == LO)
     f(std::integral_constant<int, LO>{});
   else if constexpr (LO < HI)
     with_lg<LO + 1, HI>(lg, f);
+  else
+    throw DeviceError{hipErrorInvalidValue, "no transform pass for lines of 2^" + std::to_string(lg) + " elements"};
 }
 
 // An axis's table on the host: the N roots exp(-2 pi i j / N), then the

@@ -93,12 +93,12 @@ class Solver : public SolverBase {
       }
       if (wallkin() && !wall_supported()) {
         last_error = "the wall-kinetic corrector needs the D2Q9 cavity, FP64 storage, tau+ = tau- = 1 and "
-                     "extents up to 256";
+                     "extents up to 256 x 512";
         return MSC_ERR_UNSUPPORTED;
       }
       if (fullsym() && !fs_supported()) {
-        last_error = "the full-symbol corrector needs D2Q9 with FP64 or FP32 storage and its transforms "
-                     "in LDS (N_x, N_y <= 512 FP32 / 256 FP64 per line pass)";
+        last_error = "the full-symbol corrector needs D2Q9 with FP64 or FP32 storage and extents up to "
+                     "256 x 512 (FP64) or 512 x 1024 (FP32)";
         return MSC_ERR_UNSUPPORTED;
       }
       allocate();
@@ -595,8 +595,8 @@ class Solver : public SolverBase {
     const double tol = P.krylov_tol > 0.0 ? P.krylov_tol : 1e-12;
     if (!(beta0 > 0.0) || !std::isfinite(beta0)) return;  // delta = 0
     int& pred = wk_pred[std::min(ell, kWallPred) - 1];
-    with_lg<2, 8>(ilog2(G.N2), [&](auto lgy) {
-      with_lg<2, 8>(ilog2(G.N0), [&](auto lgx) {
+    with_lg<2, LineMax<double>::wall_rows>(ilog2(G.N2), [&](auto lgy) {
+      with_lg<2, LineMax<double>::wall_cols>(ilog2(G.N0), [&](auto lgx) {
         if (tol >= 1e-5)
           wall_solve_t<lgx.value, lgy.value, float>(rhs, beta0, fT, tol, pred);
         else
@@ -860,7 +860,7 @@ class Solver : public SolverBase {
                      std::to_string(records.size()) + ")";
         return MSC_ERR_INVALID_ARG;
       }
-      if (P.corrector == MSC_CORRECTOR_SHADOW && !fft_fits(sizeof(cpx<double>))) {
+      if (P.corrector == MSC_CORRECTOR_SHADOW && !fft_fits<double>()) {
         last_error = "the FP64 transforms of the adjoint correction do not fit this grid size";
         return MSC_ERR_UNSUPPORTED;
       }
@@ -1170,20 +1170,18 @@ class Solver : public SolverBase {
   bool walls() const { return P.boundary == MSC_BOUNDARY_CAVITY; }
   bool wall_supported() const {
     return D == 2 && std::is_same<T, double>::value && walls() && P.tau_plus == 1.0 && P.tau_minus == 1.0 &&
-           fs_supported();
+           ilog2(G.N2) <= LineMax<double>::wall_rows && ilog2(G.N0) <= LineMax<double>::wall_cols;
   }
-  // the full-symbol passes at their minimum block shape: one row of
-  // (Q+1)/2 packed lines, one column of Q lines, each with its LDS ping-pong
-  bool fs_supported(size_t c = sizeof(cpx<CT>)) const {
-    if (D != 2 || DV) return false;
-    return (size_t)2 * ((Q + 1) / 2) * G.N2 * c <= 131072 && (size_t)2 * Q * G.N0 * c <= 131072;
+  bool fs_supported() const {
+    return D == 2 && !DV && ilog2(G.N2) <= LineMax<CT>::fs_rows && ilog2(G.N0) <= LineMax<CT>::fs_cols;
   }
 
-  // LDS of the transform passes at their minimum block shape
-  bool fft_fits(size_t c = sizeof(cpx<CT>)) const {
-    if (D == 2) return (size_t)4 * G.N2 * c <= 131072 && (size_t)6 * G.N0 * c <= 131072;
-    const int Nmax = std::max(G.n[0], std::max(G.n[1], G.n[2]));
-    return (size_t)4 * G.n[2] * c <= 131072 && (size_t)8 * Nmax * c <= 131072;
+  // the shadow correction's passes, in the context's precision or (the
+  // adjoint's) in FP64
+  template <class CX = CT>
+  bool fft_fits() const {
+    if (D == 2) return ilog2(G.N2) <= LineMax<CX>::rows2 && ilog2(G.N0) <= LineMax<CX>::cols2;
+    return ilog2(std::max(G.n[0], std::max(G.n[1], G.n[2]))) <= LineMax<CX>::line3;
   }
 
   // The context's buffers: the small ones share one device allocation (256-byte
@@ -2215,11 +2213,11 @@ class Solver : public SolverBase {
       F.inv_ns = 1.0 / (double)G.NS;
       F.fb = fb;
       F.out = out;
-      constexpr int LM = sizeof(CT) == 8 ? 8 : 9;  // the longest lines that fit (fs_supported)
+      constexpr int LX = LineMax<CT>::fs_cols, LY = LineMax<CT>::fs_rows;
       if (head) {
         const AcceptArgs<L, T> acc = Ac ? *Ac : AcceptArgs<L, T>{};
         const FinishArgs fin = Fin ? *Fin : FinishArgs{};
-        with_lg<2, LM>(ilog2(G.N2), [&](auto lg) {
+        with_lg<2, LY>(ilog2(G.N2), [&](auto lg) {
           using S = FsRows<CT, lg.value>;
           hipLaunchKernelGGL((k_fs_rows_fwd<L, T, CT, TM, lg.value>), dim3((G.N0 + S::R - 1) / S::R), dim3(S::NT), 0,
                              st, F, acc, fin);
@@ -2231,7 +2229,7 @@ class Solver : public SolverBase {
         // iteration; at N_x <= 256 the extra launches cost more than the
         // parallelism gains)
         const bool split = (tune.fs_split == 1) || (tune.fs_split == 0 && G.N0 >= 512);
-        with_lg<2, LM>(ilog2(G.N0), [&](auto lg) {
+        with_lg<2, LX>(ilog2(G.N0), [&](auto lg) {
           if (split) {
             constexpr int LPB = 256 / LineFft<CT, lg.value, line_le(lg.value)>::TPL;
             const int lgrid = pad8((Q * F.NH + LPB - 1) / LPB);  // XCD-aware order
@@ -2245,7 +2243,7 @@ class Solver : public SolverBase {
           }
         });
         MSC_HIPCK(hipGetLastError());
-        with_lg<2, LM>(ilog2(G.N2), [&](auto lg) {
+        with_lg<2, LY>(ilog2(G.N2), [&](auto lg) {
           using S = FsRows<CT, lg.value>;
           hipLaunchKernelGGL((k_fs_rows_inv<L, T, CT, TM, lg.value>), dim3((G.N0 + S::R - 1) / S::R), dim3(S::NT), 0,
                              st, F);
@@ -2292,8 +2290,7 @@ class Solver : public SolverBase {
       F.a = a;
       F.nu = nu;
       F.inv_ns = 1.0 / (double)G.NS;
-      // the longest lines whose transforms fit (fft_fits)
-      constexpr int LX = sizeof(CX) == 8 ? 10 : 11, LY = LX + 1;
+      constexpr int LX = LineMax<CX>::cols2, LY = LineMax<CX>::rows2;
       if (!rows_in_sweep)
         with_lg<2, LY>(ilog2(G.N2), [&](auto lg) {
           using S = RowsShape<CX, lg.value>;
@@ -2334,7 +2331,7 @@ class Solver : public SolverBase {
       F.a = a;
       F.nu = nu;
       F.inv_ns = 1.0 / (double)G.NS;
-      constexpr int LM = sizeof(CX) == 8 ? 10 : 11;  // the longest lines that fit (fft_fits)
+      constexpr int LM = LineMax<CX>::line3;
       auto col_grid = [&](int planes, int cw) { return dim3(pad8(planes * ((F.NBz + cw - 1) / cw))); };
       // z passes: the forward one (which decides) at most one block per
       // resident slot, each looping over pencil groups

@@ -177,12 +177,17 @@ __global__ __launch_bounds__(256) void k_axpy_multi(double* __restrict__ w, cons
     w[t] = comb_all<true, VT>(w[t], V, stride, nv, coef, t);
 }
 
+// Lines along y: each in one wavefront (eight elements per thread at 512).
+template <int LGY>
+using WallLine = LineFft<double, LGY, line_le(LGY)>;
+
 // Forward row transforms of P v for the row whose nine populations are in
 // vrow (9 x T2): two packed lines, half spectrum j_y <= N_y/2.
 template <int LGY>
 __device__ __forceinline__ void wall_rows_fwd(const WallArgs& A, const double* vrow, cpx<double>* buf, int x) {
   constexpr int T2 = 1 << LGY;
-  using F = LineFft<double, LGY, 2>;
+  using F = WallLine<LGY>;
+  static_assert(F::WAVE, "lines of at most 512");
   for (int y = threadIdx.x; y < T2; y += blockDim.x) {
     double M[3] = {0.0, 0.0, 0.0};
 #pragma unroll
@@ -198,15 +203,15 @@ __device__ __forceinline__ void wall_rows_fwd(const WallArgs& A, const double* v
   __syncthreads();
   if ((int)threadIdx.x >= 2 * F::TPL) return;
   const int line = threadIdx.x / F::TPL, t = threadIdx.x & (F::TPL - 1);
-  cpx<double> w[F::NTW], v[4];
+  cpx<double> w[F::NTW], v[F::E];
   F::load_tw(A.twy, t, w);
   cpx<double>* ln = buf + line * T2;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) v[i] = ln[t + i * F::TPL];
+  for (int i = 0; i < F::E; ++i) v[i] = ln[t + i * F::TPL];
   wave_fence();
   F::template run<-1>(v, t, ln, ln, w);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) ln[t + i * F::TPL] = v[i];
+  for (int i = 0; i < F::E; ++i) ln[t + i * F::TPL] = v[i];
   wave_fence();
   const int64_t FS = Spec2<double>::field(A.Nx, T2 / 2 + 1);
   auto store = [&](int j, cpx<double> z) {
@@ -219,9 +224,9 @@ __device__ __forceinline__ void wall_rows_fwd(const WallArgs& A, const double* v
     A.spec[o] = {0.5 * (z.x + zc.x), 0.5 * (z.y - zc.y)};
     A.spec[FS + o] = {0.5 * (z.y + zc.y), 0.5 * (zc.x - z.x)};
   };
-  store(t, v[0]);
-  store(t + F::TPL, v[1]);
-  if (t == 0) store(T2 / 2, v[2]);
+#pragma unroll
+  for (int i = 0; i < F::E / 2; ++i) store(t + i * F::TPL, v[i]);
+  if (t == 0) store(T2 / 2, v[F::E / 2]);
 }
 
 // z on the three rows x - 1, x, x + 1: line 2p holds z_0 + i z_1 of row
@@ -229,15 +234,16 @@ __device__ __forceinline__ void wall_rows_fwd(const WallArgs& A, const double* v
 template <int LGY>
 __device__ __forceinline__ void wall_rows_inv(const WallArgs& A, cpx<double>* buf, int x) {
   constexpr int T2 = 1 << LGY;
-  using F = LineFft<double, LGY, 2>;
+  using F = WallLine<LGY>;
+  static_assert(F::WAVE, "lines of at most 512");
   const int line = threadIdx.x / F::TPL, t = threadIdx.x & (F::TPL - 1);
   if (line < 6) {
-    cpx<double> w[F::NTW], v[4];
+    cpx<double> w[F::NTW], v[F::E];
     F::load_tw(A.twy, t, w);
     const int64_t FS = Spec2<double>::field(A.Nx, T2 / 2 + 1);
     const int xl = (x - 1 + (line >> 1)) & (A.Nx - 1);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < F::E; ++i) {
       const int j = t + i * F::TPL;
       const bool lower = 2 * j <= T2, real_term = j == 0 || 2 * j == T2;
       const int64_t o = Spec2<double>::at(xl, lower ? j : T2 - j, A.Nx);
@@ -255,7 +261,7 @@ __device__ __forceinline__ void wall_rows_inv(const WallArgs& A, cpx<double>* bu
     cpx<double>* ln = buf + line * T2;
     F::template run<+1>(v, t, ln, ln, w);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) ln[t + i * F::TPL] = v[i];
+    for (int i = 0; i < F::E; ++i) ln[t + i * F::TPL] = v[i];
   }
   __syncthreads();
 }
