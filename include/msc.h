@@ -185,7 +185,10 @@ msc_status msc_init(const msc_params* p, const double* phat0, const double* u0, 
  * (Sec. 3.1).  stats: NULL or an array of nsteps records (caller-owned).
  * Errors: MSC_ERR_NONCONVERGED (K_max reached) or MSC_ERR_NONFINITE: the
  * context stays at the last accepted step and stats are filled up to and
- * including the failing step.  MSC_ERR_INVALID_ARG for nsteps < 0. */
+ * including the failing step.  MSC_ERR_OUT_OF_MEMORY while recording, where
+ * the memory ends before the call does: the context stays at the last accepted
+ * step, with the records and stats of the steps up to it.
+ * MSC_ERR_INVALID_ARG for nsteps < 0. */
 msc_status msc_bdf2_step(msc_ctx* c, int32_t nsteps, msc_step_stats* stats);
 
 /* Advance nsteps lattice steps of the source-free TRT map (the sweep with

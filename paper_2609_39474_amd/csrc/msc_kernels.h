@@ -100,6 +100,19 @@ __device__ inline void accept_sites(const AcceptArgs<L, T>& A, int64_t s0, int64
   }
 }
 
+// m = (P f + h/2) / (1 + a/2) (Eq. macro-reconstruct) of an accepted state, as
+// accept_sites forms it.
+template <class L, class T>
+__global__ __launch_bounds__(256) void k_reconstruct(const T* __restrict__ f, const double* __restrict__ h,
+                                                     double inv1pa2, double* __restrict__ m, int64_t NS) {
+  for (int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; s < NS; s += (int64_t)gridDim.x * blockDim.x) {
+    double M[4];
+    site_moments<L, T>(f, NS, s, M);
+#pragma unroll
+    for (int b = 0; b <= L::D; ++b) m[b * NS + s] = (M[b] + 0.5 * h[b * NS + s]) * inv1pa2;
+  }
+}
+
 // Without the shadow corrector: the acceptance decision and, if accepted,
 // the reconstruction.
 template <class L, class T>

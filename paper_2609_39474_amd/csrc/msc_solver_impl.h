@@ -7,6 +7,7 @@
 #include <cstring>
 #include <initializer_list>
 #include <memory>
+#include <new>
 #include <string>
 #include <type_traits>
 #include <vector>
@@ -168,7 +169,24 @@ class Solver : public SolverBase {
       int64_t bdf_dev = bdf_count;
       msc_status rc = MSC_OK;
       while (n_dev < n_end) {
-        const int B = std::min(batch, n_end - n_dev);
+        int B = std::min(batch, n_end - n_dev);
+        if (recording) {
+          // only steps that have a record are enqueued
+          B = reserve_records(n_dev, bdf_dev, B, stat_base, n_end - n_dev);
+          if (B == 0) {
+            // (a step that still iterates has one: the march stands at an
+            // accepted step, whose m^n was left to the step that does not come)
+            if (n_dev > stat_base) reconstruct(n_dev, bdf_dev);
+            copy_stats(out, stat_base, n_dev - stat_base);
+            recs.accept(n_dev - stat_base);
+            n_next = n_dev;
+            bdf_count = bdf_dev;
+            if (use_sched) sched_pos += n_dev - stat_base;
+            sync();
+            last_error = "device allocation failed for the record of physical step " + std::to_string(n_dev);
+            return MSC_ERR_OUT_OF_MEMORY;
+          }
+        }
         for (int i = 0; i < B; ++i) {
           const int n = n_dev + i;
           const int64_t bc = bdf_dev + i;
@@ -197,7 +215,7 @@ class Solver : public SolverBase {
           CkptArgs<T>* rec = nullptr;
           CkptArgs<T> ck;
           if (recording && ell0 == 1) {
-            ck = checkpoint_args(n, bc, order, recs.base + (size_t)(n - stat_base), n_end - n);
+            ck = checkpoint_args(n, recs.base + (size_t)(n - stat_base));
             rec = &ck;
           }
           // the decision on this step's last sweep goes with the next step's
@@ -1063,6 +1081,7 @@ class Solver : public SolverBase {
     std::shared_ptr<void> mem;  // the slab it lies in
     const T* f[3];              // f^n, f^{n-1}, f^{n-2} (storage format), null beyond the order
     const double* h;            // history term h_q
+    int own;                    // how many of the last of these are its own (f^n always is)
     int64_t bc;                 // BDF steps accepted before this step
     int K;                      // inner sweeps at acceptance; 0 while the step is in flight
     float sig;                  // deviation-storage scale of the populations
@@ -1103,6 +1122,9 @@ class Solver : public SolverBase {
     } catch (const OomError&) {
       last_error = "device allocation failed";
       return MSC_ERR_OUT_OF_MEMORY;
+    } catch (const std::bad_alloc&) {
+      last_error = "host allocation failed";
+      return MSC_ERR_OUT_OF_MEMORY;
     }
   }
 
@@ -1122,16 +1144,22 @@ class Solver : public SolverBase {
     MSC_HIPCK(hipStreamWaitEvent(st, order_ev, 0));
   }
 
+  // (the failed call's error is not one of the launches that follow)
+  [[noreturn]] static void out_of_memory() {
+    (void)hipGetLastError();
+    throw OomError{};
+  }
+
   void* dalloc(size_t bytes) {
     void* p = nullptr;
     if (bytes == 0) bytes = 1;
     if (P.alloc_fn) {
       p = P.alloc_fn(bytes, P.alloc_user);
-      if (!p) throw OomError{};
+      if (!p) out_of_memory();
       after_default_stream();
     } else {
       hipError_t e = hipMalloc(&p, bytes);
-      if (e == hipErrorOutOfMemory) throw OomError{};
+      if (e == hipErrorOutOfMemory) out_of_memory();
       if (e != hipSuccess) throw DeviceError{e, std::string("hipMalloc: ") + hipGetErrorString(e)};
     }
     return p;
@@ -1514,52 +1542,90 @@ class Solver : public SolverBase {
   }
 
   // ------------------------------------------------------ adjoint pieces --
-  // Arguments of the record of step n, the idx-th in the list, in a slab with
-  // room for it (allocated for up to 32 of the call's remaining steps).  A step
+  // Records for the steps n0 .. n0 + B - 1 (bc0 accepted steps before the first)
+  // of the call that began at step base, made before any of them is enqueued;
+  // how many have one (fewer than B, or none, where the memory ends).  A step
   // enqueued again, because the march had not reached it, has its record.
-  CkptArgs<T> checkpoint_args(int n, int64_t bc, int order, size_t idx, int remaining) {
+  int reserve_records(int n0, int64_t bc0, int B, int base, int remaining) {
+    const int max_order = (P.extrap_states == 0) ? 2 : P.extrap_states - 1;
+    for (int i = 0; i < B; ++i) {
+      const size_t idx = rec_base + (size_t)(n0 + i - base);
+      if (idx < records.size()) continue;
+      try {
+        make_record(bc0 + i, (int)std::min<int64_t>(bc0 + i, max_order), remaining - i);
+      } catch (const OomError&) {
+        return i;
+      } catch (const std::bad_alloc&) {
+        return i;
+      }
+    }
+    return B;
+  }
+
+  // older populations that the record of a trial of that order keeps itself:
+  // the others are f^n of the call's earlier records
+  int own_populations(size_t idx, int order) const {
+    return std::max(order - (int)std::min<size_t>(idx - rec_base, 2), 0);
+  }
+
+  // The next record of the list, in a slab with room for it: for up to 32 of
+  // the call's remaining steps, or for as many fewer as there is memory.
+  void make_record(int64_t bc, int order, int remaining) {
     const size_t fq = pop_bytes(), fm = sizeof(double) * (size_t)(D + 1) * G.NS;
-    const size_t first = rec_base;
-    const int back = (int)std::min<size_t>(idx - first, 2);  // earlier records of this call
-    const int own = std::max(order - back, 0);               // older populations it keeps itself
-    if (idx == records.size()) {
-      const size_t need = fm + (size_t)(1 + own) * fq;
-      if (!slab || slab_at + need > slab_end) {
+    const size_t idx = records.size();
+    const int own = own_populations(idx, order);
+    const size_t need = fm + (size_t)(1 + own) * fq;
+    if (!slab || slab_at + need > slab_end) {
+      for (int steps = std::min(remaining, 32);; steps /= 2) {
         // (a call's second record may keep an older population as well)
-        const size_t bytes = need + (size_t)(std::min(remaining, 32) - 1) * (fm + fq) + (idx == first ? fq : 0);
-        slab = std::shared_ptr<void>(dalloc(bytes), [this](void* p) { dfree(p); });
+        const size_t bytes = need + (size_t)(steps - 1) * (fm + fq) + (steps > 1 && idx == rec_base ? fq : 0);
+        try {
+          slab = std::shared_ptr<void>(dalloc(bytes), [this](void* p) { dfree(p); });
+        } catch (const OomError&) {
+          if (steps == 1) throw;
+          continue;
+        }
         slab_at = (char*)slab.get();
         slab_end = slab_at + bytes;
+        break;
       }
-      Record r{};
-      r.mem = slab;
-      auto take = [&](size_t bytes) {
-        char* p = slab_at;
-        slab_at += bytes;
-        return p;
-      };
-      for (int i = 0; i <= order; ++i) {
-        if (i == 0 || i > back)
-          r.f[i] = (const T*)take(fq);
-        else
-          r.f[i] = records[idx - 1].f[i - 1];
-      }
-      r.h = (const double*)take(fm);
-      r.bc = bc;
-      r.sig = sig;
-      records.push_back(std::move(r));
     }
+    Record r{};
+    r.mem = slab;
+    char* at = slab_at;
+    auto take = [&](size_t bytes) {
+      char* p = at;
+      at += bytes;
+      return p;
+    };
+    for (int i = 0; i <= order; ++i) {
+      if (i == 0 || i > order - own)
+        r.f[i] = (const T*)take(fq);
+      else
+        r.f[i] = records[idx - 1].f[i - 1];
+    }
+    r.own = own;
+    r.h = (const double*)take(fm);
+    r.bc = bc;
+    r.sig = sig;
+    records.push_back(std::move(r));
+    slab_at = at;
+  }
+
+  // Arguments of the copy into the record of step n, the idx-th in the list.
+  CkptArgs<T> checkpoint_args(int n, size_t idx) {
     const Record& r = records[idx];
     CkptArgs<T> A{};
     A.ctl = ctl;
     A.n = n;
     A.fb = fb;
     A.h = h_of(n);
-    for (int i = 0; i < 3; ++i)
-      if (r.f[i] && (i == 0 || i > back)) A.rf[i] = (uint4*)r.f[i];
+    const int last = r.f[2] ? 2 : (r.f[1] ? 1 : 0);
+    for (int i = 0; i <= last; ++i)
+      if (i == 0 || i > last - r.own) A.rf[i] = (uint4*)r.f[i];
     A.rh = (uint4*)r.h;
-    A.nf = (int64_t)(fq / sizeof(uint4));
-    A.nh = (int64_t)(fm / sizeof(uint4));
+    A.nf = (int64_t)(pop_bytes() / sizeof(uint4));
+    A.nh = (int64_t)(sizeof(double) * (size_t)(D + 1) * G.NS / sizeof(uint4));
     return A;
   }
 
@@ -2167,6 +2233,17 @@ class Solver : public SolverBase {
     Ac.a = a;
     Ac.inv1pa2 = 1.0 / (1.0 + a / 2.0);
     return Ac;
+  }
+
+  // m^n of step n, the next to run, where step n - 1 (bc - 1 accepted before it)
+  // left it to a step that is not enqueued.
+  void reconstruct(int n, int64_t bc) {
+    const Roles& ro = ctl_h->roles[n & 1];
+    const double a = (bc - 1 == 0) ? 1.0 / P.dt : 3.0 / (2.0 * P.dt);
+    hipLaunchKernelGGL((k_reconstruct<L, T>), dim3(ew_grid()), dim3(256), 0, st,
+                       (const T*)fb.p[ro.slot_hist[0]], (const double*)h_of(n - 1), 1.0 / (1.0 + a / 2.0),
+                       mb[ro.slot_m[0]], G.NS);
+    MSC_HIPCK(hipGetLastError());
   }
 
   // Blocks of a kernel that the device holds at once (occupancy per CU times
