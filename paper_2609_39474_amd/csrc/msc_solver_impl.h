@@ -165,6 +165,8 @@ class Solver : public SolverBase {
         MSC_HIPCK(hipMemcpyAsync(sched_d, K.data(), sizeof(int32_t) * nsteps, hipMemcpyHostToDevice, st));
         sched_host_view = K;
       }
+      if (replayed && !use_sched) batch = 1;
+      replayed = use_sched;
       int n_dev = n_next, ell_dev = 1;
       int64_t bdf_dev = bdf_count;
       msc_status rc = MSC_OK;
@@ -854,6 +856,7 @@ class Solver : public SolverBase {
       sync();
       lazy_history = false;
       bdf_count = bc;
+      batch = 1;
       return MSC_OK;
     });
   }
@@ -1041,7 +1044,11 @@ class Solver : public SolverBase {
   int n_next = 0;
   int64_t bdf_count = 0;
   bool lazy_history = false;  // complete_history has copies to make
-  int batch = 1;  // physical steps enqueued before the next synchronisation
+  // physical steps enqueued before the next synchronisation: one where the
+  // steps' counts are not to be expected from those before (a new state, a free
+  // march behind a replay), twice as many after each accepted batch
+  int batch = 1;
+  bool replayed = false;  // the last march replayed a schedule
   int last_iters = 4;
   float sig = 1.0f;  // scale of FP16 deviation storage (unused otherwise)
 
@@ -1427,6 +1434,7 @@ class Solver : public SolverBase {
                        check ? partials : nullptr);
     MSC_HIPCK(hipGetLastError());
     bdf_count = 0;
+    batch = 1;
     lazy_history = true;
     return check ? sum_partials_host(grid) : 0.0;
   }

@@ -1,0 +1,66 @@
+"""How many steps a call of the march enqueues before it first waits, seen in
+the trace of its launches: one step where what the context has learnt about its
+steps does not hold."""
+import numpy as np
+import pytest
+
+from paper_2609_39474_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+N = 32
+
+
+@pytest.fixture(scope="module")
+def M():
+    from paper_2609_39474_amd import msc
+    msc.lib()
+    return msc
+
+
+def _launches(fn):
+    """Kernel launches before each wait of the host in fn()."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+
+    torch.zeros(1, device="cuda")
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as p:
+        fn()
+    out, n = [], 0
+    for e in sorted(p.events(), key=lambda e: e.time_range.start):
+        if "LaunchKernel" in e.name:
+            n += 1
+        elif e.name == "hipStreamSynchronize":
+            out.append(n)
+            n = 0
+    assert out, "no calls traced"
+    return out
+
+
+def _marched(M, schedule):
+    """A context that has marched 63 steps by a schedule (batches of up to 32)."""
+    p0, u0 = W.random_field_2d(N, 0.1 / 6.0 / N, seed=8)
+    s = M.Solver(M.make_params(2, N, dt=4.0, eps=1e-8, extrap_states=1), p0, u0)
+    s.set_schedule(schedule)
+    s.bdf2_step(63)
+    return s
+
+
+@pytest.mark.parametrize("what", ["nothing", "set_populations", "set_state", "explicit_step", "schedule ends"])
+def test_first_batch(M, what):
+    s = _marched(M, [3] * (63 if what == "schedule ends" else 70))
+    if what == "set_populations":
+        s.set_populations(s.populations())
+    elif what == "set_state":
+        s.set_state(*s.get_state())
+    elif what == "explicit_step":
+        s.explicit_step(2)
+    waits = _launches(lambda: s.bdf2_step(7))
+    s.close()
+    print("launches before each wait:", what, waits, flush=True)
+    # a step of three sweeps: the sweeps, two corrections, the decision
+    if what == "nothing":
+        assert waits[0] >= 7 * 5 and len(waits) == 1
+    else:
+        assert waits[0] <= 8
