@@ -171,7 +171,8 @@ class Solver : public SolverBase {
       int64_t bdf_dev = bdf_count;
       msc_status rc = MSC_OK;
       while (n_dev < n_end) {
-        int B = std::min(batch, n_end - n_dev);
+        // (key 2 may have been lowered since the batch grew)
+        int B = std::min({batch, std::max(1, tune.batch_steps), n_end - n_dev});
         if (recording) {
           // only steps that have a record are enqueued
           B = reserve_records(n_dev, bdf_dev, B, stat_base, n_end - n_dev);

@@ -64,3 +64,14 @@ def test_first_batch(M, what):
         assert waits[0] >= 7 * 5 and len(waits) == 1
     else:
         assert waits[0] <= 8
+
+
+@pytest.mark.parametrize("steps,want", [(1, 7), (3, 3), (64, 1)])
+def test_steps_per_wait_from_the_next_call(M, steps, want):
+    """Tuning key 2 holds from the next call, also below what was reached."""
+    s = _marched(M, [3] * 70)
+    s.set_tuning(2, steps)
+    waits = _launches(lambda: s.bdf2_step(7))
+    s.close()
+    print("launches before each wait: key 2 =", steps, waits, flush=True)
+    assert len(waits) == want
