@@ -77,10 +77,7 @@ class Solver : public SolverBase {
       sync();
       choose_sweep();
       ensure_partials(sweep_grid_max());
-      if (gexec) (void)hipGraphExecDestroy(gexec);
-      if (graph) (void)hipGraphDestroy(graph);
-      gexec = nullptr;
-      graph = nullptr;
+      for (auto& g : graphs) drop_graph(g);
       return MSC_OK;
     });
   }
@@ -1053,16 +1050,20 @@ class Solver : public SolverBase {
   int last_iters = 4;
   float sig = 1.0f;  // scale of FP16 deviation storage (unused otherwise)
 
-  // explicit-march graph cache
-  hipGraphExec_t gexec = nullptr;
-  hipGraph_t graph = nullptr;
-  // key of the captured explicit-march graph: the sweep arguments it holds by
-  // value (buffers, chunk length and the deviation-storage scale)
-  const T* g_a = nullptr;
-  const T* g_b = nullptr;
-  int g_chunk = 0;
-  float g_sig = 0.0f;
-  int g_kind = 0;
+  // Captured chunks of the explicit march, each with the arguments it holds by
+  // value (buffers, chunk length, the deviation-storage scale).  Two: behind a
+  // chunk an odd number of launches from one buffer to the other exchanges
+  // them, so that calls of one length alternate between both orders.
+  struct ExplicitGraph {
+    hipGraphExec_t exec;
+    hipGraph_t graph;
+    const T* a;
+    const T* b;  // null where the march is in place
+    int chunk, kind;
+    float sig;
+  };
+  ExplicitGraph graphs[2] = {};
+  int graph_used = 0;  // the one used last
 
   // kernel timing
   bool timing = false;
@@ -1307,10 +1308,7 @@ class Solver : public SolverBase {
   }
 
   void release() {
-    if (gexec) (void)hipGraphExecDestroy(gexec);
-    if (graph) (void)hipGraphDestroy(graph);
-    gexec = nullptr;
-    graph = nullptr;
+    for (auto& g : graphs) drop_graph(g);
     for (auto& e : ev_live) {
       (void)hipEventDestroy(e.a);
       (void)hipEventDestroy(e.b);
@@ -2052,12 +2050,24 @@ class Solver : public SolverBase {
     }
   }
 
+  static void drop_graph(ExplicitGraph& g) {
+    if (g.exec) (void)hipGraphExecDestroy(g.exec);
+    if (g.graph) (void)hipGraphDestroy(g.graph);
+    g = ExplicitGraph{};
+  }
+
   hipGraphExec_t explicit_graph(T* A, T* B, int chunk, int kind) {
-    if (gexec && g_a == A && g_b == B && g_chunk == chunk && g_sig == sig && g_kind == kind) return gexec;
-    if (gexec) (void)hipGraphExecDestroy(gexec);
-    if (graph) (void)hipGraphDestroy(graph);
-    gexec = nullptr;
-    graph = nullptr;
+    const T* other = kind == EX_AA ? nullptr : B;
+    for (int i = 0; i < 2; ++i) {
+      const ExplicitGraph& g = graphs[i];
+      if (g.exec && g.a == A && g.b == other && g.chunk == chunk && g.sig == sig && g.kind == kind) {
+        graph_used = i;
+        return g.exec;
+      }
+    }
+    graph_used ^= 1;
+    ExplicitGraph& g = graphs[graph_used];
+    drop_graph(g);
     sync();
     MSC_HIPCK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
     SweepArgs<T, TM> S = sweep_args(0.0);
@@ -2080,14 +2090,14 @@ class Solver : public SolverBase {
       else
         launch_sweep_d3<T, TM>(tile_id, SW_EXPLICIT, S, sweep_grid(SW_EXPLICIT), st);
     }
-    MSC_HIPCK(hipStreamEndCapture(st, &graph));
-    MSC_HIPCK(hipGraphInstantiate(&gexec, graph, nullptr, nullptr, 0));
-    g_a = A;
-    g_b = B;
-    g_chunk = chunk;
-    g_sig = sig;
-    g_kind = kind;
-    return gexec;
+    MSC_HIPCK(hipStreamEndCapture(st, &g.graph));
+    MSC_HIPCK(hipGraphInstantiate(&g.exec, g.graph, nullptr, nullptr, 0));
+    g.a = A;
+    g.b = other;
+    g.chunk = chunk;
+    g.sig = sig;
+    g.kind = kind;
+    return g.exec;
   }
 
   // --------------------------------------------------- Algorithm 1 pieces --

@@ -75,3 +75,40 @@ def test_steps_per_wait_from_the_next_call(M, steps, want):
     s.close()
     print("launches before each wait: key 2 =", steps, waits, flush=True)
     assert len(waits) == want
+
+
+@pytest.mark.parametrize("shape,steps,storage,aa", [((128, 128), 72, "fp64", 1), ((512, 512), 100, "fp32", 1),
+                                                    ((16, 16), 65, "fp64", 1), ((16, 16, 16), 65, "fp32", 1),
+                                                    ((64, 64), 65, "fp64", 0), ((64, 64), 65, "fp16dev", 1)])
+def test_explicit_chunks_captured_once(M, shape, steps, storage, aa):
+    """Calls of one length whose launches behind the graph's chunks exchange the
+    two buffers: after two calls no chunk is captured again, and the state is
+    that of one call without graphs."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+
+    d, n = len(shape), min(shape)
+    p0, u0 = (W.random_field_2d(n, 0.1 / 6.0 / n, seed=8) if d == 2 else
+              (np.zeros(shape), W.random_perturbation_3d(n, 0.1 / 6.0 / n, seed=8, jmax=3)))
+    s, r = [M.Solver(M.make_params(d, n, dt=4.0, eps=1e-8, storage=storage), p0, u0) for _ in range(2)]
+    s.set_tuning(10, aa)
+    s.explicit_step(steps)
+    s.explicit_step(steps)
+    with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as p:
+        for _ in range(4):
+            s.explicit_step(steps)
+    names = [e.name for e in p.events()]
+    print("explicit", shape, steps, storage, "graph launches", names.count("hipGraphLaunch"), "captures",
+          names.count("hipGraphInstantiate"), flush=True)
+    assert names.count("hipGraphLaunch") >= 4 and names.count("hipGraphInstantiate") == 0
+    r.set_tuning(10, aa)
+    r.set_tuning(4, 0)
+    r.explicit_step(6 * steps)
+    np.testing.assert_array_equal(s.populations(), r.populations())
+    # marches between explicit calls, in other buffers
+    for x in (s, r):
+        x.bdf2_step(1)
+        x.explicit_step(steps)
+    np.testing.assert_array_equal(s.populations(), r.populations())
+    s.close()
+    r.close()
