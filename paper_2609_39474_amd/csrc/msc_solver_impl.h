@@ -2222,10 +2222,13 @@ class Solver : public SolverBase {
     enqueue_transform<CT, TM>(ctl, n, ell, a, nullptr, false, B, nullptr, fuse_rows, fuse_inv);
   }
 
-  // The decision left to the next enqueued sweep (ctl null: none).
+  // The decision left to the next enqueued sweep (ctl null: none).  Each of its
+  // blocks then sums the partials, so not on grids whose partials are folded
+  // first (more than 4096 one-row blocks, which only key 1 asks for).
   FinishArgs handed_on{};
   bool merge_ok() const {
-    return D == 2 && tile.T1 == 1 && tile.T2 == G.N2 && tile.T2 >= 64 && strip_setup == 1 && !fullsym() && !wallkin();
+    return D == 2 && tile.T1 == 1 && tile.T2 == G.N2 && tile.T2 >= 64 && strip_setup == 1 &&
+           sweep_grid_max() <= kFusedParts && !fullsym() && !wallkin();
   }
 
   // partial sums of r^2 of step n's sweeps: a step's first sweep writes its own

@@ -112,3 +112,24 @@ def test_explicit_chunks_captured_once(M, shape, steps, storage, aa):
     np.testing.assert_array_equal(s.populations(), r.populations())
     s.close()
     r.close()
+
+
+@pytest.mark.parametrize("rows,folded", [(4096, False), (8192, True)])
+def test_many_partials_are_folded_first(M, rows, folded):
+    """One-row blocks on more than 4096 rows (tuning key 1): one launch folds the
+    partials of each sweep, not every block of the next step's first sweep."""
+    from torch.profiler import ProfilerActivity, profile
+
+    shape = (rows, 64)
+    p0, u0 = W.random_field_2d(64, 1.0 / 6.0 / 64, seed=8)
+    p = M.make_params(2, 64, dt=2.0, eps=1e-3, corrector="picard")
+    p.n[0] = rows
+    s = M.Solver(p, np.tile(p0, (rows // 64, 1)), np.tile(u0, (1, rows // 64, 1)))
+    s.set_tuning(1, 1)
+    s.bdf2_step(31)
+    with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as pr:
+        st = s.bdf2_step(8)[1]
+    s.close()
+    n = sum("k_presum" in e.name for e in pr.events())
+    print("many partials", shape, "counts", [x["iters"] for x in st], "folds", n, flush=True)
+    assert n >= sum(x["iters"] for x in st) if folded else n == 0
