@@ -368,12 +368,14 @@ msc_status msc_set_tuning(msc_ctx* c, int32_t key, int32_t value);
  * The caller keeps ownership of every buffer.
  *
  * Device memory of its own: the per-block partial sums of r^2 live in a
- * fixed array of 65536 doubles (512 KiB, and 2 KiB of counters for grids whose
- * sweep forms R itself) that each GPU holds from the first call on it until
+ * fixed array of 65536 doubles (512 KiB, and a counter for grids whose sweep
+ * forms R itself) that each GPU holds from the first call on it until
  * the process ends; grids with more sweep blocks than that
  * (far beyond N = 16384^2 in 2D) return MSC_ERR_INVALID_ARG.  Every call on
  * one GPU uses that one array, so calls that overlap in time on one GPU (other
- * streams, other threads) race and must be serialised by the caller.
+ * streams, other threads, replays of captured calls) race and must be
+ * serialised by the caller; the R of calls that do overlap is undefined, that
+ * of later calls is not.
  *
  * Errors: MSC_ERR_INVALID_ARG (unknown lattice, extents, rates, a, storage,
  * NULL buffers other than R, or a grid beyond the fixed array);

@@ -6,7 +6,6 @@
 // every call on a GPU.
 #include <hip/hip_runtime.h>
 
-#include <atomic>
 #include <cmath>
 #include <mutex>
 
@@ -16,37 +15,56 @@
 namespace {
 // one FP64 partial sum of r^2 per sweep block
 constexpr int kScratchDoubles = 65536;
-// behind them, arrival counters of sweeps that form R in the same launch (zero
-// between calls).  Calls take them in turn, so that calls overlapping in time
-// against the contract still leave every counter at zero.
-constexpr int kCounters = 256;
+// behind them (on a line of its own), the arrival counter of sweeps that form R
+// in the same launch
+constexpr int kCounterDoubles = 16;
 }  // namespace
 
 // Held by each GPU the library runs on until the process ends.  Host code
 // never passes this name to a kernel: it takes the array's device address per
 // GPU (scratch_on_device) and passes that.
-static __device__ __align__(256) double scratch[kScratchDoubles + kCounters];
+static __device__ __align__(256) double scratch[kScratchDoubles + kCounterDoubles];
 
 namespace {
 
 constexpr int kMaxDevices = 64;
-std::mutex scratch_mu;
-std::atomic<unsigned> counter_turn{0};
-double* scratch_dev[kMaxDevices] = {};
 
-// Device address of this GPU's copy of the scratch array, looked up once per
-// device with that device current.
-msc_status scratch_on_device(double** out) {
+// One GPU's scratch array.  Every block of a sweep that forms R itself adds one to
+// the counter and nothing ever takes from it: a launch is told what it has
+// counted before, `arrivals`, so that calls overlapping in time against the
+// contract (whose R, like their partial sums, are then mixed up) leave the right
+// count to the calls after them.  The lock is held over such a launch: launches
+// reach a stream in the order of their counts.
+struct Scratch {
+  std::mutex mu;
+  double* at = nullptr;
+  unsigned arrivals = 0;
+};
+Scratch scratch_dev[kMaxDevices];
+
+// This GPU's scratch array, its device address looked up once per device with
+// that device current.
+msc_status scratch_on_device(Scratch** out) {
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return MSC_ERR_DEVICE;
-  std::lock_guard<std::mutex> lk(scratch_mu);
-  if (!scratch_dev[dev]) {
+  Scratch& s = scratch_dev[dev];
+  std::lock_guard<std::mutex> lk(s.mu);
+  if (!s.at) {
     void* p = nullptr;
     if (hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)) != hipSuccess || !p) return MSC_ERR_DEVICE;
-    scratch_dev[dev] = static_cast<double*>(p);
+    s.at = static_cast<double*>(p);
   }
-  *out = scratch_dev[dev];
+  *out = &s;
   return MSC_OK;
+}
+
+// A captured launch runs as often as its graph, which no count can know: it
+// leaves R to a launch of its own.
+bool captured(hipStream_t st) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
 }
 
 // R = sqrt(sum of the partials / (Q N_sites)) in one block, folded in a fixed
@@ -107,9 +125,10 @@ msc_status run(const int* n, double tau_plus, double tau_minus, const T* f, cons
   const int strip = sweep_strip_for<L, T>(tile, N0, N1, N2, 0, wide ? STRIP_DUAL_WIDE : STRIP_DUAL);
   const int64_t grid = (int64_t)(N1 / tile.T1) * (N2 / tile.T2) * (N0 / strip);
   if (grid > kScratchDoubles) return MSC_ERR_INVALID_ARG;
-  double* parts = nullptr;
-  const msc_status ss = scratch_on_device(&parts);
+  Scratch* scr = nullptr;
+  const msc_status ss = scratch_on_device(&scr);
   if (ss != MSC_OK) return ss;
+  double* parts = scr->at;
   SweepArgs<T, T> S{};
   S.N0 = N0;
   S.N1 = N1;
@@ -133,9 +152,12 @@ msc_status run(const int* n, double tau_plus, double tau_minus, const T* f, cons
   S.isig = 1.0f;
   // one row per block (k_sweep_rows): R in the same launch (N = 64 FP64: 10.6 ->
   // 8.0 us per call; the second launch was 2.2 us of it on the GPU)
-  if (R && L::D == 2 && strip == 1 && tile.T1 == 1 && tile.T2 == N2) {
+  std::unique_lock<std::mutex> in_order(scr->mu, std::defer_lock);
+  if (R && L::D == 2 && strip == 1 && tile.T1 == 1 && tile.T2 == N2 && !captured(st)) {
+    in_order.lock();
     S.rms = R;
-    S.arrived = reinterpret_cast<unsigned*>(parts + kScratchDoubles + counter_turn.fetch_add(1) % kCounters);
+    S.arrived = reinterpret_cast<unsigned*>(parts + kScratchDoubles);
+    S.arrivals = scr->arrivals;
     S.inv_count = 1.0 / ((double)L::Q * (double)NS);
   }
   if constexpr (L::D == 3) {
@@ -147,6 +169,7 @@ msc_status run(const int* n, double tau_plus, double tau_minus, const T* f, cons
     launch_dts<T>(L::D, tile_id, S, (int)grid, st);
   }
   if (hipGetLastError() != hipSuccess) return MSC_ERR_DEVICE;
+  if (S.rms) scr->arrivals += (unsigned)grid;
   if (R && !S.rms) {
     hipLaunchKernelGGL(k_noalloc_rms, dim3(1), dim3(256), 0, st, parts, (int)grid, 1.0 / ((double)L::Q * (double)NS),
                        R);

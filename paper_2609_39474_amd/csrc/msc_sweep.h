@@ -273,10 +273,12 @@ struct SweepArgs {
   // the previous step's last enqueued sweep (see merged_sources)
   int merge;
   FinishArgs fin;
-  // k_sweep_rows: the RMS raw residual out (or null), formed by the block that
-  // raises *arrived (0 before and after) to the grid's size
+  // k_sweep_rows: the RMS raw residual out (or null), formed by the last block to
+  // add itself to *arrived, which counts the blocks of such launches, `arrivals`
+  // (modulo 2^32) before this one
   double* rms;
   unsigned* arrived;
+  unsigned arrivals;
   double inv_count;  // 1/(Q N_sites)
   // D2Q9 lid-driven cavity: wall rows after streaming (every mode)
   int walls;

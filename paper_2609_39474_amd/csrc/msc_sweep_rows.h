@@ -28,12 +28,13 @@ namespace msc {
 // sqrt(sum of the grid's partials * inv_count) by the last block to get here, in
 // a fixed order.  Thread 0 of each block has written its partial.
 template <int NT>
-__device__ __forceinline__ void rows_rms(const double* partials, double* rms, unsigned* arrived, double inv_count) {
+__device__ __forceinline__ void rows_rms(const double* partials, double* rms, unsigned* arrived, unsigned before,
+                                         double inv_count) {
   __shared__ double sum[NT];
   __shared__ int last;
   const int tid = threadIdx.x, n = gridDim.x;
   if (tid == 0)
-    last = __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)n - 1;
+    last = __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) - before == (unsigned)n - 1;
   __syncthreads();
   if (!last) return;  // uniform
   double acc = 0.0;
@@ -50,7 +51,6 @@ __device__ __forceinline__ void rows_rms(const double* partials, double* rms, un
     double tot = 0.0;
     for (int i = 0; i < NT; i += STEP) tot += sum[i];
     *rms = sqrt(tot * inv_count);
-    __hip_atomic_store(arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
@@ -232,7 +232,7 @@ __global__ __launch_bounds__(3 * T2) void k_sweep_rows(SweepArgs<T, TM> A) {
       for (int i = 0; i < NRED; ++i) acc += red[i];
       A.partials[blockIdx.x] = acc;
     }
-    if (MODE == SW_DTS && A.rms) rows_rms<3 * T2>(A.partials, A.rms, A.arrived, A.inv_count);
+    if (MODE == SW_DTS && A.rms) rows_rms<3 * T2>(A.partials, A.rms, A.arrived, A.arrivals, A.inv_count);
     if (A.fuse_rows) row_spectrum<T2>(A.spec, N0, A.NBr, fbuf, tid, x0, tw);
   }
 }
