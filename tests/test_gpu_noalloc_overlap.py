@@ -12,7 +12,7 @@ from test_gpu_noalloc_rms import _device, _reference
 pytestmark = pytest.mark.gpu
 
 A = 3.0 / 128.0
-SHAPES = [(512, 64), (256, 64), (64, 128), (1024, 16)]
+SHAPES = [(128, 64), (64, 64), (64, 256), (512, 64)]
 
 
 @pytest.fixture(scope="module")
@@ -113,3 +113,22 @@ def test_threads_in_turn(M, sets):
     for t in th:
         t.join()
     assert not bad, bad[:4]
+
+
+@pytest.mark.parametrize("shape,one", [((128, 64), True), ((128, 16), True), ((64, 256), True), ((128, 128), False),
+                                       ((256, 64), False), ((512, 16), False)])
+def test_few_blocks_form_the_residual_themselves(M, shape, one):
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+
+    d = _device(shape, "fp64", 80)
+    want = _reference(M, shape, "fp64", d[0], d[1], A)
+    R = torch.zeros(1, dtype=torch.float64, device="cuda")
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as p:
+        _call(M, shape, d, R, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+    n = sum("k_noalloc_rms" in e.name for e in p.events())
+    print("residual", shape, "launches of its own", n, flush=True)
+    assert (n == 0) == one
+    np.testing.assert_allclose(R.item(), want, rtol=1e-13, atol=0)
