@@ -776,7 +776,11 @@ __device__ __forceinline__ void row_spectrum(cpx<CT>* __restrict__ spec, int N0,
   if (t == 0) store(F::TPL, v[1]);
 }
 
-template <class L, class T, class TM, int NT, int T1, int T2, int MODE>
+// ROWS: with the forward row transform of P r (2D, tiles that span whole rows).
+// An instantiation of its own: the transform's line and twiddles in registers
+// spilled 23 to 26 of the FP32 dual-time sweeps' 128 (N = 4096 FP32: 360.9 us per
+// sweep where a run-time switch chose, 356.4 without it).
+template <class L, class T, class TM, int NT, int T1, int T2, int MODE, bool ROWS>
 __global__ __launch_bounds__(NT, (sweep_min_waves<L, T, MODE, T1>())) void k_sweep(SweepArgs<T, TM> A) {
   using CT = typename CompT<T>::type;
   constexpr int Q = L::Q, D = L::D;
@@ -790,9 +794,9 @@ __global__ __launch_bounds__(NT, (sweep_min_waves<L, T, MODE, T1>())) void k_swe
   // post-collision values travel through LDS in the storage type, or FP32
   // for deviation storage (they are full populations there)
   using LT = typename std::conditional<PopDev<T>::value, float, T>::type;
-  constexpr bool ROWFFT = (L::D == 2 && T1 == 1 && MODE != SW_EXPLICIT && NT == T2);
+  static_assert(!ROWS || (L::D == 2 && T1 == 1 && MODE != SW_EXPLICIT && NT == T2), "tiles that span whole rows");
   static_assert(MODE != SW_DTS_LIFT_ROWS, "k_sweep_rows serves the inverse row transforms");
-  __shared__ cpx<CT> fbuf[ROWFFT ? 2 * T2 : 1];
+  __shared__ cpx<CT> fbuf[ROWS ? 2 * T2 : 1];
   constexpr bool TWOBAR = sweep_two_barriers<L, T>();
   constexpr int DP = ring_depth(0, TWOBAR), DZ = ring_depth(1, TWOBAR), DM = ring_depth(2, TWOBAR);
   __shared__ LT ldsP[DP][NGP][NI];
@@ -1089,7 +1093,7 @@ __global__ __launch_bounds__(NT, (sweep_min_waves<L, T, MODE, T1>())) void k_swe
           for (int bb = 0; bb <= D; ++bb) pr[bb] = (CT)((double)Mq[bb] - mprev[j][bb]);
         }
         if (MODE != SW_EXPLICIT) {
-          if (ROWFFT && A.fuse_rows) {
+          if (ROWS) {
             // the row of P r (fields 0 and 1 packed in one complex line, field 2 in a second)
             fbuf[i2] = {pr[0], pr[1]};
             fbuf[T2 + i2] = {pr[2], (CT)0};
@@ -1099,15 +1103,13 @@ __global__ __launch_bounds__(NT, (sweep_min_waves<L, T, MODE, T1>())) void k_swe
           }
         }
       }
-      if constexpr (ROWFFT) {
-        if (A.fuse_rows) {
-          __syncthreads();
-          using F = LineFft<CT, ilog2c(T2), 2>;
-          cpx<CT> tw[F::NTW];
-          F::load_tw(A.twr, tid & (F::TPL - 1), tw);
-          row_spectrum<T2>(A.spec, N0, A.NBr, fbuf, tid, xd, tw);
-          __syncthreads();  // fbuf is refilled by the next plane
-        }
+      if constexpr (ROWS) {
+        __syncthreads();
+        using F = LineFft<CT, ilog2c(T2), 2>;
+        cpx<CT> tw[F::NTW];
+        F::load_tw(A.twr, tid & (F::TPL - 1), tw);
+        row_spectrum<T2>(A.spec, N0, A.NBr, fbuf, tid, xd, tw);
+        __syncthreads();  // fbuf is refilled by the next plane
       }
     }
     if constexpr (TWOBAR) __syncthreads();  // the rings' slots are refilled next step

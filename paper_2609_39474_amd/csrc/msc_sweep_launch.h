@@ -62,10 +62,15 @@ void launch_sweep_mode(const SweepArgs<T, TM>& A, int grid, hipStream_t st, hipE
       return;
     }
   }
-  if constexpr (MODE == SW_DTS_LIFT_ROWS)
+  if constexpr (MODE == SW_DTS_LIFT_ROWS) {
     throw DeviceError{hipErrorInvalidValue, "inverse-row lift requested for strips of several planes"};
-  else
-    go(k_sweep<L, T, TM, NT, T1, T2, MODE>, NT);
+  } else if (!A.fuse_rows) {
+    go(k_sweep<L, T, TM, NT, T1, T2, MODE, false>, NT);
+  } else if constexpr (L::D == 2 && T1 == 1 && NT == T2 && (setup_mode(MODE) || MODE == SW_DTS_LIFT)) {
+    go(k_sweep<L, T, TM, NT, T1, T2, MODE, true>, NT);
+  } else {
+    throw DeviceError{hipErrorInvalidValue, "row transforms requested of a sweep without them"};
+  }
 }
 
 template <class L, class T, class TM, int NT, int T1, int T2>
