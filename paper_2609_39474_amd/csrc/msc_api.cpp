@@ -291,13 +291,13 @@ msc_status msc_kernel_time(msc_ctx* c, int32_t kind, double* seconds, int64_t* l
 // 1 = planes per strip, 2 = physical steps enqueued per host synchronisation,
 // 3 = speculative extra iterations, 4 = graph capture of explicit chunks,
 // 5 = tile by table index, 6 = row transforms inside the sweep (0/1/2),
-// 7 / 8 = pencils / columns per block of the 3D transform passes, 9 = the
-// full-symbol column pass split in three kernels (0 auto / 1 split / 2 fused),
+// 7 / 8 = accepted and without effect, 9 = the full-symbol column pass split in
+// three kernels (0 auto / 1 split / 2 fused),
 // 10 = the in-place (AA) explicit march, 11 = the 512-thread D3Q19 dual-time
 // tile at N_z = 128, 12 = the last lift sweep enqueued for a step leaving P r
 // out (3D, and 2D with row passes of their own; formed afterwards only if the
 // step goes on).
-// Keys 0, 1 and 5-8 re-pick the launch shapes at once; the others apply
+// Keys 0, 1 and from 5 on re-pick the launch shapes at once; the others apply
 // from the next call.
 msc_status msc_set_tuning(msc_ctx* c, int32_t key, int32_t value) {
   if (!c) return MSC_ERR_INVALID_ARG;

@@ -81,8 +81,12 @@ __device__ __forceinline__ void fetch_kernargs() {
 // Algorithm 1 runs as a sequence of kernels enqueued ahead by the host.  The
 // device decides acceptance; every kernel launched for (step n, iteration
 // ell) first reads one 64-bit phase word and returns at once unless the march
-// is exactly at that point.  Only single-block kernels write the phase, so
-// the word every block of a grid reads is the same.
+// is exactly at that point.  Block 0 of a deciding grid writes the word and, on
+// acceptance, the next step's roles, while other blocks of that grid may not
+// have read either yet: each of them has to take the word as it was and the
+// word with this very decision recorded alike, and may read only the roles of
+// the step that is being decided (finish_end, merged_sources).  Every other
+// grid reads a word that does not change under it.
 enum : uint32_t { PH_RUNNING = 1, PH_ACCEPTED = 2, PH_FAILED = 3 };
 
 __host__ __device__ inline uint64_t make_phase(int n, int ell, uint32_t st) {

@@ -1755,7 +1755,6 @@ class Solver : public SolverBase {
     S.wm = wm;
     if (rows) {
       S.fuse_rows = 1;
-      S.lgr = ilog2(G.N2);
       S.NBr = G.N2 / 4 + 1;
       S.spec = adj_spec_of(ell);
       S.twr = adj_x.tw[2];
@@ -2103,8 +2102,9 @@ class Solver : public SolverBase {
   // --------------------------------------------------- Algorithm 1 pieces --
   // One inner iteration of Algorithm 1 for (step n, sweep ell), guarded on the
   // device: the sweep (the first one of a step also forms h_q and the
-  // extrapolated trial), the one-block acceptance test, then either the
-  // reconstruction of m^{n+1} (accepted) or the shadow correction.
+  // extrapolated trial), then one grid whose blocks all take the acceptance
+  // decision, and which goes on with the reconstruction of m^{n+1} (accepted) or
+  // the correction's first pass, and the correction's other passes.
   // last: the final iteration enqueued for this step; its correction is left
   // out (it runs only if the step goes on, and then enqueue_correction_tail
   // supplies it before the next sweep).
@@ -2157,7 +2157,6 @@ class Solver : public SolverBase {
     S.skip_pr = skip_pr ? 1 : 0;
     if (fuse_rows) {
       S.fuse_rows = 1;
-      S.lgr = ilog2(G.N2);
       S.NBr = G.N2 / 4 + 1;
       S.spec = spec_of(ell);
       S.twr = tw[2];

@@ -263,7 +263,7 @@ struct SweepArgs {
   // with the shadow corrector): the band spectrum of P r goes to spec
   // (j <= N_y/4, Spec2 layout, as the first transform pass writes it) instead
   // of P r to Pr
-  int fuse_rows, lgr, NBr;
+  int fuse_rows, NBr;
   cpx<TM>* spec;
   const cpx<TM>* twr;
   // SW_DTS_LIFT_ROWS: the solved band spectrum of the previous correction
@@ -779,7 +779,7 @@ __device__ __forceinline__ void row_spectrum(cpx<CT>* __restrict__ spec, int N0,
 // ROWS: with the forward row transform of P r (2D, tiles that span whole rows).
 // An instantiation of its own: the transform's line and twiddles in registers
 // spilled 23 to 26 of the FP32 dual-time sweeps' 128 (N = 4096 FP32: 360.9 us per
-// sweep where a run-time switch chose, 356.4 without it).
+// sweep where a run-time switch chose, 354.4 now).
 template <class L, class T, class TM, int NT, int T1, int T2, int MODE, bool ROWS>
 __global__ __launch_bounds__(NT, (sweep_min_waves<L, T, MODE, T1>())) void k_sweep(SweepArgs<T, TM> A) {
   using CT = typename CompT<T>::type;
