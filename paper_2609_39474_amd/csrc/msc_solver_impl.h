@@ -638,8 +638,8 @@ class Solver : public SolverBase {
       hipLaunchKernelGGL((k_wall_cols<LGX>), dim3(pad8(G.N2 / 2 + 1)), dim3(256), 0, st, A, run_on);
     };
     auto orth = [&](int j, const double* src, double scale0) {
-      hipLaunchKernelGGL((k_wall_orth<LGY, VT>), dim3(rows + 1), dim3(512), 0, st, A, V, j, (const double*)hcol, src,
-                         scale0);
+      hipLaunchKernelGGL((k_wall_orth<LGY, VT>), dim3(rows + 1), dim3(wall_threads(LGY)), 0, st, A, V, j,
+                         (const double*)hcol, src, scale0);
     };
     double beta = beta0, rel = 0.0;
     int iters = 0;
@@ -653,13 +653,15 @@ class Solver : public SolverBase {
         const int upto = std::min(m, j == 0 ? pred : j + 2);
         for (; j < upto; ++j) {
           cols(0);
-          hipLaunchKernelGGL((k_wall_rows<LGY, VT>), dim3(rows), dim3(512), 0, st, A, (const VT*)V, j);
+          hipLaunchKernelGGL((k_wall_rows<LGY, VT>), dim3(rows), dim3(wall_threads(LGY)), 0, st, A, (const VT*)V,
+                             j);
           if (reorth) {
             hipLaunchKernelGGL(k_gs_first<0>, dim3(1), dim3(1024), 0, st, (const double*)A.part, rows, j + 1, wk_coef,
                                hcol);
             hipLaunchKernelGGL(k_axpy_multi<VT>, dim3(vgrid), dim3(256), 0, st, wk_vc, (const VT*)V, n, j + 1,
                                (const double*)wk_coef, n);
-            hipLaunchKernelGGL((k_wall_dots<LGY, VT>), dim3(rows), dim3(512), 0, st, A, (const VT*)V, j);
+            hipLaunchKernelGGL((k_wall_dots<LGY, VT>), dim3(rows), dim3(wall_threads(LGY)), 0, st, A,
+                               (const VT*)V, j);
           }
           orth(j + 1, nullptr, 0.0);
         }

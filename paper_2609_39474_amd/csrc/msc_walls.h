@@ -177,6 +177,11 @@ __global__ __launch_bounds__(256) void k_axpy_multi(double* __restrict__ w, cons
     w[t] = comb_all<true, VT>(w[t], V, stride, nv, coef, t);
 }
 
+// Threads of the row kernels: on rows of 512 twice as many wavefronts share the
+// basis vectors (256 x 512, tolerance 1e-2: 96 -> 72 us per iteration, with the
+// shorter loops of wall_row_dots).
+constexpr int wall_threads(int lgy) { return lgy <= 8 ? 512 : 1024; }
+
 // Lines along y: each in one wavefront (eight elements per thread at 512).
 template <int LGY>
 using WallLine = LineFft<double, LGY, line_le(LGY)>;
@@ -318,7 +323,7 @@ __device__ __forceinline__ void wall_Lu(const WallArgs& A, const cpx<double>* bu
 // new one zeroes its last entry, g is rotated.  j = 0: v_0 = src scale0, and the
 // cycle's books are opened with g_0 = 1 / scale0.
 template <int LGY, class VT>
-__global__ __launch_bounds__(512) void k_wall_orth(WallArgs A, VT* V, int j, const double* hcol, const double* src,
+__global__ __launch_bounds__(wall_threads(LGY)) void k_wall_orth(WallArgs A, VT* V, int j, const double* hcol, const double* src,
                                                   double scale0) {
   fetch_kernargs<sizeof(A)>();
   constexpr int T2 = 1 << LGY;
@@ -466,20 +471,25 @@ __global__ __launch_bounds__(256) void k_wall_cols(WallArgs A, int run_on) {
 }
 
 // partials of <V_i, w>, i < nv, and of <w, w> (entry nv) over one row of w (9 x
-// T2, in LDS): one wavefront per vector.
+// T2, in LDS): one wavefront per vector, up to 36 of its loads in flight per lane
+// (18 on rows of 512, whose 72 at once spilled 107 registers).
 template <int T2, class VT>
 __device__ __forceinline__ void wall_row_dots(const WallArgs& A, const VT* V, int nv, const double* wrow, int x) {
-  constexpr int PER = (9 * T2 + 63) / 64;
+  constexpr int PER = (9 * T2 + 63) / 64, CH = PER > 36 ? PER / 4 : PER;
+  static_assert(PER % CH == 0 && CH <= 36, "rows of at most 512");
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   for (int i = wv; i <= nv; i += (int)(blockDim.x >> 6)) {
     double acc = 0.0;
     const VT* v = V + (int64_t)i * 9 * A.NS + (int64_t)x * T2;
+#pragma unroll 1
+    for (int q0 = 0; q0 < PER; q0 += CH) {
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int e = lane + 64 * q;
-      if (9 * T2 % 64 == 0 || e < 9 * T2) {
-        const double we = wrow[e];
-        acc += (i < nv ? (double)v[(int64_t)(e / T2) * A.NS + (e & (T2 - 1))] : we) * we;
+      for (int q = 0; q < CH; ++q) {
+        const int e = lane + 64 * (q0 + q);
+        if (9 * T2 % 64 == 0 || e < 9 * T2) {
+          const double we = wrow[e];
+          acc += (i < nv ? (double)v[(int64_t)(e / T2) * A.NS + (e & (T2 - 1))] : we) * we;
+        }
       }
     }
 #pragma unroll
@@ -491,7 +501,7 @@ __device__ __forceinline__ void wall_row_dots(const WallArgs& A, const VT* V, in
 // w = (I - L) M^{-1} v_j on row x, in place of v_j in vc, and the partials of
 // its dot products with V_0 .. V_j and itself.
 template <int LGY, class VT>
-__global__ __launch_bounds__(512) void k_wall_rows(WallArgs A, const VT* V, int j) {
+__global__ __launch_bounds__(wall_threads(LGY)) void k_wall_rows(WallArgs A, const VT* V, int j) {
   fetch_kernargs<sizeof(A)>();
   constexpr int T2 = 1 << LGY;
   __shared__ cpx<double> buf[6 * T2];
@@ -519,7 +529,7 @@ __global__ __launch_bounds__(512) void k_wall_rows(WallArgs A, const VT* V, int 
 
 // The dot products alone (after a first projection).
 template <int LGY, class VT>
-__global__ __launch_bounds__(512) void k_wall_dots(WallArgs A, const VT* V, int j) {
+__global__ __launch_bounds__(wall_threads(LGY)) void k_wall_dots(WallArgs A, const VT* V, int j) {
   constexpr int T2 = 1 << LGY;
   __shared__ double wrow[9 * T2];
   const int x = blockIdx.x;
