@@ -776,12 +776,24 @@ __device__ __forceinline__ void row_spectrum(cpx<CT>* __restrict__ spec, int N0,
   if (t == 0) store(F::TPL, v[1]);
 }
 
+// Most waves per SIMD: two for the D2Q9 sweeps that three would fit since the row
+// transform is an instantiation of its own (FP64 dual-time, FP32 first sweep).  The
+// largest grids' strips are cut into multiples of two blocks per CU; 1024 blocks in
+// waves of 768 leave the second half empty (N = 4096 FP64 647 -> 688 us per sweep
+// with three; grids of up to 512 blocks are the same either way).
+template <class L, class T, int MODE>
+__host__ __device__ constexpr int sweep_max_waves() {
+  return (L::D == 2 && ((MODE == SW_DTS && sizeof(T) == 8) || (MODE == SW_DTS_SETUP1 && sizeof(T) == 4))) ? 2 : 8;
+}
+
 // ROWS: with the forward row transform of P r (2D, tiles that span whole rows).
 // An instantiation of its own: the transform's line and twiddles in registers
 // spilled 23 to 26 of the FP32 dual-time sweeps' 128 (N = 4096 FP32: 360.9 us per
 // sweep where a run-time switch chose, 354.4 now).
 template <class L, class T, class TM, int NT, int T1, int T2, int MODE, bool ROWS>
-__global__ __launch_bounds__(NT, (sweep_min_waves<L, T, MODE, T1>())) void k_sweep(SweepArgs<T, TM> A) {
+__global__ __launch_bounds__(NT)
+    __attribute__((amdgpu_waves_per_eu((sweep_min_waves<L, T, MODE, T1>()), (sweep_max_waves<L, T, MODE>())))) void k_sweep(
+        SweepArgs<T, TM> A) {
   using CT = typename CompT<T>::type;
   constexpr int Q = L::Q, D = L::D;
   constexpr int NI = T1 * T2;
