@@ -7,6 +7,7 @@ import threading
 import numpy as np
 import pytest
 
+from test_gpu_batches import trace
 from test_gpu_noalloc_rms import _device, _reference
 
 pytestmark = pytest.mark.gpu
@@ -119,16 +120,12 @@ def test_threads_in_turn(M, sets):
                                        ((256, 64), False), ((512, 16), False)])
 def test_few_blocks_form_the_residual_themselves(M, shape, one):
     import torch
-    from torch.profiler import ProfilerActivity, profile
 
     d = _device(shape, "fp64", 80)
     want = _reference(M, shape, "fp64", d[0], d[1], A)
     R = torch.zeros(1, dtype=torch.float64, device="cuda")
-    torch.cuda.synchronize()
-    with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as p:
-        _call(M, shape, d, R, torch.cuda.current_stream().cuda_stream)
-        torch.cuda.synchronize()
-    n = sum("k_noalloc_rms" in e.name for e in p.events())
+    ev = trace(lambda: _call(M, shape, d, R, torch.cuda.current_stream().cuda_stream))
+    n = sum("k_noalloc_rms" in e.name for e in ev)
     print("residual", shape, "launches of its own", n, flush=True)
     assert (n == 0) == one
     np.testing.assert_allclose(R.item(), want, rtol=1e-13, atol=0)
