@@ -150,14 +150,14 @@ msc_status run(const int* n, double tau_plus, double tau_minus, const T* f, cons
   S.wm = 1.0 / tau_minus;
   S.sig = 1.0f;
   S.isig = 1.0f;
-  // One row per block (k_sweep_rows) and few blocks: R in the same launch.  The
-  // blocks' arrivals go one after the other, 20 to 30 ns each, against a second
-  // launch of 2 us.  us per call, two launches and one, rows of 64 sites FP64: 32
-  // blocks 7.2 and 4.9, 64 7.2 and 5.2, 128 7.2 and 6.7, 256 7.2 and 9.9, 512 7.2
-  // and 14.2; of 256 sites: 64 blocks 7.2 and 6.4, 128 7.2 and 7.8.
+  // One row per block (k_sweep_rows) and at most 256 blocks: R in the same launch.
+  // The blocks' arrivals go one after the other, 20 to 30 ns each, against a second
+  // launch of 2 us on the GPU and 2.5 us of the caller's time.  us per call from
+  // Python, one launch and two, rows of 64 sites FP64: 128 blocks 7.7 and 10.1, 256
+  // 9.9 and 10.2, 512 14.2 and 10.1; of 256 sites: 128 7.8 and 10.1, 256 11.2 and
+  // 10.1, 512 21.6 and 11.1.
   std::unique_lock<std::mutex> in_order(scr->mu, std::defer_lock);
-  if (R && L::D == 2 && strip == 1 && tile.T1 == 1 && tile.T2 == N2 && grid <= (N2 <= 64 ? 128 : 64) &&
-      !captured(st)) {
+  if (R && L::D == 2 && strip == 1 && tile.T1 == 1 && tile.T2 == N2 && grid <= 256 && !captured(st)) {
     in_order.lock();
     S.rms = R;
     S.arrived = reinterpret_cast<unsigned*>(parts + kScratchDoubles);
